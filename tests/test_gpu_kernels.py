@@ -92,6 +92,44 @@ def test_gemm_bf16x3(M, N, K, accumulate):
     assert np.max(np.abs(dC.cpu().numpy() - exact) / scale) < 2.0 ** -14
 
 
+@pytest.mark.parametrize("precision,M,N,K,lda_pad", [
+    ("fp64", 128, 128, 256, 0),       # K split inside the workgroup: one chunk of 16 per wave and a second
+    ("fp64", 256, 128, 272, 16),      # a ragged chunk count, padded rows
+    ("fp64", 128, 256, 2752, 0),      # many chunks per wave
+    ("fp64", 1024, 1024, 16, 0),      # 64 x 64 tiles, one K tile
+    ("fp64", 1024, 1024, 32, 0),      # two K tiles
+    ("fp64", 1152, 1024, 48, 16),     # three K tiles
+    ("fp64", 3200, 3200, 80, 0),      # 64 x 128 tiles
+    ("fp64", 4096, 2048, 64, 0),      # 128 x 128 tiles
+    ("fp32", 128, 128, 32, 0),        # 64 x 64 tiles, one K tile of the first FP32 group
+    ("fp32", 256, 128, 160, 32),      # a group and one tile
+    ("fp32", 3072, 2816, 192, 0),     # 64 x 128 tiles, a group and two tiles
+    ("fp32", 3072, 2816, 288, 0),     # two groups and one tile
+])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_gemm_tile_variants(precision, M, N, K, lda_pad, accumulate):
+    """Every tile shape the dispatch of the FP64 and FP32 products picks, at
+    the smallest K loops (pipeline prologue and tail) and with padded rows:
+    every element to the rounding of its own sum, K products of 2^-53 (FP64)
+    or a group of 128 in FP32 and one FP32 rounding (2^-24)."""
+    torch = need_gpu()
+    from paper_1911_12954_amd import trg_gemm
+    announce("gemm tile variants", precision, M, N, K, lda_pad, accumulate)
+    dt = torch.float64 if precision == "fp64" else torch.float32
+    npdt = np.float64 if precision == "fp64" else np.float32
+    ld = K + lda_pad
+    A, B, C0 = (random_matrix(r, c, 50 + i).astype(npdt) for i, (r, c) in enumerate([(M, ld), (N, ld), (M, N)]))
+    dA, dB, dC = (torch.from_numpy(x).cuda() for x in (A, B, C0))
+    trg_gemm(precision, dA.data_ptr(), dB.data_ptr(), dC.data_ptr(), M, N, K, ld, ld, N, accumulate,
+             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    A64, B64 = A[:, :K].astype(np.float64), B[:, :K].astype(np.float64)
+    ref = A64 @ B64.T + (C0.astype(np.float64) if accumulate else 0.0)
+    scale = np.abs(A64) @ np.abs(B64).T + (np.abs(C0) if accumulate else 0.0)
+    bound = (K + 2) * 2.0 ** -53 if precision == "fp64" else (min(K, 128) + 2) * 2.0 ** -24
+    assert np.max(np.abs(dC.cpu().numpy() - ref) / scale) < bound
+
+
 def _split3(X):
     """fl32(X) = hi + mid + lo exactly (three bfloat16 planes, round to
     nearest even at each stage), as torch tensors."""
