@@ -13,18 +13,14 @@
 //   FP32   v_mfma_f32_16x16x4_f32   gemm_pipe_kernel: 64 x 128 or 64 x 64 tile,
 //          RB 128 (32 floats, 8 k-steps); the MFMA sums 4 K tiles (128
 //          products) in FP32, the groups are summed in FP64
-//   BF16X3 v_mfma_f32_16x16x32_bf16 256 x 256 tile, eight 128 x 64 waves,
-//          RB 64 (32 bf16 per plane, 1 k-step, three products hi*hi +
-//          hi*lo + lo*hi into one FP32 accumulator), two swizzled stages
-//   BF16X6 v_mfma_f32_16x16x32_bf16 128 x 128 tile, eight 64 x 32 waves,
-//          RB 64, three planes (fl32(a) = hi + mid + lo exactly), six
+//   BF16X3 v_mfma_f32_16x16x32_bf16 gemm_split_kernel, two planes: 256 x 256
+//          tile of eight 128 x 64 waves or 128 x 128 of four 64 x 64; three
+//          products hi*hi + hi*lo + lo*hi into one FP32 accumulator
+//   BF16X6 the same kernel, three planes (fl32(a) = hi + mid + lo exactly): 128
+//          x 128 tile of eight 64 x 32 waves or 64 x 64 of four 32 x 32; six
 //          products hi*hi + hi*mid + mid*hi + mid*mid + hi*lo + lo*hi; the
 //          MFMA sums BF6_FLUSH K tiles in FP32, the groups are summed in
-//          FP64 (FP32-accurate operands and FP64-grade accumulation), two
-//          swizzled stages
-//
-// Two LDS stages: the next tile's global loads are in flight while the
-// current tile feeds the MFMAs (one barrier per tile).
+//          FP64 (FP32-accurate operands and FP64-grade accumulation)
 //
 // Workgroup ids are remapped so that each XCD (ids are dealt round-robin to
 // the 8 XCDs) works on one contiguous range of tiles, walked in groups of
@@ -51,20 +47,10 @@ constexpr int NUM_XCD = 8;
 // FP32 join: K tiles (32 floats each) summed by the MFMA in FP32 before the
 // partial sum is added to the FP64 accumulator
 constexpr uint32_t F32_FLUSH = 4;
-#ifndef TRG_GROUP_M
-#define TRG_GROUP_M 8
-#endif
-constexpr int GROUP_M = TRG_GROUP_M;
+constexpr int GROUP_M = 8;
 
 // BF16X6 join: K tiles (32 elements each) per FP32 group
-#ifndef TRG_BF6_FLUSH
-#define TRG_BF6_FLUSH 4
-#endif
-// BF16X6 join: global -> LDS prefetch distance in K tiles (1 or 2)
-#ifndef TRG_BF6_PF
-#define TRG_BF6_PF 2
-#endif
-constexpr uint32_t BF6_FLUSH = TRG_BF6_FLUSH;
+constexpr int BF6_FLUSH = 4;
 
 template <int PREC> struct Prec;
 template <> struct Prec<0> {  // FP64
@@ -100,6 +86,7 @@ template <> struct Prec<3> {  // BF16 x6
   static constexpr int elem = 2;
 };
 
+template <int GM>
 __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm,
                                    uint32_t &tn) {
   const uint32_t total = tiles_m * tiles_n;
@@ -107,283 +94,15 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
   const uint32_t xcd = wg % NUM_XCD, idx = wg / NUM_XCD;
   const uint32_t per = total / NUM_XCD, rem = total % NUM_XCD;
   const uint32_t w = xcd * per + (xcd < rem ? xcd : rem) + idx;
-  // grouped raster: GROUP_M tile-rows walked column by column
-  const uint32_t group_size = GROUP_M * tiles_n;
+  // grouped raster: GM tile-rows walked column by column
+  const uint32_t group_size = GM * tiles_n;
   const uint32_t group = w / group_size;
-  const uint32_t first_m = group * GROUP_M;
-  const uint32_t gm = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
+  const uint32_t first_m = group * GM;
+  const uint32_t gm = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
   const uint32_t in_group = w % group_size;
   tm = first_m + in_group % gm;
   tn = in_group / gm;
 }
-
-// LDS layout of one operand tile: rows of RB bytes of K.  Padded (SWZ 0):
-// row stride RB + 16.  Swizzled (SWZ 1): row stride RB, and the 16-byte
-// chunk c of row r is stored at chunk c ^ ((r / (256 / RB)) % (RB / 16)).
-// Either way the 16 rows that one lane group reads fall on 16 disjoint
-// 4-bank groups of the 64-bank LDS; with the swizzle, 16 consecutive lanes
-// also store 256 contiguous bytes (no padding, no store conflicts).
-template <int RB, int SWZ>
-__device__ inline int lds_off(int row, int chunk) {
-  if constexpr (SWZ == 0) {
-    return row * (RB + 16) + (chunk << 4);
-  } else {
-    constexpr int CPR = RB / 16, RPL = 256 / RB;
-    return row * RB + ((chunk ^ ((row / RPL) % CPR)) << 4);
-  }
-}
-template <int RB, int SWZ>
-constexpr int lds_stride() { return SWZ ? RB : RB + 16; }
-
-// BM x BN tile per workgroup, WM x WN waves of 64 lanes, K in tiles of RB
-// bytes per row.
-template <int PREC, int BM, int BN, int WM, int WN, int RB, int SWZ, int PF, bool ACCUM>
-__global__ void __launch_bounds__(64 * WM * WN)
-gemm_nt_kernel(const typename Prec<PREC>::in_t *__restrict__ A,
-               const typename Prec<PREC>::in_t *__restrict__ Bt,
-               typename Prec<PREC>::out_t *__restrict__ C, uint32_t tiles_m, uint32_t tiles_n,
-               uint32_t ktiles, uint64_t lda, uint64_t ldb, uint64_t ldc, uint64_t planeA,
-               uint64_t planeB, uint64_t batch_a, uint64_t batch_b, uint64_t batch_c) {
-  using P = Prec<PREC>;
-  using in_t = typename P::in_t;
-  using acc_t = typename P::acc_t;
-  constexpr int NT = 64 * WM * WN;
-  constexpr int TM = BM / WM, TN = BN / WN;      // wave tile
-  constexpr int FM = TM / 16, FN = TN / 16;      // 16x16 MFMA blocks per wave
-  constexpr int PL = P::planes;
-  constexpr int CPR = RB / 16;                   // 16-byte chunks per row
-  constexpr int CH_A = BM * CPR;                 // chunks per A tile plane
-  constexpr int CH_B = BN * CPR;
-  static_assert(CH_A % NT == 0 && CH_B % NT == 0, "tile/threads mismatch");
-  static_assert(RB == 64 || RB == 128, "RB must be 64 or 128");
-  constexpr int LA = CH_A / NT, LB = CH_B / NT;  // chunks per thread
-  constexpr int STR = lds_stride<RB, SWZ>();
-  constexpr int STAGE = (BM + BN) * STR * PL;
-  constexpr int NF = RB / 64;                    // 16-byte fragments per lane per block row
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  const int g = lane >> 4, r16 = lane & 15;
-
-  uint32_t tm, tn;
-  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
-  const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
-
-  // batch: blockIdx.z selects a product of the strided batch (elements)
-  A += uint64_t(blockIdx.z) * batch_a;
-  Bt += uint64_t(blockIdx.z) * batch_b;
-  C += uint64_t(blockIdx.z) * batch_c;
-  const unsigned char *gA = reinterpret_cast<const unsigned char *>(A + m0 * lda);
-  const unsigned char *gB = reinterpret_cast<const unsigned char *>(Bt + n0 * ldb);
-  const uint64_t ldaB = lda * P::elem, ldbB = ldb * P::elem;
-  const uint64_t plA = planeA * P::elem, plB = planeB * P::elem;
-
-  // PF register sets for the global -> LDS staging: with PF = 2 the loads
-  // of tile t are issued two compute phases before tile t is stored to LDS
-  static_assert(PF == 1 || PF == 2, "prefetch distance 1 or 2");
-  u32x4 ra[PF][PL][LA], rb[PF][PL][LB];
-
-  auto gload = [&](uint32_t kt, int set) {
-    const uint64_t kb = uint64_t(kt) * RB;
-#pragma unroll
-    for (int p = 0; p < PL; ++p) {
-#pragma unroll
-      for (int i = 0; i < LA; ++i) {
-        const int c = tid + i * NT, row = c / CPR, col = c % CPR;
-        ra[set][p][i] = *reinterpret_cast<const u32x4 *>(gA + p * plA + row * ldaB + kb + col * 16);
-      }
-#pragma unroll
-      for (int i = 0; i < LB; ++i) {
-        const int c = tid + i * NT, row = c / CPR, col = c % CPR;
-        rb[set][p][i] = *reinterpret_cast<const u32x4 *>(gB + p * plB + row * ldbB + kb + col * 16);
-      }
-    }
-  };
-  auto sstore = [&](int stage, int set) {
-    unsigned char *base = smem + stage * STAGE;
-#pragma unroll
-    for (int p = 0; p < PL; ++p) {
-      unsigned char *sA = base + p * (BM + BN) * STR;
-      unsigned char *sB = sA + BM * STR;
-#pragma unroll
-      for (int i = 0; i < LA; ++i) {
-        const int c = tid + i * NT, row = c / CPR, col = c % CPR;
-        *reinterpret_cast<u32x4 *>(sA + lds_off<RB, SWZ>(row, col)) = ra[set][p][i];
-      }
-#pragma unroll
-      for (int i = 0; i < LB; ++i) {
-        const int c = tid + i * NT, row = c / CPR, col = c % CPR;
-        *reinterpret_cast<u32x4 *>(sB + lds_off<RB, SWZ>(row, col)) = rb[set][p][i];
-      }
-    }
-  };
-
-  acc_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = acc_t{};
-  // BF16X6: the MFMA accumulates one group of K tiles in FP32, the groups are
-  // summed in FP64, so the rounding of the sum no longer grows with the full
-  // length of K
-  constexpr bool F64SUM = PREC == 3;
-  constexpr uint32_t FLUSH = BF6_FLUSH;
-  v4d acc64[F64SUM ? FM : 1][F64SUM ? FN : 1];
-  if constexpr (F64SUM) {
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) acc64[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
-  }
-
-  // MFMAs of the tile in LDS stage `cur`, then the FP64 fold of a finished
-  // group (K tile kt is the last of its group, or the last one)
-  auto compute = [&](int cur, uint32_t kt) {
-    const unsigned char *base = smem + cur * STAGE;
-    // fragments: lane group g owns chunks [g NF, g NF + NF) of every row
-    using frag_t = typename P::frag_t;
-    frag_t fa[PL][FM][NF], fb[PL][FN][NF];
-#pragma unroll
-    for (int p = 0; p < PL; ++p) {
-      const unsigned char *sA = base + p * (BM + BN) * STR;
-      const unsigned char *sB = sA + BM * STR;
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-          fa[p][i][f] = *reinterpret_cast<const frag_t *>(sA + lds_off<RB, SWZ>(wm * TM + i * 16 + r16, g * NF + f));
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int f = 0; f < NF; ++f)
-          fb[p][j][f] = *reinterpret_cast<const frag_t *>(sB + lds_off<RB, SWZ>(wn * TN + j * 16 + r16, g * NF + f));
-    }
-
-    if constexpr (PREC == 3) {
-      static_assert(NF == 1, "BF16X6 uses one 32-element k-step per K tile");
-      // the six products of each block, the small ones first; each term
-      // sweeps all accumulators so consecutive MFMAs are independent
-      constexpr int TA[6] = {2, 0, 1, 1, 0, 0}, TB[6] = {0, 2, 1, 0, 1, 0};  // lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi
-#pragma unroll
-      for (int term = 0; term < 6; ++term)
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[TA[term]][i][0], fb[TB[term]][j][0], acc[i][j], 0, 0, 0);
-    } else {
-#pragma unroll
-      // the three products of a block are spread over all accumulators so
-      // that consecutive MFMAs never depend on each other
-      for (int s = 0; s < NF; ++s)
-#pragma unroll
-        for (int term = 0; term < 3; ++term)
-#pragma unroll
-          for (int i = 0; i < FM; ++i)
-#pragma unroll
-            for (int j = 0; j < FN; ++j) {
-              const int pa = term == 0 ? 1 : 0, pb = term == 1 ? 1 : 0;  // lo*hi, hi*lo, hi*hi
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pa][i][s], fb[pb][j][s], acc[i][j], 0, 0, 0);
-            }
-    }
-
-    if constexpr (F64SUM) {
-      if ((kt + 1) % FLUSH == 0 || kt + 1 == ktiles) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc64[i][j][e] += double(acc[i][j][e]);
-            acc[i][j] = acc_t{};
-          }
-      }
-    }
-  };
-
-  if constexpr (PF == 2) {
-    // tile t: registers set t % 2, LDS stage t % 2.  Iteration t issues the
-    // loads of tile t + 2 into the set that tile t has left, computes stage
-    // t % 2, then stores tile t + 1 (loaded during iteration t - 1) into the
-    // stage that iteration t - 1 computed; one barrier per tile.  The main
-    // loop has no conditional loads or stores, so the wait before a store
-    // leaves the six loads issued after it in flight; the last one to three
-    // tiles run in a tail with the bounds checks.
-    gload(0, 0);
-    sstore(0, 0);
-    if (ktiles > 1) gload(1, 1);
-    __syncthreads();
-    auto body = [&](uint32_t kt, auto half) {
-      constexpr int h = decltype(half)::value;
-      gload(kt + 2, h);
-      // keep the loads ahead of the MFMAs: the compiler would otherwise sink
-      // them towards their use and shorten the prefetch distance to one tile
-      // (the empty asm with a memory clobber stops sinking in the IR, the
-      // scheduling barrier reordering in the machine scheduler)
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      compute(h, kt);
-      sstore(h ^ 1, h ^ 1);
-      __syncthreads();
-    };
-    auto tail = [&](uint32_t kt, auto half) {
-      constexpr int h = decltype(half)::value;
-      if (kt + 2 < ktiles) gload(kt + 2, h);
-      compute(h, kt);
-      if (kt + 1 < ktiles) sstore(h ^ 1, h ^ 1);
-      __syncthreads();
-    };
-    uint32_t kt = 0;
-    for (; kt + 3 < ktiles; kt += 2) {
-      body(kt, std::integral_constant<int, 0>{});
-      body(kt + 1, std::integral_constant<int, 1>{});
-    }
-    // kt is even here and 1 to 3 tiles remain
-    tail(kt, std::integral_constant<int, 0>{});
-    if (kt + 1 < ktiles) tail(kt + 1, std::integral_constant<int, 1>{});
-    if (kt + 2 < ktiles) tail(kt + 2, std::integral_constant<int, 0>{});
-  } else {
-    gload(0, 0);
-    sstore(0, 0);
-    __syncthreads();
-    for (uint32_t kt = 0; kt < ktiles; ++kt) {
-      const int cur = kt & 1;
-      if (kt + 1 < ktiles) gload(kt + 1, 0);
-      compute(cur, kt);
-      if (kt + 1 < ktiles) sstore(cur ^ 1, 0);
-      __syncthreads();
-    }
-  }
-
-  // epilogue: register e of lane (g, r16) holds column r16, row 4g + e of each
-  // 16x16 block
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = 4 * g + e;
-        const uint64_t m = m0 + wm * TM + i * 16 + row;
-        const uint64_t n = n0 + wn * TN + j * 16 + r16;
-        auto *dst = C + m * ldc + n;
-        if constexpr (F64SUM) {
-          if constexpr (ACCUM)
-            *dst = float(double(*dst) + acc64[i][j][e]);
-          else
-            *dst = float(acc64[i][j][e]);
-        } else {
-          if constexpr (ACCUM)
-            *dst += acc[i][j][e];
-          else
-            *dst = acc[i][j][e];
-        }
-      }
-}
-
 
 // ------------------------------------------------ pipelined FP64 / FP32 join ---
 // LDS layout of the pipelined kernel: rows of 128 bytes (8 chunks of 16),
@@ -436,7 +155,7 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
   const int wm = wave / WN, wn = wave % WN;
   const int g = lane >> 4, r16 = lane & 15;
   uint32_t tm, tn;
-  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  tile_coords<GROUP_M>(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
   A += uint64_t(blockIdx.z) * batch_a;
   Bt += uint64_t(blockIdx.z) * batch_b;
@@ -607,6 +326,230 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
       }
 }
 
+// ------------------------------------------------------ split-BF16 joins ---
+// 16 bytes per lane from memory straight into LDS: lane l's go to lds + 16 l
+// (lds: wave-uniform byte offset).  No register receives the data; the
+// compiler does not count the load, so wait_vm must cover it before a barrier
+// publishes it.  Writing M0 needs one wait state before the load reads it.
+__device__ inline void dma16(const void *p, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory");
+}
+template <int N>
+__device__ inline void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Chunk swizzle of 64-byte LDS rows (four chunks of 16 bytes, four rows per
+// 256-byte line): chunk c of row r sits at chunk c ^ split_swz(r).  The 16
+// lanes of one phase of a 16-byte read hold rows 0-3 and 12-15 of one chunk
+// and rows 4-11 of the next: 0, 2, 3, 1 over r / 4 puts them on 16 different
+// 4-bank groups (r / 4 itself does not: 37 % of the LDS cycles were conflicts).
+__device__ inline int split_swz(int row) { return int((0x1320u >> (4 * ((row >> 2) & 3))) & 3u); }
+
+// The split-BF16 joins: PL planes per operand (2: hi*hi + hi*lo + lo*hi; 3:
+// the six products down to 2^-24), K in tiles of 32 elements (64-byte rows),
+// small products first.
+//
+// What bounds it: an MFMA takes 16 cycles, so a K tile is over in 1536 (PL 3,
+// 128 x 128) to 3072 cycles (PL 2, 256 x 256) and neither LDS reads nor the
+// 1-2 us of a load from beyond L2 may stand between two tiles; under a long
+// launch the clock then falls to 1.8-1.9 GHz (of 2.4).  Hence:
+// - tiles go from memory straight to LDS (no staging registers, no LDS
+//   stores), issued NST tiles ahead into a ring of NST stages;
+// - every LDS read is issued half a tile ahead of the MFMAs that use it, A in
+//   halves of the wave's rows, B in two register sets;
+// - reads and loads are issued one by one between MFMAs (issued in a block,
+//   the loads of all waves queue in front of the MFMAs);
+// - one barrier per tile, between the two halves.
+// PL 3: the MFMAs sum FLUSH tiles in FP32; a finished group is added to FP64
+// sums between the first MFMAs of the next one.
+//
+// Measured against the kernel before (loads through registers, all fragments
+// of a tile read right before its MFMAs), TFLOP/s of the product:
+//   PL 3  10112^2 x 25056: 154 -> 178 (1.07 PFLOP/s of MFMA, pipes busy 46 ->
+//         57 %); 3200^2 x 3136: 158 -> 192
+//   PL 2  10240^2 x 25056: 346 -> 407 (1.22 PFLOP/s); 2048^2 x 8192: 125 -> 338
+template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH, bool ACCUM>
+__global__ void __launch_bounds__(64 * WM * WN)
+gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bt, float *__restrict__ C,
+                  uint32_t tiles_m, uint32_t tiles_n, uint32_t ktiles, uint64_t lda, uint64_t ldb, uint64_t ldc,
+                  uint64_t planeA, uint64_t planeB, uint64_t batch_a, uint64_t batch_b, uint64_t batch_c) {
+  constexpr int NW = WM * WN, TM = BM / WM, TN = BN / WN, FM = TM / 16, FN = TN / 16, RB = 64;
+  constexpr int HM = FM / 2;
+  constexpr int LA = BM / 16 / NW, LB = BN / 16 / NW;   // 1 KB blocks (16 rows) per wave and plane
+  static_assert(LA >= 1 && LB >= 1, "every wave loads whole blocks");
+  static_assert(FLUSH == 0 || FLUSH == 4, "the loop below folds every fourth tile");
+  constexpr int PLANE = (BM + BN) * RB, STAGE = PLANE * PL;
+  constexpr int PERT = PL * (LA + LB);                  // loads of a wave per tile
+  constexpr int NTERM = PL == 3 ? 6 : 3;
+  // planes of each product: lo*hi, hi*lo, mid*mid, mid*hi, hi*mid, hi*hi or lo*hi, hi*lo, hi*hi
+  constexpr int TA[6] = {PL == 3 ? 2 : 1, 0, PL == 3 ? 1 : 0, 1, 0, 0};
+  constexpr int TB[6] = {0, PL == 3 ? 2 : 1, PL == 3 ? 1 : 0, 0, 1, 0};
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN, g = lane >> 4, r16 = lane & 15;
+  uint32_t tm, tn;
+  // PL 3: groups of four tile rows (178 TFLOP/s against 173 with eight)
+  tile_coords<PL == 3 ? 4 : GROUP_M>(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
+  A += uint64_t(blockIdx.z) * batch_a;
+  Bt += uint64_t(blockIdx.z) * batch_b;
+  C += uint64_t(blockIdx.z) * batch_c;
+  // block u of this wave: rows 16 (wave LA + u) .. + 15; lane l fills chunk l % 4 of row l / 4
+  const int drow = lane >> 2, dchunk = (lane & 3) ^ split_swz(drow);
+  const unsigned char *pa[PL][LA], *pb[PL][LB];
+#pragma unroll
+  for (int p = 0; p < PL; ++p) {
+#pragma unroll
+    for (int u = 0; u < LA; ++u)
+      pa[p][u] = reinterpret_cast<const unsigned char *>(A + p * planeA + (m0 + (wave * LA + u) * 16 + drow) * lda) +
+                 dchunk * 16;
+#pragma unroll
+    for (int u = 0; u < LB; ++u)
+      pb[p][u] = reinterpret_cast<const unsigned char *>(Bt + p * planeB + (n0 + (wave * LB + u) * 16 + drow) * ldb) +
+                 dchunk * 16;
+  }
+  const uint32_t lds0 = uint32_t(reinterpret_cast<uintptr_t>(smem));   // low 32 bits of a flat LDS address are its offset
+  // one of the PERT blocks of tile kt
+  auto dma1 = [&](uint64_t kb, uint32_t base, int q) {
+    const int p = q / (LA + LB), u = q % (LA + LB);
+    if (u < LA) dma16(pa[p][u] + kb, base + p * PLANE + (wave * LA + u) * 1024);
+    else dma16(pb[p][u - LA] + kb, base + p * PLANE + BM * RB + (wave * LB + u - LA) * 1024);
+  };
+  auto dma = [&](uint32_t kt, uint32_t stage) {
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) dma1(uint64_t(kt) * RB, lds0 + stage * STAGE, q);
+  };
+  const int fro = (g ^ split_swz(r16)) << 4;
+  const int aoff = (wm * TM + r16) * RB + fro, boff = BM * RB + (wn * TN + r16) * RB + fro;
+  bf16x8 fa[PL][FM], fb[2][PL][FN];
+  // fragment reads one at a time: q-th of the rows [lo, hi) of A; q-th of B
+  auto aload1 = [&](uint32_t stage, int lo, int q) {
+    const int i = lo + q / PL, p = q % PL;
+    fa[p][i] = *reinterpret_cast<const bf16x8 *>(smem + stage * STAGE + aoff + p * PLANE + i * 16 * RB);
+  };
+  auto bload1 = [&](uint32_t stage, auto par, int q) {
+    const int p = q / FN, j = q % FN;
+    fb[decltype(par)::value][p][j] =
+        *reinterpret_cast<const bf16x8 *>(smem + stage * STAGE + boff + p * PLANE + j * 16 * RB);
+  };
+  v4f acc[FM][FN];
+  constexpr bool F64 = FLUSH > 0;
+  v4d acc64[F64 ? FM : 1][F64 ? FN : 1];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      acc[i][j] = v4f{};
+      if constexpr (F64) acc64[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+    }
+  // the products of the rows [lo, hi) of A; hook(n) runs after the n-th MFMA
+  auto mfma = [&](auto par, auto lo, auto hi, auto fold, auto &&hook) {
+    constexpr int L0 = decltype(lo)::value, NR = decltype(hi)::value - L0;
+#pragma unroll
+    for (int n = 0; n < NTERM * NR * FN; ++n) {
+      const int t = n / (NR * FN), i = L0 + n / FN % NR, j = n % FN;
+      if constexpr (decltype(fold)::value) {
+        if (t == 0) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc64[i][j][e] += double(acc[i][j][e]);
+          acc[i][j] = v4f{};
+        }
+      }
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[TA[t]][i], fb[decltype(par)::value][TB[t]][j], acc[i][j],
+                                                          0, 0, 0);
+      hook(n);
+    }
+  };
+  constexpr auto I0 = std::integral_constant<int, 0>{};
+  constexpr auto I1 = std::integral_constant<int, 1>{};
+  constexpr auto IH = std::integral_constant<int, HM>{};
+  constexpr auto IF = std::integral_constant<int, FM>{};
+  constexpr auto NO = std::false_type{};
+  auto barrier = [&] {   // waits for this wave's LDS reads, not for its loads
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+  };
+  auto phase = [] { __builtin_amdgcn_sched_barrier(0); };
+  const uint32_t last = ktiles - 1;
+  uint32_t cur = 0;   // stage of tile kt
+  constexpr int NM = NTERM * HM * FN;   // MFMAs of one phase
+  auto body = [&](uint32_t kt, auto par, auto fold) {
+    constexpr int P = decltype(par)::value;
+    constexpr auto PN = std::integral_constant<int, P ^ 1>{};
+    mfma(par, I0, IH, fold, [&](int n) {
+      if (n < PL * HM) {
+        aload1(cur, HM, n);
+        phase();
+      }
+    });
+    phase();
+    // this wave's part of tile kt + 1 has landed; past the barrier all of it
+    // has, and no wave reads the stage of tile kt any more
+    wait_vm<(NST - 2) * PERT>();
+    barrier();
+    phase();
+    const uint32_t nxt = cur + 1 == NST ? 0 : cur + 1;
+    const uint32_t kn = kt + NST < last ? kt + NST : last;   // past the end: the last tile again, never read
+    const uint64_t kb = uint64_t(kn) * RB;
+    const uint32_t base = lds0 + cur * STAGE;
+    constexpr int NR = PL * (HM + FN);        // LDS reads of the phase
+    constexpr int DS = NM / PERT;             // MFMAs per load
+    static_assert(DS >= 1 && NM > 4, "phase too short");
+    mfma(par, IH, IF, fold, [&](int n) {
+      bool any = false;
+#pragma unroll
+      for (int q = n * NR / (NM - 4); q < (n + 1) * NR / (NM - 4) && q < NR; ++q) {
+        if (q < PL * FN) bload1(nxt, PN, q);
+        else aload1(nxt, 0, q - PL * FN);
+        any = true;
+      }
+      if (n % DS == DS / 2 && n / DS < PERT) {
+        dma1(kb, base, n / DS);
+        any = true;
+      }
+      if (any) phase();
+    });
+    phase();
+    cur = nxt;
+  };
+#pragma unroll
+  for (int s = 0; s < NST; ++s) dma(uint32_t(s) < last ? s : last, s);
+  wait_vm<(NST - 1) * PERT>();
+  barrier();
+#pragma unroll
+  for (int q = 0; q < PL * HM; ++q) aload1(0, 0, q);
+#pragma unroll
+  for (int q = 0; q < PL * FN; ++q) bload1(0, I0, q);
+  constexpr auto FD = std::integral_constant<bool, F64>{};
+  for (uint32_t kt = 0;; kt += 4) {
+    body(kt, I0, FD);
+    if (kt == last) break;
+    body(kt + 1, I1, NO);
+    if (kt + 1 == last) break;
+    body(kt + 2, I0, NO);
+    if (kt + 2 == last) break;
+    body(kt + 3, I1, NO);
+    if (kt + 3 == last) break;
+  }
+  wait_vm<0>();
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float *dst = C + (m0 + wm * TM + i * 16 + 4 * g + e) * ldc + n0 + wn * TN + j * 16 + r16;
+        if constexpr (F64) {
+          const double v = acc64[i][j][e] + double(acc[i][j][e]);
+          *dst = ACCUM ? float(double(*dst) + v) : float(v);
+        } else {
+          *dst = ACCUM ? *dst + acc[i][j][e] : acc[i][j][e];
+        }
+      }
+}
+
 template <int PREC, int BM, int BN, int WM, int WN, int MINW>
 void launch_pipe(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K, uint64_t lda,
                  uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t splits, uint64_t c_split_stride,
@@ -769,65 +712,45 @@ bool check_gemm(uint64_t BM, uint64_t BN, uint64_t BK, void *C, uint64_t M, uint
   return true;
 }
 
-template <int PREC, int BM, int BN, int WM, int WN, int RB, int SWZ, int PF>
-void launch_gemm(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K,
-                 uint64_t lda, uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t nb, uint64_t batch_a,
-                 uint64_t batch_b, uint64_t batch_c) {
-  using P = Prec<PREC>;
-  constexpr int BK = RB / P::elem;
-  if (!check_gemm<PREC>(BM, BN, BK, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
-  constexpr size_t lds = 2 * size_t(BM + BN) * lds_stride<RB, SWZ>() * P::planes;
+template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH>
+void launch_split(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K, uint64_t lda,
+                  uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t nb, uint64_t batch_a,
+                  uint64_t batch_b, uint64_t batch_c) {
+  constexpr size_t lds = NST * size_t(BM + BN) * 64 * PL;
   static_assert(lds <= 160 * 1024, "LDS tile exceeds 160 KB");
-  using in_t = typename P::in_t;
-  using out_t = typename P::out_t;
-  auto *a = static_cast<const in_t *>(A);
-  auto *b = static_cast<const in_t *>(Bt);
-  auto *c = static_cast<out_t *>(C);
+  static const bool attr = [] {   // dynamic LDS above 64 KB must be allowed per kernel
+    TRG_HIP_CHECK(hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, true>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    TRG_HIP_CHECK(hipFuncSetAttribute(
+        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, false>),
+        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    return true;
+  }();
+  (void)attr;
+  const uint32_t tm = uint32_t(M / BM), tn = uint32_t(N / BN), kt = uint32_t(K / 32);
+  const dim3 grid(tm * tn, 1, nb), block(64 * WM * WN);
+  auto *a = static_cast<const uint16_t *>(A);
+  auto *b = static_cast<const uint16_t *>(Bt);
+  auto *c = static_cast<float *>(C);
   const uint64_t plA = M * lda, plB = N * ldb;
-  const uint32_t tm = uint32_t(M / BM), tn = uint32_t(N / BN), kt = uint32_t(K / BK);
-  dim3 grid(tm * tn, 1, nb), block(64 * WM * WN);
-  // dynamic LDS above 64 KB must be allowed per kernel (once per instantiation)
-  static bool attr_set = false;
-  if (!attr_set) {
-    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_kernel<PREC, BM, BN, WM, WN, RB, SWZ, PF, true>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_kernel<PREC, BM, BN, WM, WN, RB, SWZ, PF, false>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-    attr_set = true;
-  }
   if (accum)
-    hipLaunchKernelGGL((gemm_nt_kernel<PREC, BM, BN, WM, WN, RB, SWZ, PF, true>), grid, block, lds, st, a, b, c, tm, tn,
+    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, true>), grid, block, lds, st, a, b, c, tm, tn,
                        kt, lda, ldb, ldc, plA, plB, batch_a, batch_b, batch_c);
   else
-    hipLaunchKernelGGL((gemm_nt_kernel<PREC, BM, BN, WM, WN, RB, SWZ, PF, false>), grid, block, lds, st, a, b, c, tm,
+    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, false>), grid, block, lds, st, a, b, c, tm,
                        tn, kt, lda, ldb, ldc, plA, plB, batch_a, batch_b, batch_c);
   TRG_HIP_CHECK(hipGetLastError());
 }
 
 }  // namespace
 
-// BF16x3 join: 256 x 256 workgroup tile, eight waves of 128 x 64 (two per
-// SIMD), 64-byte K rows (32 bf16 per plane), two swizzled LDS stages of
-// 64 KB.  Measured against 128 x 128 tiles of four 64 x 64 waves with
-// 128-byte rows: 1.6x the MFMA issue rate, 2.5x less L2 -> fabric traffic.
-struct BF {
-  static constexpr int BM = 256, BN = 256, WM = 2, WN = 4, RB = 64, SWZ = 1;
-};
-// BF16x6 join: 128 x 128 workgroup tile, eight waves of 64 x 32 (two per
-// SIMD: 32 FP32 accumulators, 64 FP64 group sums, 18 operand fragments of
-// 16 bytes per lane), 64-byte K rows of three planes, swizzled LDS stages of
-// 48 KB.  Six products per three planes read from LDS: per MFMA it reads a
-// third less LDS than the BF16x3 join's two-plane, three-product blocks.
-struct BF6 {
-  static constexpr int BM = 128, BN = 128, WM = 2, WN = 4, RB = 64, SWZ = 1, PF = TRG_BF6_PF;
-};
-
 GemmTile gemm_tile(int prec) {
   switch (prec) {
     case 0: return {128, 128, 16};
     case 1: return {128, 128, 32};
-    case 2: return {BF::BM, BF::BN, BF::RB / 2};
-    case 3: return {BF6::BM, BF6::BN, BF6::RB / 2};
+    case 2: return {256, 256, 32};
+    case 3: return {128, 128, 32};
   }
   throw Error(-1, "gemm: unknown precision");
 }
@@ -841,41 +764,60 @@ namespace {
 //   M = N = 10112 (K 25008)  128 x 128 72.3, 64 x 128 65.7, 64 x 64 64.1 TFLOP/s
 //   M = N = 3200 (K 3136)    128 x 128 59.7, 64 x 128 69.9, 64 x 64 65.7
 //   M = N = 1024 (K 1024)    128 x 128 17.4, 64 x 128 31.4, 64 x 64 49.8
-// The K split needs a K of a few chunks per wave.
+//   M = N = 256 (K 2752)     64 x 64 3.6, K split 8.6
+double f64_cost(uint64_t M, uint64_t N, double count, uint64_t bm, uint64_t bn, double rate) {
+  if (M % bm || N % bn) return 1e300;
+  return std::ceil(double(M / bm) * double(N / bn) * count / 256.0) * double(bm * bn) / rate;
+}
+constexpr double RATE_128 = 74.0, RATE_64_128 = 70.0, RATE_64 = 66.0, RATE_KSPLIT = 50.0;
+
 void gemm_f64(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K, uint64_t lda, uint64_t ldb,
               uint64_t ldc, bool accum, hipStream_t st, uint32_t splits, uint64_t c_split_stride, uint32_t nb,
-              uint64_t batch_a, uint64_t batch_b, uint64_t batch_c) {
-  auto cost = [&](uint64_t bm, uint64_t bn, double rate) {
-    if (M % bm || N % bn) return 1e300;
-    const double tiles = double(M / bm) * double(N / bn) * splits * nb;
-    return std::ceil(tiles / 256.0) * double(bm * bn) / rate;
-  };
-  const double c128 = cost(128, 128, 74.0), c64 = cost(64, 128, 70.0), c6464 = cost(64, 64, 66.0);
-  const double cks = K / splits >= 16 * 2 * KSP_WAVES ? cost(KSP_T, KSP_T, 50.0) : 1e300;
-  const double best = std::min(std::min(c128, c64), std::min(c6464, cks));
-  if (best == c128)
-    launch_pipe<0, 128, 128, 2, 2, 2>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
-                                      batch_b, batch_c);
-  else if (best == c64)
-    launch_pipe<0, 64, 128, 2, 2, 3>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
-                                     batch_b, batch_c);
-  else if (best == c6464)
-    launch_pipe<0, 64, 64, 2, 2, 4>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
-                                    batch_b, batch_c);
-  else
+              uint64_t batch_a, uint64_t batch_b, uint64_t batch_c, bool ksplit) {
+  if (ksplit) {
     launch_ksplit(static_cast<const double *>(A), static_cast<const double *>(Bt), static_cast<double *>(C), M, N, K,
                   lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a, batch_b, batch_c);
+    return;
+  }
+  const double count = double(splits) * nb;
+  const double c128 = f64_cost(M, N, count, 128, 128, RATE_128), c64 = f64_cost(M, N, count, 64, 128, RATE_64_128);
+  const double c6464 = f64_cost(M, N, count, 64, 64, RATE_64);
+  if (c128 <= c64 && c128 <= c6464)
+    launch_pipe<0, 128, 128, 2, 2, 2>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
+                                      batch_b, batch_c);
+  else if (c64 <= c6464)
+    launch_pipe<0, 64, 128, 2, 2, 3>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
+                                     batch_b, batch_c);
+  else
+    launch_pipe<0, 64, 64, 2, 2, 4>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, splits, c_split_stride, nb, batch_a,
+                                    batch_b, batch_c);
+}
+
+// Split-BF16 products: whether tiles of `small` squared finish before tiles of
+// `big` squared, whose last round may leave most of the 256 CUs idle; `rate`
+// is the speed of the small-tile kernel over the big-tile one on full rounds.
+bool split_small(uint64_t M, uint64_t N, uint32_t nb, uint64_t big, uint64_t small, double rate) {
+  auto cost = [&](uint64_t b) { return std::ceil(double(M / b) * double(N / b) * nb / 256.0) * double(b * b); };
+  return cost(small) < rate * cost(big);
 }
 
 }  // namespace
 
+bool gemm_f64_ksplit(uint64_t M, uint64_t N, uint64_t K) {
+  if (M % KSP_T || N % KSP_T || K < 16 * 2 * KSP_WAVES) return false;   // a few chunks per wave
+  const double tiled = std::min(std::min(f64_cost(M, N, 1, 128, 128, RATE_128), f64_cost(M, N, 1, 64, 128, RATE_64_128)),
+                                f64_cost(M, N, 1, 64, 64, RATE_64));
+  return f64_cost(M, N, 1, KSP_T, KSP_T, RATE_KSPLIT) < tiled;
+}
+
 void gemm_nt(int prec, const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K,
              uint64_t lda, uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t nb, uint64_t batch_a,
-             uint64_t batch_b, uint64_t batch_c) {
+             uint64_t batch_b, uint64_t batch_c, int ksplit) {
   switch (prec) {
     case 0:
       if (check_gemm<0>(128, 128, 16, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c))
-        gemm_f64(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, 1, 0, nb, batch_a, batch_b, batch_c);
+        gemm_f64(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, 1, 0, nb, batch_a, batch_b, batch_c,
+                 ksplit < 0 ? gemm_f64_ksplit(M, N, K) : ksplit != 0);
       return;
     case 1:
       if (!check_gemm<1>(128, 128, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
@@ -887,12 +829,22 @@ void gemm_nt(int prec, const void *A, const void *Bt, void *C, uint64_t M, uint6
         launch_pipe<1, 64, 128, 2, 2, 2>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, 1, 0, nb, batch_a, batch_b, batch_c);
       return;
     case 2:
-      launch_gemm<2, BF::BM, BF::BN, BF::WM, BF::WN, BF::RB, BF::SWZ, 1>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st,
-                                                                         nb, batch_a, batch_b, batch_c);
+      if (!check_gemm<2>(256, 256, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
+      // four waves of 64 x 64, two workgroups per CU, while the 256 x 256 tiles leave CUs idle in
+      // their last round: 2048^2 x 8192 338 against 186 TFLOP/s, 10240^2 x 25056 290 against 407
+      if (split_small(M, N, nb, 256, 128, 290.0 / 407.0))
+        launch_split<2, 128, 128, 2, 2, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
+      else
+        launch_split<2, 256, 256, 2, 4, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
       return;
     case 3:
-      launch_gemm<3, BF6::BM, BF6::BN, BF6::WM, BF6::WN, BF6::RB, BF6::SWZ, BF6::PF>(
-          A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
+      if (!check_gemm<3>(128, 128, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
+      if (split_small(M, N, nb, 128, 64, 0.6))
+        launch_split<3, 64, 64, 2, 2, 3, BF6_FLUSH>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
+                                                    batch_c);
+      else
+        launch_split<3, 128, 128, 2, 4, 3, BF6_FLUSH>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
+                                                      batch_c);
       return;
   }
   throw Error(-1, "gemm: unknown precision");
@@ -906,7 +858,7 @@ void gemm_nt_splitk_f64(const double *A, const double *Bt, double *Cpart, uint64
                         hipStream_t st) {
   TRG_REQUIRE(K == uint64_t(splits) * kper, "splitk: K != splits * kper");
   if (check_gemm<0>(64, 64, 16, Cpart, M, N, K, lda, ldb, N, false, st, splits, 1, 0, 0, 0))
-    gemm_f64(A, Bt, Cpart, M, N, K, lda, ldb, N, false, st, splits, M * N, 1, 0, 0, 0);
+    gemm_f64(A, Bt, Cpart, M, N, K, lda, ldb, N, false, st, splits, M * N, 1, 0, 0, 0, false);
 }
 
 }  // namespace trg

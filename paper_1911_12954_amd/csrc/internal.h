@@ -19,7 +19,13 @@ GemmTile gemm_tile(int prec);
 // (element strides)
 void gemm_nt(int prec, const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K,
              uint64_t lda, uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t nb = 1,
-             uint64_t batch_a = 0, uint64_t batch_b = 0, uint64_t batch_c = 0);
+             uint64_t batch_a = 0, uint64_t batch_b = 0, uint64_t batch_c = 0, int ksplit = -1);
+// Whether an FP64 product of this shape splits K over the waves of a workgroup
+// (gemm_nt's ksplit: 1 and 0 prescribe it, -1 asks this rule).  The split
+// orders the sum over K differently; the tile shapes do not.  A caller whose
+// bits must not depend on how it cuts a product into launches asks once, for
+// the whole product.
+bool gemm_f64_ksplit(uint64_t M, uint64_t N, uint64_t K);
 // split-K FP64 Gram product: C[s] = A[:, ks] * Bt[:, ks]^T for split s, tile 64
 void gemm_nt_splitk_f64(const double *A, const double *Bt, double *Cpart, uint64_t M, uint64_t N,
                         uint64_t K, uint64_t lda, uint64_t ldb, uint32_t splits, uint64_t kper,

@@ -180,6 +180,46 @@ def test_gemm_bf16x6(M, N, K, accumulate):
     assert err < 12 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("precision,M,N", [("bf16x3", 256, 512), ("bf16x3", 4096, 4096), ("bf16x6", 128, 256),
+                                           ("bf16x6", 2048, 2304)])
+@pytest.mark.parametrize("K", [32, 64, 96, 160, 288])
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_gemm_split_tile_variants(precision, M, N, K, accumulate):
+    """Both tile shapes of each split-BF16 product (the large ones from about
+    256 tiles on) at K loops of one to nine tiles, shorter and longer than the
+    ring of LDS stages and than the group of four, with rows farther apart
+    than K: bounds as above (every dropped or FP32-summed term)."""
+    torch = need_gpu()
+    from paper_1911_12954_amd import trg_gemm
+    announce("gemm split tiles", precision, M, N, K, accumulate)
+    planes, ld = (2 if precision == "bf16x3" else 3), K + 64
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+
+    def operand(rows):
+        x = torch.randn((rows, ld), generator=g, device="cuda")
+        out = torch.empty((planes, rows, ld), dtype=torch.bfloat16, device="cuda")
+        for p in range(planes):
+            out[p] = x.to(torch.bfloat16)
+            x = x - out[p].float()
+        return out
+
+    A, B = operand(M), operand(N)
+    C = torch.randn((M, N), generator=g, device="cuda")
+    A64, B64 = (x[:, :, :K].double() for x in (A, B))
+    if precision == "bf16x6":
+        ref = A64.sum(0) @ B64.sum(0).T
+    else:
+        ref = A64[0] @ B64[0].T + A64[0] @ B64[1].T + A64[1] @ B64[0].T
+    scale = A64.sum(0).abs() @ B64.sum(0).abs().T
+    if accumulate:
+        ref, scale = ref + C.double(), scale + C.double().abs()
+    trg_gemm(precision, A.data_ptr(), B.data_ptr(), C.data_ptr(), M, N, K, ld, ld, N, accumulate,
+             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    bound = 12 * 2.0 ** -24 if precision == "bf16x6" else 4 * 2.0 ** -24 * K ** 0.5 + 1e-7
+    assert float(((C.double() - ref).abs() / scale).max()) < bound
+
+
 @pytest.mark.parametrize("n", [1, 2, 4, 7, 16, 33, 100, 144, 161, 200, 333, 576])
 def test_jacobi_eigh(n):
     """Orders up to 160 use cyclic Jacobi, larger ones Householder
