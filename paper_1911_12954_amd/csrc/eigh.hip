@@ -510,33 +510,58 @@ tridiag_ql_kernel(double *Aall, double *wall, double *Vall, int *status, int n) 
 // The isometry selection needs every eigenvalue (the discarded weight, the
 // degenerate-cut flag, the spectrum record) but the eigenvectors only of the
 // kept indices and of the rest of a cluster of near-degenerate eigenvalues
-// that the cut splits.  tridiag_top_kernel computes exactly that, with no
-// serial QL sweeps and no n x n rotation accumulation:
-//   1. Householder reduction to tridiagonal T (as for the full solver);
+// that the cut splits.  No serial QL sweeps, no n x n rotation accumulation:
+//   1. Householder reduction to tridiagonal T: one launch per column while
+//      more than TD_LDS columns remain (td_column_kernel, many workgroups per
+//      matrix), the rest in LDS (td_finish_kernel, one workgroup);
 //   2. T splits into blocks where an off-diagonal is negligible against its
 //      neighbours or exactly zero (as between the parity sectors of a
-//      sector-ordered matrix); every eigenvalue of every block by bisection
-//      on Sturm counts, one thread per eigenvalue, then sorted descending;
-//   3. the number kk of vectors needed: k, extended while the next
-//      eigenvalue continues a cluster (gap <= cluster_rel * lambda_max);
-//   4. each needed eigenvector of its block by inverse iteration: LU with
-//      partial pivoting of T_b - lambda I (pivots below eps ||T_b|| raised to
-//      that size), three solves from a fixed start vector, each followed by
-//      Gram-Schmidt against the block's earlier vectors and normalisation;
-//      one wave per block, vectors in descending order (Wilkinson, The
-//      Algebraic Eigenvalue Problem, 1965, ch. 5 and 9);
-//   5. back-transformation by the reflectors, one wave per vector;
-//   6. V gets the kk vectors as its leading columns (zeros elsewhere), w
-//      every eigenvalue, status the number of vectors computed.
-// work: per matrix 2 n^2 + TOP_WAVES * 6 n doubles (reflectors row by row,
-// the vectors, each wave's LU factors and iterate).
-constexpr int TOP_THREADS = 1024;
-constexpr int TOP_WAVES = TOP_THREADS / 64;
+//      sector-ordered matrix); every eigenvalue of every block by
+//      multisection on Sturm counts (td_values_kernel);
+//   3. sorted descending; the number kk of vectors needed: k, extended while
+//      the next eigenvalue continues a cluster (gap <= cluster_rel *
+//      lambda_max);
+//   4. inverse iteration for the kk vectors at once, one lane per vector: LU
+//      with partial pivoting of T_b - lambda I (pivots below eps ||T_b||
+//      raised to that size), three solves from fixed start vectors, each
+//      followed by Gram-Schmidt in descending order (td_vectors_kernel;
+//      Wilkinson, The Algebraic Eigenvalue Problem, 1965, ch. 5 and 9);
+//   5. back-transformation by the reflectors, one wave per vector
+//      (td_back_kernel); V gets the kk vectors as its leading columns (zeros
+//      elsewhere), w every eigenvalue, status the number of vectors computed.
+// What bounds it is latency: a column's reflector needs the whole previous
+// update, and each recurrence along T is a chain of divisions.  Measured:
+// 9.4 ms for six matrices of order 576 with 24 vectors (448 columns of 10 us,
+// 0.6 ms in LDS, values 1.1, vectors 1.6) and 2.0 ms for two of order 196 (68
+// columns of 7 us, 0.6 in LDS, 0.4, 0.4), against 81 and 11.2 ms with one
+// workgroup per matrix for all of it (140 us a column at order 576: 2.6 MB
+// through one CU and 33 barriers).
+constexpr int TD_THREADS = 256, TD_WAVES = TD_THREADS / 64;
+constexpr int TD_LDS = 128;          // order from which the trailing matrix lives in LDS
+constexpr int TD_FIN = 1024;         // threads of td_finish_kernel and td_vectors_kernel
 constexpr int TOP_ITERS = 3;
+constexpr int TD_CHUNK = 64;         // vectors solved together: lanes of a wave
+constexpr int TD_MS = 16;            // multisection points per eigenvalue
+// doubles of scratch per n beside two n x n matrices; td_scratch uses 78 of them
+constexpr int TOP_SCRATCH = 96;
 
 __device__ inline double top_wave_sum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
+}
+__device__ inline double top_wave_max(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+// over the NW waves of a workgroup, in a fixed order; sh: NW doubles, free again after the next barrier
+template <int NW, bool MAX>
+__device__ inline double td_reduce(double v, double *sh) {
+  v = MAX ? top_wave_max(v) : top_wave_sum(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double r = sh[0];
+  for (int i = 1; i < NW; ++i) r = MAX ? fmax(r, sh[i]) : r + sh[i];
+  return r;
 }
 
 // fixed start vector of inverse iteration: entries in [-1, 1) from a hash of
@@ -551,223 +576,558 @@ __device__ inline double top_start(int r, int i) {
   return double(x) * (2.0 / 4294967296.0) - 1.0;
 }
 
-__global__ void __launch_bounds__(TOP_THREADS)
-tridiag_top_kernel(double *Aall, double *wall, double *Vall, int *status, int n, int k, double cluster_rel,
-                   double *workall) {
-  __shared__ double sh[TOP_THREADS];
-  __shared__ double vv[TQ_MAX], ww[TQ_MAX], w2[TQ_MAX];
-  __shared__ double dd[TQ_MAX], ee[TQ_MAX];
-  __shared__ int blk_of[TQ_MAX], bstart[TQ_MAX + 1], slot_of[TQ_MAX];
-  __shared__ int nblk_s, kk_s;
-  double *lam = vv, *ee2 = w2;   // reused once the reduction is done
-  const int b = blockIdx.x;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  double *A = Aall + size_t(b) * n * n;
-  double *V = Vall + size_t(b) * n * n;
-  double *w = wall + size_t(b) * n;
-  double *work = workall + size_t(b) * (size_t(2) * n * n + size_t(TOP_WAVES) * 6 * n);
-  double *Ur = work;                          // reflector j in row j (entries of rows j+1..n-1)
-  double *Zv = work + size_t(n) * n;          // vector of rank r in row r
-  double *scr = work + size_t(2) * n * n + size_t(wave) * 6 * n;
-  const double eps = 2.220446049250313e-16;
+// scratch of one matrix (offsets in units of n doubles from its end of work)
+struct TdScratch {
+  double *dd, *ee, *lam, *p[2], *v[2], *tau;   // diagonal, subdiagonal, eigenvalues by slot, A v and v of a column
+  int *slot_of, *s0, *e0, *kk;                 // slot of each rank, block of each slot, vectors needed
+  unsigned long long *piv;                     // row swaps of the LU, one bit per lane
+  double *X;                                   // iterates of a chunk, [entry][lane]
+};
+__device__ inline TdScratch td_scratch(double *scr, int n) {
+  TdScratch t;
+  t.dd = scr;
+  t.ee = scr + n;
+  t.lam = scr + 2 * n;
+  t.p[0] = scr + 3 * n;
+  t.p[1] = scr + 4 * n;
+  t.v[0] = scr + 5 * n;
+  t.v[1] = scr + 6 * n;
+  t.tau = scr + 7 * n;
+  t.slot_of = reinterpret_cast<int *>(scr + 8 * n);
+  t.s0 = reinterpret_cast<int *>(scr + 9 * n);
+  t.e0 = reinterpret_cast<int *>(scr + 10 * n);
+  t.kk = reinterpret_cast<int *>(scr + 11 * n);
+  t.piv = reinterpret_cast<unsigned long long *>(scr + 12 * n);
+  t.X = scr + 13 * n;                          // 64 n
+  return t;
+}
+__device__ inline double *td_work(double *work, int n, int b) {
+  return work + size_t(b) * (size_t(2) * n * n + size_t(TOP_SCRATCH) * n);
+}
 
-  // ---- 1. tridiagonal T; reflectors out of V's columns into rows of Ur
-  tq_tridiagonalise(A, V, n, sh, vv, ww, w2, dd, ee);
-  for (int idx = t; idx < n * n; idx += TOP_THREADS) {
-    const int j = idx / n, i = idx % n;
-    Ur[idx] = (i < n - j - 1) ? V[size_t(j + 1 + i) * n + j] : 0.0;
-    Zv[idx] = 0.0;
+// Reflector of the column x (entries k+1.. of length m, in vv), scaled by a
+// power of two that brings its largest entry into [1, 2): H = I - tau v v^T
+// does not depend on the scale of v, and sums of squares of columns far below
+// the matrix's scale (a parity block of a Gram whose weights are 1e-150 of
+// the other block's) neither underflow nor make tau overflow.  vv becomes v
+// (zero and tau = 0 for a column that is reduced already); returns the new
+// subdiagonal entry.  Every thread calls it; vv is complete after it.
+template <int NT>
+__device__ inline double td_reflector(double *vv, int m, double &tau, double *sh0, double *sh1) {
+  const int t = threadIdx.x;
+  double amax = 0.0;
+  for (int i = t; i < m; i += NT) amax = fmax(amax, fabs(vv[i]));
+  amax = td_reduce<NT / 64, true>(amax, sh0);
+  int ex = 0;
+  if (amax > 0.0) (void)frexp(amax, &ex);
+  double s2 = 0.0;
+  for (int i = t; i < m; i += NT) {
+    const double x = ldexp(vv[i], -ex);
+    s2 += x * x;
+  }
+  const double raw0 = vv[0];
+  const double nrm2 = td_reduce<NT / 64, false>(s2, sh1);   // its barrier: raw0 is read everywhere
+  const double x0 = ldexp(raw0, -ex);
+  const double alpha = x0 >= 0.0 ? -sqrt(nrm2) : sqrt(nrm2);
+  const double vtv = nrm2 - 2.0 * alpha * x0 + alpha * alpha;  // |x - alpha e1|^2
+  const bool on = amax > 0.0 && vtv > 0.0;
+  tau = on ? 2.0 / vtv : 0.0;
+  for (int i = t; i < m; i += NT) vv[i] = on ? (i == 0 ? x0 - alpha : ldexp(vv[i], -ex)) : 0.0;
+  __syncthreads();
+  return on ? ldexp(alpha, ex) : raw0;
+}
+
+// Column k: every workgroup of a matrix rebuilds w of column k - 1 from its
+// product p = A v, brings row k up to date and forms the reflector of column
+// k; then each wave updates its rows of the trailing matrix with column k - 1
+// and multiplies them by the new v in the same pass, so the matrix is read and
+// written once per column.
+__global__ void __launch_bounds__(TD_THREADS)
+td_column_kernel(double *Aall, double *workall, int n, int k) {
+  __shared__ double vo[MAX_N], wo[MAX_N], vn[MAX_N];
+  __shared__ double sh[3][TD_WAVES];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  double *A = Aall + size_t(blockIdx.y) * n * n;
+  double *work = td_work(workall, n, blockIdx.y);
+  TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  const int m = n - k - 1;                 // trailing order; entry i of vn is row k + 1 + i
+  const double *p = T.p[(k + 1) & 1], *vp = T.v[(k + 1) & 1];
+  double tau_o = 0.0;
+  if (k > 0) {
+    // vo, wo: entries of rows k .. n - 1
+    tau_o = T.tau[k - 1];
+    double pv = 0.0;
+    for (int i = t; i <= m; i += TD_THREADS) {
+      vo[i] = vp[i];
+      wo[i] = tau_o * p[i];
+      pv += wo[i] * vo[i];
+    }
+    const double K = 0.5 * tau_o * td_reduce<TD_WAVES, false>(pv, sh[0]);
+    for (int i = t; i <= m; i += TD_THREADS) wo[i] -= K * vo[i];
+  } else {
+    for (int i = t; i <= m; i += TD_THREADS) vo[i] = wo[i] = 0.0;
   }
   __syncthreads();
-  // ---- 2. blocks, bisection
+  const double v0 = vo[0], w0 = wo[0];
+  const double *row = A + size_t(k) * n + k;
+  for (int i = t; i < m; i += TD_THREADS) vn[i] = row[1 + i] - (v0 * wo[1 + i] + w0 * vo[1 + i]);
+  __syncthreads();
+  double tau;
+  const double sub = td_reflector<TD_THREADS>(vn, m, tau, sh[1], sh[2]);
+  if (blockIdx.x == 0) {
+    double *u = work + size_t(k) * n;      // reflector k, scaled: H = I - u u^T
+    const double st = sqrt(tau);
+    for (int i = t; i < n; i += TD_THREADS) u[i] = i > k ? vn[i - k - 1] * st : 0.0;
+    double *vk = T.v[k & 1];
+    for (int i = t; i < m; i += TD_THREADS) vk[i] = vn[i];
+    if (t == 0) {
+      T.dd[k] = row[0] - 2.0 * v0 * w0;
+      T.ee[k] = sub;
+      T.tau[k] = tau;
+    }
+  }
+  // rows of this wave, two at a time
+  const int nw = gridDim.x * TD_WAVES;
+  double *pk = T.p[k & 1];
+  for (int i0 = (blockIdx.x * TD_WAVES + wave) * 2; i0 < m; i0 += 2 * nw) {
+    const bool two = i0 + 1 < m;
+    double *r0 = A + size_t(k + 1 + i0) * n + k + 1, *r1 = two ? r0 + n : r0;
+    const double a0 = vo[1 + i0], b0 = wo[1 + i0], a1 = two ? vo[2 + i0] : a0, b1 = two ? wo[2 + i0] : b0;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+    for (int j = lane; j < m; j += 64) {
+      const double wj = wo[1 + j], vj = vo[1 + j], nj = vn[j];
+      const double x0 = r0[j] - (a0 * wj + b0 * vj), x1 = r1[j] - (a1 * wj + b1 * vj);
+      r0[j] = x0;
+      if (two) r1[j] = x1;
+      s0 += x0 * nj;
+      s1 += x1 * nj;
+    }
+    s0 = top_wave_sum(s0);
+    s1 = top_wave_sum(s1);
+    if (lane == 0) {
+      pk[i0] = s0;
+      if (two) pk[i0 + 1] = s1;
+    }
+  }
+}
+
+// The last columns (trailing order q = n - k0 <= TD_LDS) with the matrix in LDS
+constexpr int TD_LD = TD_LDS + 1;
+
+__global__ void __launch_bounds__(TD_FIN)
+td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
+  extern __shared__ double L[];            // TD_LDS x TD_LD
+  __shared__ double vo[TD_LDS], wo[TD_LDS], part[8][TD_LDS];
+  __shared__ double sh[3][TD_FIN / 64];
+  const int t = threadIdx.x;
+  const double *A = Aall + size_t(blockIdx.x) * n * n;
+  double *work = td_work(workall, n, blockIdx.x);
+  TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  const int q = n - k0;
+  {
+    const double *p = T.p[(k0 + 1) & 1], *vp = T.v[(k0 + 1) & 1];
+    const double tau = k0 > 0 ? T.tau[k0 - 1] : 0.0;
+    double pv = 0.0;
+    if (t < q) {
+      vo[t] = k0 > 0 ? vp[t] : 0.0;
+      wo[t] = k0 > 0 ? tau * p[t] : 0.0;
+      pv = wo[t] * vo[t];
+    }
+    const double K = 0.5 * tau * td_reduce<TD_FIN / 64, false>(pv, sh[0]);
+    if (t < q) wo[t] -= K * vo[t];
+    __syncthreads();
+    for (int idx = t; idx < q * q; idx += TD_FIN) {
+      const int i = idx / q, j = idx - i * q;
+      L[i * TD_LD + j] = A[size_t(k0 + i) * n + k0 + j] - (vo[i] * wo[j] + wo[i] * vo[j]);
+    }
+  }
+  __syncthreads();
+  // thread (g, c) of 8 x 128: column c, every eighth row
+  const int c = t & (TD_LDS - 1), g = t / TD_LDS;
+  for (int s = 0; s + 2 < q; ++s) {
+    const int m = q - s - 1, k = k0 + s;
+    double *sub = L + (s + 1) * TD_LD + s + 1;   // trailing m x m
+    if (t < m) vo[t] = L[s * TD_LD + s + 1 + t];
+    __syncthreads();
+    double tau;
+    const double off = td_reflector<TD_FIN>(vo, m, tau, sh[0], sh[1]);
+    double a = 0.0;
+    if (c < m)
+      for (int i = g; i < m; i += 8) a += sub[i * TD_LD + c] * vo[i];
+    part[g][c] = a;
+    __syncthreads();
+    double pv = 0.0;
+    if (t < m) {
+      double x = part[0][t];
+      for (int u = 1; u < 8; ++u) x += part[u][t];
+      wo[t] = tau * x;
+      pv = wo[t] * vo[t];
+    }
+    const double K = 0.5 * tau * td_reduce<TD_FIN / 64, false>(pv, sh[2]);
+    if (t < m) wo[t] -= K * vo[t];
+    __syncthreads();
+    if (c < m) {
+      const double vc = vo[c], wc = wo[c];
+      for (int i = g; i < m; i += 8) sub[i * TD_LD + c] -= vo[i] * wc + wo[i] * vc;
+    }
+    double *u = work + size_t(k) * n;
+    const double st = sqrt(tau);
+    for (int i = t; i < n; i += TD_FIN) u[i] = i > k ? vo[i - k - 1] * st : 0.0;
+    if (t == 0) {
+      T.dd[k] = L[s * TD_LD + s];
+      T.ee[k] = off;
+    }
+    __syncthreads();
+  }
   if (t == 0) {
-    int nb = 0;
-    bstart[0] = 0;
-    for (int i = 0; i + 1 < n; ++i) {
-      const double lim = eps * sqrt(fabs(dd[i])) * sqrt(fabs(dd[i + 1]));
-      if (ee[i] == 0.0 || fabs(ee[i]) <= lim) {
-        ee[i] = 0.0;
-        bstart[++nb] = i + 1;
-      }
-    }
-    bstart[++nb] = n;
-    nblk_s = nb;
+    const int e = q - 2;
+    T.dd[n - 2] = L[e * TD_LD + e];
+    T.ee[n - 2] = L[(e + 1) * TD_LD + e];
+    T.dd[n - 1] = L[(e + 1) * TD_LD + e + 1];
+    T.ee[n - 1] = 0.0;
+  }
+}
+
+// Eigenvalues of T, TD_MS lanes each: every lane counts the eigenvalues of
+// its slot's block below one of TD_MS equally spaced points, so a pass
+// shrinks the interval 17-fold (14 passes to the rounding level instead of 55
+// halvings, each a chain of n divisions).
+__global__ void __launch_bounds__(TD_THREADS)
+td_values_kernel(double *workall, int n) {
+  __shared__ double dd[MAX_N], ee[MAX_N], ee2[MAX_N];
+  __shared__ int s0s[MAX_N], e0s[MAX_N];
+  const int t = threadIdx.x, lane = t & 63;
+  double *work = td_work(workall, n, blockIdx.y);
+  TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  const double eps = 2.220446049250313e-16;
+  for (int i = t; i < n; i += TD_THREADS) {
+    dd[i] = T.dd[i];
+    ee[i] = T.ee[i];
   }
   __syncthreads();
-  const int nblk = nblk_s;
-  for (int i = t; i < n; i += TOP_THREADS) {
-    int lo = 0, hi = nblk;   // bstart[lo] <= i < bstart[hi]
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (bstart[mid] <= i) lo = mid;
-      else hi = mid;
-    }
-    blk_of[i] = lo;
-    ee2[i] = ee[i] * ee[i];
+  for (int i = t; i < n; i += TD_THREADS) {
+    // negligible against its neighbours or exactly zero: a block ends at i
+    double e = ee[i];
+    if (i + 1 < n && fabs(e) <= eps * sqrt(fabs(dd[i])) * sqrt(fabs(dd[i + 1]))) e = 0.0;
+    ee2[i] = i + 1 < n ? e : 0.0;
   }
   __syncthreads();
-  for (int slot = t; slot < n; slot += TOP_THREADS) {
-    const int bb = blk_of[slot], s0 = bstart[bb], e0 = bstart[bb + 1];
-    const int target = e0 - slot;   // (slot - s0 + 1)-th largest = target-th smallest
-    double lo = 0.0, hi = 0.0, emax2 = 0.0;
-    for (int i = s0; i < e0; ++i) {
-      const double r = (i > s0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < e0 ? fabs(ee[i]) : 0.0);
-      lo = i == s0 ? dd[i] - r : fmin(lo, dd[i] - r);
-      hi = i == s0 ? dd[i] + r : fmax(hi, dd[i] + r);
-      if (i + 1 < e0) emax2 = fmax(emax2, ee2[i]);
+  if (t < 64) {   // block bounds of every slot, 64 slots at a time
+    int start = 0;
+    for (int base = 0; base < n; base += 64) {
+      const int i = base + lane;
+      const unsigned long long ends = __ballot(i > 0 && i < n && ee2[i > 0 ? i - 1 : 0] == 0.0);
+      const unsigned long long upto = ends & (~0ull >> (63 - lane));
+      if (i < n) s0s[i] = upto ? base + 63 - __clzll(upto) : start;
+      if (ends) start = base + 63 - __clzll(ends);
     }
-    const double bn = fmax(fabs(lo), fabs(hi));
-    const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax2);
-    lo -= 2.0 * eps * bn + pivmin;
-    hi += 2.0 * eps * bn + pivmin;
-    for (int it = 0; it < 120; ++it) {
-      const double mid = 0.5 * (lo + hi);
-      if (!(mid > lo && mid < hi) || hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + pivmin) break;
-      // Sturm count: eigenvalues of the block below mid
-      int cnt = 0;
-      double q = dd[s0] - mid;
+    int stop = n;
+    for (int base = (n - 1) / 64 * 64; base >= 0; base -= 64) {
+      const int i = base + lane;
+      const unsigned long long ends = __ballot(i < n && ee2[i < n ? i : 0] == 0.0);
+      const unsigned long long from = ends & (~0ull << lane);
+      if (i < n) e0s[i] = from ? base + __ffsll(from) : stop;
+      if (ends) stop = base + __ffsll(ends);
+    }
+  }
+  __syncthreads();
+  for (int i = t; i < n; i += TD_THREADS) {
+    const double e = ee2[i];
+    if (blockIdx.x == 0) {
+      T.ee[i] = e;                         // cleaned; read by td_vectors_kernel
+      T.s0[i] = s0s[i];
+      T.e0[i] = e0s[i];
+    }
+    ee[i] = e;
+    ee2[i] = e * e;
+  }
+  __syncthreads();
+  const int slot = (blockIdx.x * TD_THREADS + t) / TD_MS, l = t % TD_MS;
+  if (slot >= n) return;   // whole groups of TD_MS lanes
+  const int s0 = s0s[slot], e0 = e0s[slot];
+  const int target = e0 - slot;   // (slot - s0 + 1)-th largest = target-th smallest
+  double lo = 0.0, hi = 0.0, emax2 = 0.0;
+  for (int i = s0 + l; i < e0; i += TD_MS) {
+    const double r = (i > s0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < e0 ? fabs(ee[i]) : 0.0);
+    lo = i == s0 + l ? dd[i] - r : fmin(lo, dd[i] - r);
+    hi = i == s0 + l ? dd[i] + r : fmax(hi, dd[i] + r);
+    if (i + 1 < e0) emax2 = fmax(emax2, ee2[i]);
+  }
+  const bool any = s0 + l < e0;
+  if (!any) {
+    lo = 1.7976931348623157e308;
+    hi = -1.7976931348623157e308;
+  }
+  for (int off = TD_MS / 2; off > 0; off >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, off, 64));
+    hi = fmax(hi, __shfl_xor(hi, off, 64));
+    emax2 = fmax(emax2, __shfl_xor(emax2, off, 64));
+  }
+  const double bn = fmax(fabs(lo), fabs(hi));
+  const double pivmin = 2.2250738585072014e-308 * fmax(1.0, emax2);
+  lo -= 2.0 * eps * bn + pivmin;
+  hi += 2.0 * eps * bn + pivmin;
+  for (int it = 0; it < 120; ++it) {
+    const double mid = 0.5 * (lo + hi);
+    if (!(mid > lo && mid < hi) || hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + pivmin) break;
+    double x = lo + (hi - lo) * (double(l + 1) * (1.0 / (TD_MS + 1)));
+    x = fmin(fmax(x, lo), hi);
+    // Sturm count: eigenvalues of the block below x
+    int cnt = 0;
+    double q = dd[s0] - x;
+    if (fabs(q) < pivmin) q = -pivmin;
+    cnt += q < 0.0;
+    for (int i = s0 + 1; i < e0; ++i) {
+      q = (dd[i] - x) - ee2[i - 1] / q;
       if (fabs(q) < pivmin) q = -pivmin;
       cnt += q < 0.0;
-      for (int i = s0 + 1; i < e0; ++i) {
-        q = (dd[i] - mid) - ee2[i - 1] / q;
-        if (fabs(q) < pivmin) q = -pivmin;
-        cnt += q < 0.0;
-      }
-      if (cnt >= target) hi = mid;
-      else lo = mid;
     }
-    lam[slot] = 0.5 * (lo + hi);
+    // the first point with enough eigenvalues below it bounds the slot's from above
+    const unsigned mine = unsigned(__ballot(cnt >= target) >> (lane & ~(TD_MS - 1))) & ((1u << TD_MS) - 1);
+    const int f = mine ? __ffs(mine) - 1 : TD_MS;
+    const double xf = __shfl(x, (lane & ~(TD_MS - 1)) + (f < TD_MS ? f : TD_MS - 1), 64);
+    const double xb = __shfl(x, (lane & ~(TD_MS - 1)) + (f > 0 ? f - 1 : 0), 64);
+    const double nhi = f < TD_MS ? xf : hi, nlo = f > 0 ? xb : lo;
+    if (nlo == lo && nhi == hi) break;     // the points no longer separate the ends
+    lo = nlo;
+    hi = nhi;
+  }
+  if (l == 0) T.lam[slot] = 0.5 * (lo + hi);
+}
+
+// Sorting, the number of vectors and the inverse iteration of one matrix.
+// A and V (n x n each, free by now) hold the LU factors of a chunk.
+__global__ void __launch_bounds__(TD_FIN)
+td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, int k, double cluster_rel,
+                  double *workall) {
+  __shared__ double dd[MAX_N], ee[MAX_N], lam[MAX_N], w[MAX_N];
+  __shared__ int slot_of[MAX_N];
+  __shared__ int kk_s;
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  double *work = td_work(workall, n, b);
+  TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  double *Zv = work + size_t(n) * n;       // vector of rank r in row r
+  double *D = Aall + size_t(b) * n * n, *DL = D + size_t(TD_CHUNK) * n;
+  double *DU = Vall + size_t(b) * n * n, *DU2 = DU + size_t(TD_CHUNK) * n;
+  const double eps = 2.220446049250313e-16;
+  for (int i = t; i < n; i += TD_FIN) {
+    dd[i] = T.dd[i];
+    ee[i] = T.ee[i];
+    lam[i] = T.lam[i];
   }
   __syncthreads();
   // ---- sort descending (ties by slot)
-  for (int slot = t; slot < n; slot += TOP_THREADS) {
+  for (int slot = t; slot < n; slot += TD_FIN) {
     const double v = lam[slot];
     int rk = 0;
     for (int u = 0; u < n; ++u) rk += (lam[u] > v) || (lam[u] == v && u < slot);
     w[rk] = v;
     slot_of[rk] = slot;
+    wall[size_t(b) * n + rk] = v;
   }
   __syncthreads();
-  // ---- 3. vectors needed
   if (t == 0) {
     const double tol = cluster_rel * fmax(w[0], 0.0);
     int bnd = k < n ? k : n;
     while (bnd < n && w[bnd - 1] - w[bnd] <= tol) ++bnd;
     kk_s = bnd;
+    status[b] = bnd;
+    *T.kk = bnd;
   }
   __syncthreads();
   const int kk = kk_s;
-  // ---- 4. inverse iteration, one wave per block
-  double *DL = scr, *D = scr + n, *DU = scr + 2 * n, *DU2 = scr + 3 * n, *PV = scr + 4 * n, *X = scr + 5 * n;
-  for (int bb = wave; bb < nblk; bb += TOP_WAVES) {
-    const int s0 = bstart[bb], e0 = bstart[bb + 1], nb = e0 - s0;
-    double bnorm = 0.0;
-    for (int i = s0 + lane; i < e0; i += 64)
-      bnorm = fmax(bnorm, fabs(dd[i]) + (i > s0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < e0 ? fabs(ee[i]) : 0.0));
-    for (int off = 32; off > 0; off >>= 1) bnorm = fmax(bnorm, __shfl_xor(bnorm, off, 64));
-    const double ptol = fmax(eps * bnorm, 2.2250738585072014e-308);
-    for (int r = 0; r < kk; ++r) {
-      const int slot = slot_of[r];
-      if (slot < s0 || slot >= e0) continue;   // uniform: every lane reads the same slot
-      const double sigma = w[r];
-      if (lane == 0) {
-        // LU with partial pivoting of T_b - sigma I (rows i, i+1 swapped where PV[i] = 1)
-        for (int i = 0; i < nb; ++i) {
-          D[i] = dd[s0 + i] - sigma;
-          DL[i] = i + 1 < nb ? ee[s0 + i] : 0.0;
-          DU[i] = DL[i];
-          DU2[i] = 0.0;
-        }
-        for (int i = 0; i + 1 < nb; ++i) {
-          if (fabs(D[i]) >= fabs(DL[i])) {
-            PV[i] = 0.0;
-            const double f = D[i] != 0.0 ? DL[i] / D[i] : 0.0;
-            DL[i] = f;
-            D[i + 1] -= f * DU[i];
-          } else {
-            PV[i] = 1.0;
-            const double f = D[i] / DL[i];
-            D[i] = DL[i];
-            DL[i] = f;
-            const double tmp = DU[i];
-            DU[i] = D[i + 1];
-            D[i + 1] = tmp - f * D[i + 1];
-            if (i + 2 < nb) {
-              DU2[i] = DU[i + 1];
-              DU[i + 1] = -f * DU[i + 1];
-            }
-          }
-        }
+  const int chunks = (kk + TD_CHUNK - 1) / TD_CHUNK;
+  for (int it = 0; it < TOP_ITERS; ++it) {
+    for (int ch = 0; ch < chunks; ++ch) {
+      const int r0 = ch * TD_CHUNK, nr = kk - r0 < TD_CHUNK ? kk - r0 : TD_CHUNK;
+      // iterates of the chunk, transposed: X[i][lane] = entry i of the lane's block
+      for (int idx = t; idx < nr * n; idx += TD_FIN) {
+        const int r = idx / n, i = idx - r * n, s = slot_of[r0 + r], s0 = T.s0[s], e0 = T.e0[s];
+        if (i < e0 - s0) T.X[size_t(i) * TD_CHUNK + r] = it == 0 ? top_start(r0 + r, i) : Zv[size_t(r0 + r) * n + s0 + i];
+        if (it == 0 && (i < s0 || i >= e0)) Zv[size_t(r0 + r) * n + i] = 0.0;
       }
-      for (int i = lane; i < nb; i += 64) X[i] = top_start(r, i);
-      __builtin_amdgcn_wave_barrier();
-      __threadfence_block();
-      for (int it = 0; it < TOP_ITERS; ++it) {
-        if (lane == 0) {
+      __syncthreads();
+      if (wave == 0 && lane < nr) {
+        const int s = slot_of[r0 + lane], s0 = T.s0[s], nb = T.e0[s] - s0;
+        const double sigma = w[r0 + lane];
+        double bnorm = 0.0;
+        for (int i = s0; i < s0 + nb; ++i)
+          bnorm = fmax(bnorm, fabs(dd[i]) + (i > s0 ? fabs(ee[i - 1]) : 0.0) + (i + 1 < s0 + nb ? fabs(ee[i]) : 0.0));
+        const double ptol = fmax(eps * bnorm, 2.2250738585072014e-308);
+        auto inverse = [&](double piv) {
+          if (fabs(piv) < ptol) piv = piv >= 0.0 ? ptol : -ptol;
+          return 1.0 / piv;
+        };
+        double *X = T.X + lane, *d = D + lane, *dl = DL + lane, *du = DU + lane, *du2 = DU2 + lane;
+        // LU with partial pivoting of T_b - sigma I and the forward sweep
+        // together; d holds inverse pivots.  The pivots that a chunk leaves
+        // serve its later solves while they are still there (one chunk).
+        double xc = X[0];
+        if (it == 0 || chunks > 1) {
+          double dc = dd[s0] - sigma, uc = nb > 1 ? ee[s0] : 0.0;
           for (int i = 0; i + 1 < nb; ++i) {
-            if (PV[i] == 0.0) {
-              X[i + 1] -= DL[i] * X[i];
-            } else {
-              const double tmp = X[i];
-              X[i] = X[i + 1];
-              X[i + 1] = tmp - DL[i] * X[i];
-            }
+            const size_t o = size_t(i) * TD_CHUNK;
+            const double e = ee[s0 + i], dn = dd[s0 + i + 1] - sigma, un = i + 2 < nb ? ee[s0 + i + 1] : 0.0;
+            const double xn = X[o + TD_CHUNK];
+            const bool swap = !(fabs(dc) >= fabs(e));
+            const double num = swap ? dc : e, den = swap ? e : dc;
+            const double f = den != 0.0 ? num / den : 0.0;
+            d[o] = inverse(den);
+            dl[o] = f;
+            du[o] = swap ? dn : uc;
+            du2[o] = swap ? un : 0.0;
+            const unsigned long long mask = __ballot(swap);
+            if (lane == __ffsll(__ballot(1)) - 1) T.piv[i] = mask;
+            dc = swap ? uc - f * dn : dn - f * uc;
+            uc = swap ? -f * un : un;
+            X[o] = swap ? xn : xc;
+            xc = swap ? xc - f * xn : xn - f * xc;
           }
-          for (int i = nb - 1; i >= 0; --i) {
-            double piv = D[i];
-            if (fabs(piv) < ptol) piv = piv >= 0.0 ? ptol : -ptol;
-            double v = X[i];
-            if (i + 1 < nb) v -= DU[i] * X[i + 1];
-            if (i + 2 < nb) v -= DU2[i] * X[i + 2];
-            X[i] = v / piv;
+          d[size_t(nb - 1) * TD_CHUNK] = inverse(dc);
+        } else {
+#pragma unroll 4
+          for (int i = 0; i + 1 < nb; ++i) {
+            const size_t o = size_t(i) * TD_CHUNK;
+            const double xn = X[o + TD_CHUNK], f = dl[o];
+            const bool swap = (T.piv[i] >> lane) & 1;
+            X[o] = swap ? xn : xc;
+            xc = swap ? xc - f * xn : xn - f * xc;
           }
         }
-        __builtin_amdgcn_wave_barrier();
-        __threadfence_block();
-        // Gram-Schmidt against the block's earlier vectors, then normalise
-        for (int r2 = 0; r2 < r; ++r2) {
-          const int sl2 = slot_of[r2];
-          if (sl2 < s0 || sl2 >= e0) continue;
-          const double *z = Zv + size_t(r2) * n + s0;
-          double dot = 0.0;
-          for (int i = lane; i < nb; i += 64) dot += z[i] * X[i];
-          dot = top_wave_sum(dot);
-          for (int i = lane; i < nb; i += 64) X[i] -= dot * z[i];
+        double x1 = xc * d[size_t(nb - 1) * TD_CHUNK], x2 = 0.0;
+        X[size_t(nb - 1) * TD_CHUNK] = x1;
+#pragma unroll 4
+        for (int i = nb - 2; i >= 0; --i) {
+          const size_t o = size_t(i) * TD_CHUNK;
+          const double x = (X[o] - du[o] * x1 - du2[o] * x2) * d[o];
+          X[o] = x;
+          x2 = x1;
+          x1 = x;
         }
-        double nrm = 0.0;
-        for (int i = lane; i < nb; i += 64) nrm += X[i] * X[i];
-        nrm = top_wave_sum(nrm);
-        const double inv = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
-        for (int i = lane; i < nb; i += 64) X[i] *= inv;
-        __builtin_amdgcn_wave_barrier();
-        __threadfence_block();
       }
-      for (int i = lane; i < nb; i += 64) Zv[size_t(r) * n + s0 + i] = X[i];
-      __builtin_amdgcn_wave_barrier();
-      __threadfence_block();
+      __syncthreads();
+      for (int idx = t; idx < nr * n; idx += TD_FIN) {
+        const int r = idx / n, i = idx - r * n, s = slot_of[r0 + r], s0 = T.s0[s], e0 = T.e0[s];
+        if (i < e0 - s0) Zv[size_t(r0 + r) * n + s0 + i] = T.X[size_t(i) * TD_CHUNK + r];
+      }
+      __syncthreads();
     }
-  }
-  __syncthreads();
-  // ---- 5. back-transformation z <- H_0 ... H_{n-3} z, one wave per vector
-  for (int r = wave; r < kk; r += TOP_WAVES) {
-    double *z = Zv + size_t(r) * n;
-    for (int j = n - 3; j >= 0; --j) {
-      const int m = n - j - 1;
-      const double *u = Ur + size_t(j) * n;
-      double dot = 0.0;
-      for (int i = lane; i < m; i += 64) dot += u[i] * z[j + 1 + i];
-      dot = top_wave_sum(dot);
-      if (dot != 0.0)
-        for (int i = lane; i < m; i += 64) z[j + 1 + i] -= u[i] * dot;
+    // Gram-Schmidt in descending order: vector r, normalised, is taken out of
+    // all later ones (vectors of different blocks have disjoint entries)
+    for (int r = 0; r < kk; ++r) {
+      double *z = Zv + size_t(r) * n;
+      double amax = 0.0;
+      for (int i = lane; i < n; i += 64) amax = fmax(amax, fabs(z[i]));
+      amax = top_wave_max(amax);
+      int ex = 0;
+      if (amax > 0.0) (void)frexp(amax, &ex);
+      double nrm = 0.0;
+      for (int i = lane; i < n; i += 64) {
+        const double x = ldexp(z[i], -ex);
+        nrm += x * x;
+      }
+      nrm = top_wave_sum(nrm);
+      const double inv = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
+      for (int r2 = r + 1 + wave; r2 < kk; r2 += TD_FIN / 64) {
+        double *y = Zv + size_t(r2) * n;
+        double dot = 0.0;
+        for (int i = lane; i < n; i += 64) dot += ldexp(z[i], -ex) * inv * y[i];
+        dot = top_wave_sum(dot);
+        if (dot != 0.0)
+          for (int i = lane; i < n; i += 64) y[i] -= dot * (ldexp(z[i], -ex) * inv);
+      }
+      __syncthreads();
+      if (wave == r % (TD_FIN / 64))   // nobody reads z in this pass any more
+        for (int i = lane; i < n; i += 64) z[i] = ldexp(z[i], -ex) * inv;
     }
+    __syncthreads();
   }
-  __syncthreads();
-  // ---- 6. output
-  for (int idx = t; idx < n * n; idx += TOP_THREADS) {
-    const int i = idx / n, c = idx % n;
-    V[idx] = c < kk ? Zv[size_t(c) * n + i] : 0.0;
+}
+
+// Back-transformation z <- H_0 ... H_{n-3} z, one wave per vector, z in
+// registers (entry lane + 64 u), the next reflector loaded during the sum.
+template <int R>
+__global__ void __launch_bounds__(TD_THREADS)
+td_back_kernel(double *workall, int n) {
+  const int lane = threadIdx.x & 63, r = blockIdx.x * TD_WAVES + (threadIdx.x >> 6);
+  double *work = td_work(workall, n, blockIdx.y);
+  const TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  if (r >= *T.kk) return;
+  double *zg = work + size_t(n) * n + size_t(r) * n;
+  double z[R], u[R], un[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int i = lane + 64 * q;
+    z[q] = i < n ? zg[i] : 0.0;
+    un[q] = i < n ? work[size_t(n - 3) * n + i] : 0.0;
   }
-  if (t == 0) status[b] = kk;
+  for (int j = n - 3; j >= 0; --j) {
+#pragma unroll
+    for (int q = 0; q < R; ++q) u[q] = un[q];
+    const double *next = work + size_t(j > 0 ? j - 1 : 0) * n;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int i = lane + 64 * q;
+      un[q] = i < n ? next[i] : 0.0;
+    }
+    double dot = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) dot += u[q] * z[q];
+    dot = top_wave_sum(dot);
+#pragma unroll
+    for (int q = 0; q < R; ++q) z[q] -= u[q] * dot;
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int i = lane + 64 * q;
+    if (i < n) zg[i] = z[q];
+  }
+}
+
+__global__ void __launch_bounds__(TD_THREADS)
+td_output_kernel(double *Vall, double *workall, int n) {
+  double *work = td_work(workall, n, blockIdx.y);
+  const TdScratch T = td_scratch(work + size_t(2) * n * n, n);
+  const double *Zv = work + size_t(n) * n;
+  const int kk = *T.kk;
+  for (int idx = blockIdx.x * TD_THREADS + threadIdx.x; idx < n * n; idx += gridDim.x * TD_THREADS) {
+    const int i = idx / n, c = idx - i * n;
+    Vall[size_t(blockIdx.y) * n * n + idx] = c < kk ? Zv[size_t(c) * n + i] : 0.0;
+  }
+}
+
+void launch_tridiag_top(double *A, double *w, double *V, int *sweeps, int n, int batch, int k, double cluster_rel,
+                        double *work, hipStream_t st) {
+  const size_t lds = size_t(TD_LDS) * TD_LD * 8;
+  static const bool attr = [&] {
+    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&td_finish_kernel),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    return true;
+  }();
+  (void)attr;
+  const int k0 = n > TD_LDS ? n - TD_LDS : 0;
+  for (int col = 0; col < k0; ++col) {
+    // about two workgroups per CU over the batch, at least two rows per wave
+    const int rows = n - col - 1;
+    const int want = (512 + batch - 1) / batch, most = (rows + 2 * TD_WAVES - 1) / (2 * TD_WAVES);
+    hipLaunchKernelGGL(td_column_kernel, dim3(uint32_t(want < most ? want : most), uint32_t(batch)), dim3(TD_THREADS), 0,
+                       st, A, work, n, col);
+  }
+  hipLaunchKernelGGL(td_finish_kernel, dim3(batch), dim3(TD_FIN), lds, st, A, work, n, k0);
+  hipLaunchKernelGGL(td_values_kernel, dim3(uint32_t((n * TD_MS + TD_THREADS - 1) / TD_THREADS), uint32_t(batch)),
+                     dim3(TD_THREADS), 0, st, work, n);
+  hipLaunchKernelGGL(td_vectors_kernel, dim3(batch), dim3(TD_FIN), 0, st, A, w, V, sweeps, n, k, cluster_rel, work);
+  const dim3 bg(uint32_t((n + TD_WAVES - 1) / TD_WAVES), uint32_t(batch));
+  if (n <= 256)
+    hipLaunchKernelGGL((td_back_kernel<4>), bg, dim3(TD_THREADS), 0, st, work, n);
+  else if (n <= 576)
+    hipLaunchKernelGGL((td_back_kernel<9>), bg, dim3(TD_THREADS), 0, st, work, n);
+  else
+    hipLaunchKernelGGL((td_back_kernel<16>), bg, dim3(TD_THREADS), 0, st, work, n);
+  hipLaunchKernelGGL(td_output_kernel, dim3(uint32_t((n * n + 4 * TD_THREADS - 1) / (4 * TD_THREADS)), uint32_t(batch)),
+                     dim3(TD_THREADS), 0, st, V, work, n);
+  TRG_HIP_CHECK(hipGetLastError());
 }
 
 // ------------------------------------------------------------- selection ---
@@ -888,7 +1248,7 @@ void eigh_batched(double *A, double *w, double *V, int *sweeps, int n, int batch
 }
 
 size_t eigh_top_work_doubles(int n, int batch) {
-  return size_t(batch) * (size_t(2) * n * n + size_t(TOP_WAVES) * 6 * n);
+  return size_t(batch) * (size_t(2) * n * n + size_t(TOP_SCRATCH) * n);
 }
 
 void eigh_top_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, int k, double cluster_rel,
@@ -898,8 +1258,7 @@ void eigh_top_batched(double *A, double *w, double *V, int *sweeps, int n, int b
     hipLaunchKernelGGL(jacobi_kernel, dim3(batch), dim3(EIGH_THREADS), 0, st, A, w, V, sweeps, n);
   } else {
     TRG_REQUIRE(work != nullptr, "eigh_top: workspace missing");
-    hipLaunchKernelGGL(tridiag_top_kernel, dim3(batch), dim3(TOP_THREADS), 0, st, A, w, V, sweeps, n, k,
-                       cluster_rel, work);
+    launch_tridiag_top(A, w, V, sweeps, n, batch, k, cluster_rel, work, st);
   }
   TRG_HIP_CHECK(hipGetLastError());
 }

@@ -379,6 +379,33 @@ def test_eigh_top_leading_pairs(n):
         assert np.max(np.abs(A[b] @ Vk - Vk * w[b][:q])) < 1e-12 * nrm
 
 
+@pytest.mark.parametrize("n,k,rank,batch", [(161, 1, 161, 1), (161, 65, 161, 3), (193, 20, 8, 2), (400, 130, 400, 1),
+                                            (577, 24, 577, 1), (1024, 3, 40, 1)])
+def test_eigh_top_edges(n, k, rank, batch):
+    """The edges of the selection solver: the smallest and the largest order,
+    one column and many reduced before the trailing matrix fits LDS, vectors
+    in one and in several chunks of 64, and Grams of low rank, whose zero
+    eigenvalues (most of the spectrum) form one cluster that the cut splits, so
+    that every vector is computed.  Bounds as above."""
+    announce("eigh_top edges", n, k, rank, batch)
+    rng = np.random.default_rng(n + k)
+    mats = []
+    for _ in range(batch):
+        X = rng.standard_normal((n, rank)) * 0.9 ** np.arange(rank)
+        mats.append(X @ X.T)
+    A = np.stack(mats)
+    w, V, kk = _eigh_top(A, k, 1e-10)
+    for b in range(batch):
+        nrm = np.linalg.norm(A[b])
+        assert np.max(np.abs(w[b] - np.linalg.eigvalsh(A[b])[::-1])) < 1e-13 * nrm
+        q = int(kk[b])
+        assert k <= q <= n and (q == n if rank < k else True)
+        Vk = V[b][:, :q]
+        assert np.all(V[b][:, q:] == 0.0)
+        assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
+        assert np.max(np.abs(A[b] @ Vk - Vk * w[b][:q])) < 1e-12 * nrm
+
+
 def test_eigh_top_extends_over_a_split_cluster():
     """Eigenvalues 5, 4, 3 (x3), 2, ...: with k = 3 the cut splits the triple,
     so kk = 5 vectors come back, spanning the triple's eigenspace."""
