@@ -3,13 +3,11 @@
 // environment) and the selection of the truncated isometry.
 //
 // Eigensolver: cyclic two-sided Jacobi in parallel (round-robin) order, one
-// workgroup per matrix.  Each round rotates n/2 disjoint index pairs: rows
-// first (A <- J^T A), then columns (A <- A J, V <- V J).  A sweep is n-1
-// rounds; sweeps repeat until the off-diagonal Frobenius norm falls below
-// 1e-14 of the matrix norm, plus one final sweep.  The matrix and vectors live in global memory
-// (they are small and stay in L2); the rotation parameters of a round are
-// in LDS.  Everything is deterministic: fixed pairing order, fixed
-// reduction trees.
+// workgroup per matrix.  Each round rotates n/2 disjoint index pairs (A <- J^T
+// A J, V <- V J).  A sweep is n-1 rounds; sweeps repeat until the off-diagonal
+// Frobenius norm falls below 1e-14 of the matrix norm, plus one final sweep.
+// Everything is deterministic: fixed pairing order, fixed reduction trees.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.h"
@@ -17,46 +15,237 @@
 namespace trg {
 namespace {
 
-constexpr int EIGH_THREADS = 512;
 constexpr int MAX_N = 1024;
 constexpr int MAX_SWEEPS = 40;
 
-__device__ inline double wg_sum(double v, double *sh) {
-  const int t = threadIdx.x;
-  sh[t] = v;
+__device__ inline double wave_sum(double v) {
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+__device__ inline double wave_max(double v) {
+  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
+  return v;
+}
+// over the NW waves of a workgroup, in a fixed order; sh: NW doubles, free again after the next barrier
+template <int NW, bool MAX>
+__device__ inline double wg_reduce(double v, double *sh) {
+  v = MAX ? wave_max(v) : wave_sum(v);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int s = EIGH_THREADS / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] += sh[t + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
+  double r = sh[0];
+  for (int i = 1; i < NW; ++i) r = MAX ? fmax(r, sh[i]) : r + sh[i];
   return r;
 }
 
-__global__ void __launch_bounds__(EIGH_THREADS)
-jacobi_kernel(double *Aall, double *wall, double *Vall, int *sweeps_out, int n) {
-  __shared__ double sh[EIGH_THREADS];
-  __shared__ int pp[MAX_N / 2], pq[MAX_N / 2];
-  __shared__ double pc[MAX_N / 2], ps[MAX_N / 2];
-  __shared__ double wdiag[MAX_N];
-  __shared__ int rank[MAX_N];
+// 1 / sqrt(x) for x in a range where nothing overflows: the hardware estimate
+// and two Newton steps
+__device__ inline double jac_rsqrt(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = y * __builtin_fma(-0.5 * x * y, y, 1.5);
+  return y * __builtin_fma(-0.5 * x * y, y, 1.5);
+}
 
-  const int b = blockIdx.x;
-  double *A = Aall + size_t(b) * n * n;
-  double *V = Vall + size_t(b) * n * n;
-  double *w = wall + size_t(b) * n;
-  const int t = threadIdx.x;
-  const int n2 = n * n;
+// Rotation (c, s), t = s / c that takes a_pq of [[app, apq], [apq, aqq]] to
+// zero: t = x sgn(d) / (|d| + sqrt(d^2 + x^2)), d = aqq - app, x = 2 apq, both
+// scaled by the power of two that brings the larger into [1, 2).  One chain
+// of multiplications from hardware estimates instead of two square roots and
+// three divisions; the last correction brings c^2 + s^2 back to 1 to a rounding, so
+// that the vectors' norms do not drift over a run's thousands of rotations.
+__device__ inline void jac_rotation(double app, double aqq, double apq, double &c, double &s, double &t) {
+  double d = aqq - app, x = 2.0 * apq;
+  int ex;
+  (void)frexp(fmax(fabs(d), fabs(x)), &ex);
+  d = ldexp(d, -ex);
+  x = ldexp(x, -ex);
+  const double hh = __builtin_fma(d, d, x * x);
+  const double den = __builtin_fma(hh, jac_rsqrt(hh), fabs(d));
+  double r = __builtin_amdgcn_rcp(den);
+  r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
+  r = __builtin_fma(r, __builtin_fma(-den, r, 1.0), r);
+  x = copysign(1.0, d) * x;
+  t = x * r;
+  t = __builtin_fma(__builtin_fma(-den, t, x), r, t);
+  c = jac_rsqrt(__builtin_fma(t, t, 1.0));
+  s = t * c;
+  const double e = 0.5 * __builtin_fma(-s, s, __builtin_fma(-c, c, 1.0));
+  c = __builtin_fma(e, c, c);
+  s = __builtin_fma(e, s, s);
+}
 
-  for (int i = t; i < n2; i += EIGH_THREADS) V[i] = (i / n == i % n) ? 1.0 : 0.0;
-  double fro = 0.0;
-  for (int i = t; i < n2; i += EIGH_THREADS) fro += A[i] * A[i];
+// LDS of one workgroup: A over np players (its lower triangle, or all of it),
+// rl rows of V (column by column), two sets of rotations, the reductions
+constexpr int JAC_LDS = 160 * 1024;
+constexpr size_t jac_fixed(int np, bool tri) {
+  return size_t(np) * (tri ? np + 1 : 2 * np) / 2 * 8 + size_t(np) * 16 + 512;
+}
+static_assert(jac_fixed(JACOBI_MAX_N, true) + size_t(JACOBI_MAX_N) * 8 * 8 <= JAC_LDS, "eight rows of V fit");
+static_assert(jac_fixed(JACOBI_SQUARE_N, false) + size_t(JACOBI_SQUARE_N) * 8 <= JAC_LDS, "a row of V fits");
+__device__ inline int jac_tri(int x, int y) {   // x >= y
+  return int(__umul24(x, x + 1) >> 1) + y;
+}
+
+// What bounds it: a round is a chain (three entries of A, the rotation, then
+// every entry of A moves once), and there are n - 1 rounds a sweep.  Hence A's
+// lower triangle in LDS, each 2 x 2 block of it taking both rotations in one
+// visit; and V by rows over blockIdx.x: every workgroup of a matrix repeats the
+// rotations of A (the same operations, the same bits) and applies them to its
+// own rows of V, while its first waves work out the next round's rotations.
+// Measured, six Gram-like and random matrices (square; triangle): order 16 0.14
+// ms, 36 0.26, 64 1.7; 1.2, 100 4.0; 2.6, 144 7.3 (triangle), against 0.26, 0.7,
+// 16.5, 46.6 and 180 ms with A and V in L2, rows and columns of all of A
+// rotated in turn by one workgroup; |V^T V - 1| of order 100 1.2e-13 (square,
+// as before), 5e-15 (triangle).
+//
+// TRI false keeps all of A and, operation for operation, the rotations of that
+// slower form (hypot, two square roots, three divisions), so that its
+// eigensystems come out bit for bit: in a mixed-precision HOTRG run the sign
+// and the pick among near-degenerate vectors hang on the last bits of the
+// Grams' eigensystems, and a run repeated, resumed or batched with another
+// form of the solver would part from its earlier tensors after a few steps.
+template <int NT, bool TRI>
+__global__ void __launch_bounds__(NT)
+jacobi_kernel(const double *Aall, double *wall, double *Vall, int *sweeps_out, int n, int rl, FastDiv by_n,
+              FastDiv by_rl, FastDiv by_half) {
+  extern __shared__ __attribute__((aligned(16))) double lds[];
+  __shared__ double red[4][NT / 64];
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  const int b = blockIdx.y, t = threadIdx.x, n2 = n * n;
+  const double *Ag = Aall + size_t(b) * n2;
+  double *Vg = Vall + size_t(b) * n2, *w = wall + size_t(b) * n;
+  const int np = (n + 1) & ~1;   // even number of players; index n is a dummy of zeros
+  const int half = np / 2, cyc = np - 1;
+  const int row0 = blockIdx.x * rl, rows = n - row0 < rl ? n - row0 : rl;
+  d2 *cs = reinterpret_cast<d2 *>(lds);   // rotations (16-byte aligned): set u, pair j at cs[u half + j]
+  double *A = lds + 2 * np;
+  const int elems = TRI ? np * (np + 1) / 2 : np * np;
+  double *V = A + elems;
+  // entry (x, y); the triangle needs x >= y
+  auto at = [&](int x, int y) { return TRI ? jac_tri(x, y) : x * np + y; };
+  for (int i = t; i < elems; i += NT) A[i] = 0.0;
+  for (int i = t; i < np * rl; i += NT) {
+    const int col = int(fast_div(i, by_rl));
+    V[i] = col == row0 + i - col * rl ? 1.0 : 0.0;
+  }
   __syncthreads();
-  const double norm2 = wg_sum(fro, sh);
+  double fro = 0.0;
+  for (int i = t; i < n2; i += NT) {
+    const int x = int(fast_div(i, by_n)), y = i - x * n;
+    const double v = Ag[i];
+    if (!TRI || x >= y) A[at(x, y)] = v;
+    fro += v * v;
+  }
+  const double norm2 = wg_reduce<NT / 64, false>(fro, red[0]);   // its barrier: A is complete
 
-  const int np = (n + 1) & ~1;  // even number of players; index n is a dummy
-  const int half = np / 2;
+  // pairs of round r: player np - 1 against r, r + j against r - j (mod np - 1)
+  auto players = [&](int r, int j, int &p, int &q) {
+    int x = r + j < cyc ? r + j : r + j - cyc;
+    int y = j == 0 ? cyc : (r - j >= 0 ? r - j : r - j + cyc);
+    p = x < y ? x : y;
+    q = x < y ? y : x;
+  };
+  auto rotate = [](d2 g, double &x, double &y) {
+    const double nx = __builtin_fma(g.x, x, -(g.y * y));
+    y = __builtin_fma(g.y, x, g.x * y);
+    x = nx;
+  };
+  auto offdiag = [&](double *sh) {
+    double v = 0.0;
+    for (int x = 1 + (t >> 6); x < n; x += NT / 64)
+      for (int y = t & 63; y < x; y += 64) {
+        const double a = A[at(x, y)];
+        v += a * a;
+      }
+    return 2.0 * wg_reduce<NT / 64, false>(v, sh);
+  };
+  // rotations of round r into set u, the 2 x 2 blocks on the diagonal included
+  auto pivots = [&](int r, int u) {
+    for (int j = t; j < half; j += NT) {
+      int p, q;
+      players(r, j, p, q);
+      double c = 1.0, s = 0.0;
+      const int iq = TRI ? jac_tri(q, p) : p * np + q;
+      const double apq = A[iq];
+      if constexpr (!TRI) {
+        if (apq != 0.0) {
+          const double tau = (A[q * np + q] - A[p * np + p]) / (2.0 * apq);
+          const double tt = copysign(1.0, tau) / (fabs(tau) + hypot(1.0, tau));
+          c = 1.0 / sqrt(1.0 + tt * tt);
+          s = tt * c;
+        }
+      } else if (apq != 0.0) {
+        const int ip = jac_tri(p, p), id = jac_tri(q, q);
+        const double app = A[ip], aqq = A[id];
+        double tt;
+        jac_rotation(app, aqq, apq, c, s, tt);
+        A[ip] = __builtin_fma(-tt, apq, app);
+        A[id] = __builtin_fma(tt, apq, aqq);
+        A[iq] = 0.0;
+      }
+      cs[u * half + j] = d2{c, s};
+    }
+  };
+  // the blocks of pairs j1 < j2: rows j1 = i and half - 1 - i of the triangle of pairs side by side
+  const int width = half - 1, lines = half / 2;   // half - 1 blocks in each of half / 2 lines (+ half a line)
+  auto blocks = [&](int r, int u) {
+    if constexpr (!TRI) {   // every block, the ones on the diagonal too
+      for (int e = t; e < half * half; e += NT) {
+        const int j1 = int(fast_div(e, by_half)), j2 = e - j1 * half;
+        int p1, q1, p2, q2;
+        players(r, j1, p1, q1);
+        players(r, j2, p2, q2);
+        const d2 g1 = cs[u * half + j1], g2 = cs[u * half + j2];
+        double *x = A + p1 * np, *y = A + q1 * np;
+        double a00 = x[p2], a01 = x[q2], a10 = y[p2], a11 = y[q2];
+        rotate(g1, a00, a10);
+        rotate(g1, a01, a11);
+        rotate(g2, a00, a01);
+        rotate(g2, a10, a11);
+        x[p2] = a00;
+        x[q2] = a01;
+        y[p2] = a10;
+        y[q2] = a11;
+      }
+      return;
+    }
+    for (int l = t >> 6; l < lines + (half & 1); l += NT / 64)
+      for (int e = t & 63; e < width; e += 64) {
+        const int first = half - 1 - l;           // blocks of row l: j2 = l + 1 ..
+        int j1 = l, j2 = l + 1 + e;
+        if (e >= first) {
+          if (l == lines) continue;               // the middle row of an odd triangle stands alone
+          j1 = half - 1 - l;
+          j2 = j1 + 1 + e - first;
+        }
+        int p1, q1, p2, q2;
+        players(r, j1, p1, q1);
+        players(r, j2, p2, q2);
+        const d2 g1 = cs[u * half + j1], g2 = cs[u * half + j2];
+        double *e00 = A + (p1 > p2 ? jac_tri(p1, p2) : jac_tri(p2, p1));
+        double *e01 = A + (p1 > q2 ? jac_tri(p1, q2) : jac_tri(q2, p1));
+        double *e10 = A + (q1 > p2 ? jac_tri(q1, p2) : jac_tri(p2, q1));
+        double *e11 = A + (q1 > q2 ? jac_tri(q1, q2) : jac_tri(q2, q1));
+        double a00 = *e00, a01 = *e01, a10 = *e10, a11 = *e11;
+        rotate(g1, a00, a10);
+        rotate(g1, a01, a11);
+        rotate(g2, a00, a01);
+        rotate(g2, a10, a11);
+        *e00 = a00;
+        *e01 = a01;
+        *e10 = a10;
+        *e11 = a11;
+      }
+  };
+  // this workgroup's rows of V, by the threads from t0 on
+  auto vectors = [&](int r, int u, int t0) {
+    for (int e = t - t0; e < half * rl; e += NT - t0) {
+      const int j = int(fast_div(e, by_rl)), i = e - j * rl;
+      int p, q;
+      players(r, j, p, q);
+      rotate(cs[u * half + j], V[p * rl + i], V[q * rl + i]);
+    }
+  };
+  const int t0 = half <= 64 ? 64 : 128;   // threads below it compute rotations
+
   // converged once the off-diagonal norm is below 1e-14 of the matrix norm;
   // one more sweep then brings it to the rounding level
   int used = -1;
@@ -66,94 +255,82 @@ jacobi_kernel(double *Aall, double *wall, double *Vall, int *sweeps_out, int n) 
       used = sweep;
       break;
     }
-    double off = 0.0;
-    for (int i = t; i < n2; i += EIGH_THREADS)
-      if (i / n != i % n) off += A[i] * A[i];
-    const double offs = wg_sum(off, sh);
+    const double offs = offdiag(red[1 + (sweep & 1)]);
     if (offs == 0.0 || norm2 == 0.0) {
       used = sweep;
       break;
     }
     if (offs <= 1e-28 * norm2) last = true;
     if (sweep == MAX_SWEEPS) break;
-    for (int r = 0; r < np - 1; ++r) {
-      // circle pairing: player np-1 fixed, the others rotate
-      for (int j = t; j < half; j += EIGH_THREADS) {
-        int p, q;
-        if (j == 0) {
-          p = r;
-          q = np - 1;
-        } else {
-          p = (r + j) % (np - 1);
-          q = (r - j + (np - 1)) % (np - 1);
-        }
-        if (p > q) {
-          const int tmp = p;
-          p = q;
-          q = tmp;
-        }
-        double c = 1.0, s = 0.0;
-        if (q < n) {
-          const double apq = A[p * n + q];
-          if (apq != 0.0) {
-            const double tau = (A[q * n + q] - A[p * n + p]) / (2.0 * apq);
-            const double tt = copysign(1.0, tau) / (fabs(tau) + hypot(1.0, tau));
-            c = 1.0 / sqrt(1.0 + tt * tt);
-            s = tt * c;
-          }
-        }
-        pp[j] = p;
-        pq[j] = q < n ? q : p;
-        pc[j] = c;
-        ps[j] = s;
-      }
+    pivots(0, 0);
+    __syncthreads();
+    for (int r = 0; r < cyc; ++r) {
+      const int u = r & 1;
+      blocks(r, u);
       __syncthreads();
-      // rows: A[p,:], A[q,:] <- c A[p,:] - s A[q,:], s A[p,:] + c A[q,:]
-      for (int e = t; e < half * n; e += EIGH_THREADS) {
-        const int j = e / n, col = e % n;
-        const int p = pp[j], q = pq[j];
-        if (p == q) continue;
-        const double c = pc[j], s = ps[j];
-        const double ap = A[p * n + col], aq = A[q * n + col];
-        A[p * n + col] = c * ap - s * aq;
-        A[q * n + col] = s * ap + c * aq;
-      }
-      __syncthreads();
-      // columns of A and V
-      for (int e = t; e < half * n; e += EIGH_THREADS) {
-        const int j = e / n, row = e % n;
-        const int p = pp[j], q = pq[j];
-        if (p == q) continue;
-        const double c = pc[j], s = ps[j];
-        const double ap = A[row * n + p], aq = A[row * n + q];
-        A[row * n + p] = c * ap - s * aq;
-        A[row * n + q] = s * ap + c * aq;
-        const double vp = V[row * n + p], vq = V[row * n + q];
-        V[row * n + p] = c * vp - s * vq;
-        V[row * n + q] = s * vp + c * vq;
-      }
+      if (t >= t0)
+        vectors(r, u, t0);
+      else if (r + 1 < cyc)
+        pivots(r + 1, u ^ 1);
       __syncthreads();
     }
   }
-  if (t == 0) sweeps_out[b] = used;
+  if (blockIdx.x == 0 && t == 0) sweeps_out[b] = used;
 
   // sort descending (ties by index): rank of each eigenvalue
-  for (int i = t; i < n; i += EIGH_THREADS) wdiag[i] = A[i * n + i];
+  double *wdiag = lds;
+  int *rank = reinterpret_cast<int *>(lds + np);
   __syncthreads();
-  for (int i = t; i < n; i += EIGH_THREADS) {
+  for (int i = t; i < n; i += NT) wdiag[i] = A[at(i, i)];
+  __syncthreads();
+  for (int i = t; i < n; i += NT) {
     const double v = wdiag[i];
     int rk = 0;
     for (int j = 0; j < n; ++j) rk += (wdiag[j] > v) || (wdiag[j] == v && j < i);
     rank[i] = rk;
+    if (blockIdx.x == 0) w[rk] = v;
   }
   __syncthreads();
-  for (int i = t; i < n; i += EIGH_THREADS) w[rank[i]] = wdiag[i];
-  // move V to A (scratch), then scatter columns into sorted order
-  for (int i = t; i < n2; i += EIGH_THREADS) A[i] = V[i];
-  __syncthreads();
-  for (int i = t; i < n2; i += EIGH_THREADS) {
-    const int row = i / n, col = i % n;
-    V[row * n + rank[col]] = A[i];
+  for (int i = t; i < rows * n; i += NT) {
+    const int x = int(fast_div(i, by_n)), col = i - x * n;
+    Vg[(row0 + x) * n + rank[col]] = V[col * rl + x];
+  }
+}
+
+template <int NT, bool TRI>
+void launch_jacobi_as(const double *A, double *w, double *V, int *sweeps, int n, int batch, hipStream_t st) {
+  static const bool attr = [] {   // dynamic LDS above 64 KB must be allowed per kernel
+    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&jacobi_kernel<NT, TRI>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, JAC_LDS - 512));
+    return true;
+  }();
+  (void)attr;
+  // rows of V per workgroup: what LDS leaves, and as few as eight while the
+  // matrices of the batch leave CUs idle
+  const int np = (n + 1) & ~1;
+  const int fit = int((JAC_LDS - jac_fixed(np, TRI)) / (size_t(np) * 8));
+  const int groups = std::max(1, 256 / batch);
+  const int rl = std::max(1, std::min(std::min(fit, n), std::max(8, (n + groups - 1) / groups)));
+  const size_t lds = jac_fixed(np, TRI) - 512 + size_t(np) * rl * 8;
+  hipLaunchKernelGGL((jacobi_kernel<NT, TRI>), dim3(uint32_t((n + rl - 1) / rl), uint32_t(batch)), dim3(NT), lds, st, A,
+                     w, V, sweeps, n, rl, make_fastdiv(uint32_t(n)), make_fastdiv(uint32_t(rl)),
+                     make_fastdiv(uint32_t(np / 2)));
+}
+
+// Two waves up to order 20, where a round has no more than 100 blocks.  The
+// triangle from order 56 on unless the caller asks for the square: half the
+// LDS traffic against more address arithmetic (six matrices: order 16 0.14 ms
+// square, 0.24 triangle; 49 0.51, 0.65; 64 1.74, 1.18; 100 4.0, 2.6).
+constexpr int JAC_TRI_N = 56;
+
+void launch_jacobi(const double *A, double *w, double *V, int *sweeps, int n, int batch, bool square, hipStream_t st) {
+  if (n < JAC_TRI_N || (square && n <= JACOBI_SQUARE_N)) {
+    if (n <= 20)
+      launch_jacobi_as<128, false>(A, w, V, sweeps, n, batch, st);
+    else
+      launch_jacobi_as<512, false>(A, w, V, sweeps, n, batch, st);
+  } else {
+    launch_jacobi_as<512, true>(A, w, V, sweeps, n, batch, st);
   }
 }
 
@@ -545,25 +722,6 @@ constexpr int TD_MS = 16;            // multisection points per eigenvalue
 // doubles of scratch per n beside two n x n matrices; td_scratch uses 78 of them
 constexpr int TOP_SCRATCH = 96;
 
-__device__ inline double top_wave_sum(double v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-__device__ inline double top_wave_max(double v) {
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off, 64));
-  return v;
-}
-// over the NW waves of a workgroup, in a fixed order; sh: NW doubles, free again after the next barrier
-template <int NW, bool MAX>
-__device__ inline double td_reduce(double v, double *sh) {
-  v = MAX ? top_wave_max(v) : top_wave_sum(v);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = sh[0];
-  for (int i = 1; i < NW; ++i) r = MAX ? fmax(r, sh[i]) : r + sh[i];
-  return r;
-}
-
 // fixed start vector of inverse iteration: entries in [-1, 1) from a hash of
 // the vector's rank and the entry's index
 __device__ inline double top_start(int r, int i) {
@@ -617,7 +775,7 @@ __device__ inline double td_reflector(double *vv, int m, double &tau, double *sh
   const int t = threadIdx.x;
   double amax = 0.0;
   for (int i = t; i < m; i += NT) amax = fmax(amax, fabs(vv[i]));
-  amax = td_reduce<NT / 64, true>(amax, sh0);
+  amax = wg_reduce<NT / 64, true>(amax, sh0);
   int ex = 0;
   if (amax > 0.0) (void)frexp(amax, &ex);
   double s2 = 0.0;
@@ -626,7 +784,7 @@ __device__ inline double td_reflector(double *vv, int m, double &tau, double *sh
     s2 += x * x;
   }
   const double raw0 = vv[0];
-  const double nrm2 = td_reduce<NT / 64, false>(s2, sh1);   // its barrier: raw0 is read everywhere
+  const double nrm2 = wg_reduce<NT / 64, false>(s2, sh1);   // its barrier: raw0 is read everywhere
   const double x0 = ldexp(raw0, -ex);
   const double alpha = x0 >= 0.0 ? -sqrt(nrm2) : sqrt(nrm2);
   const double vtv = nrm2 - 2.0 * alpha * x0 + alpha * alpha;  // |x - alpha e1|^2
@@ -662,7 +820,7 @@ td_column_kernel(double *Aall, double *workall, int n, int k) {
       wo[i] = tau_o * p[i];
       pv += wo[i] * vo[i];
     }
-    const double K = 0.5 * tau_o * td_reduce<TD_WAVES, false>(pv, sh[0]);
+    const double K = 0.5 * tau_o * wg_reduce<TD_WAVES, false>(pv, sh[0]);
     for (int i = t; i <= m; i += TD_THREADS) wo[i] -= K * vo[i];
   } else {
     for (int i = t; i <= m; i += TD_THREADS) vo[i] = wo[i] = 0.0;
@@ -703,8 +861,8 @@ td_column_kernel(double *Aall, double *workall, int n, int k) {
       s0 += x0 * nj;
       s1 += x1 * nj;
     }
-    s0 = top_wave_sum(s0);
-    s1 = top_wave_sum(s1);
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
     if (lane == 0) {
       pk[i0] = s0;
       if (two) pk[i0 + 1] = s1;
@@ -734,7 +892,7 @@ td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
       wo[t] = k0 > 0 ? tau * p[t] : 0.0;
       pv = wo[t] * vo[t];
     }
-    const double K = 0.5 * tau * td_reduce<TD_FIN / 64, false>(pv, sh[0]);
+    const double K = 0.5 * tau * wg_reduce<TD_FIN / 64, false>(pv, sh[0]);
     if (t < q) wo[t] -= K * vo[t];
     __syncthreads();
     for (int idx = t; idx < q * q; idx += TD_FIN) {
@@ -764,7 +922,7 @@ td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
       wo[t] = tau * x;
       pv = wo[t] * vo[t];
     }
-    const double K = 0.5 * tau * td_reduce<TD_FIN / 64, false>(pv, sh[2]);
+    const double K = 0.5 * tau * wg_reduce<TD_FIN / 64, false>(pv, sh[2]);
     if (t < m) wo[t] -= K * vo[t];
     __syncthreads();
     if (c < m) {
@@ -1019,7 +1177,7 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
       double *z = Zv + size_t(r) * n;
       double amax = 0.0;
       for (int i = lane; i < n; i += 64) amax = fmax(amax, fabs(z[i]));
-      amax = top_wave_max(amax);
+      amax = wave_max(amax);
       int ex = 0;
       if (amax > 0.0) (void)frexp(amax, &ex);
       double nrm = 0.0;
@@ -1027,13 +1185,13 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
         const double x = ldexp(z[i], -ex);
         nrm += x * x;
       }
-      nrm = top_wave_sum(nrm);
+      nrm = wave_sum(nrm);
       const double inv = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
       for (int r2 = r + 1 + wave; r2 < kk; r2 += TD_FIN / 64) {
         double *y = Zv + size_t(r2) * n;
         double dot = 0.0;
         for (int i = lane; i < n; i += 64) dot += ldexp(z[i], -ex) * inv * y[i];
-        dot = top_wave_sum(dot);
+        dot = wave_sum(dot);
         if (dot != 0.0)
           for (int i = lane; i < n; i += 64) y[i] -= dot * (ldexp(z[i], -ex) * inv);
       }
@@ -1074,7 +1232,7 @@ td_back_kernel(double *workall, int n) {
     double dot = 0.0;
 #pragma unroll
     for (int q = 0; q < R; ++q) dot += u[q] * z[q];
-    dot = top_wave_sum(dot);
+    dot = wave_sum(dot);
 #pragma unroll
     for (int q = 0; q < R; ++q) z[q] -= u[q] * dot;
   }
@@ -1241,7 +1399,7 @@ select_kernel(const double *w2, const double *V2, const int *sweeps2, int n, int
 void eigh_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, hipStream_t st) {
   TRG_REQUIRE(n >= 1 && n <= MAX_N && batch >= 1, "eigh: order must be in [1, 1024]");
   if (n <= JACOBI_MAX_N)
-    hipLaunchKernelGGL(jacobi_kernel, dim3(batch), dim3(EIGH_THREADS), 0, st, A, w, V, sweeps, n);
+    launch_jacobi(A, w, V, sweeps, n, batch, false, st);
   else
     hipLaunchKernelGGL(tridiag_ql_kernel, dim3(batch), dim3(TQ_THREADS), 0, st, A, w, V, sweeps, n);
   TRG_HIP_CHECK(hipGetLastError());
@@ -1252,10 +1410,10 @@ size_t eigh_top_work_doubles(int n, int batch) {
 }
 
 void eigh_top_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, int k, double cluster_rel,
-                      double *work, hipStream_t st) {
+                      double *work, hipStream_t st, bool square) {
   TRG_REQUIRE(n >= 1 && n <= MAX_N && batch >= 1 && k >= 1, "eigh_top: bad sizes");
   if (n <= JACOBI_MAX_N) {
-    hipLaunchKernelGGL(jacobi_kernel, dim3(batch), dim3(EIGH_THREADS), 0, st, A, w, V, sweeps, n);
+    launch_jacobi(A, w, V, sweeps, n, batch, square, st);
   } else {
     TRG_REQUIRE(work != nullptr, "eigh_top: workspace missing");
     launch_tridiag_top(A, w, V, sweeps, n, batch, k, cluster_rel, work, st);

@@ -455,7 +455,7 @@ void isometries_batch(std::vector<trg_ctx *> &cs, std::vector<StepPrep> &ps, int
     const int kk = *std::max_element(kmax.begin(), kmax.end());
     double *work = n > JACOBI_MAX_N ? c0.wsp<double>("gram_top", eigh_top_work_doubles(n, int(per_ax) * nax) * 8)
                                     : nullptr;
-    eigh_top_batched(G, W, V, sw, n, int(per_ax) * nax, kk, rel, work, c0.st);
+    eigh_top_batched(G, W, V, sw, n, int(per_ax) * nax, kk, rel, work, c0.st, true);
   } else {
     for (int a = 0; a < nax; ++a) {
       const int n = c0.dims[others[a]] * c0.dims[others[a]];
@@ -463,7 +463,7 @@ void isometries_batch(std::vector<trg_ctx *> &cs, std::vector<StepPrep> &ps, int
                                                        eigh_top_work_doubles(n, int(per_ax)) * 8)
                                       : nullptr;
       eigh_top_batched(G + gbase(a), W + wbase(a), V + gbase(a), sw + size_t(a) * per_ax, n, int(per_ax),
-                       kmax[size_t(a)], rel, work, c0.st);
+                       kmax[size_t(a)], rel, work, c0.st, true);
     }
   }
   for (int a = 0; a < nax; ++a) {

@@ -118,16 +118,19 @@ void ising_init(double *T, double *SE, double *SM, int d, double beta, double h,
 // Householder tridiagonalisation + QL, which keeps a block-diagonal A block
 // diagonal only when each block's indices are contiguous.
 constexpr int JACOBI_MAX_N = 160;
+constexpr int JACOBI_SQUARE_N = 140;
 void eigh_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, hipStream_t st);
 // Every eigenvalue (descending) but eigenvectors only for the leading kk
 // indices: k, extended while the next eigenvalue continues a cluster (gap
 // <= cluster_rel * lambda_max); the other columns of V are zero.  Above the
 // Jacobi range: Householder, bisection and inverse iteration (sweeps receives
 // kk); up to it, the full Jacobi solver.  work: eigh_top_work_doubles(n,
-// batch) doubles of device memory.
+// batch) doubles of device memory.  square: the Jacobi form that keeps all of A
+// (orders up to JACOBI_SQUARE_N), for callers whose later steps hang on the
+// last bits of the eigensystem.
 size_t eigh_top_work_doubles(int n, int batch);
 void eigh_top_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, int k, double cluster_rel,
-                      double *work, hipStream_t st);
+                      double *work, hipStream_t st, bool square = false);
 
 // isometry selection of one transverse axis from both sides' eigensystems
 struct SelectOut {

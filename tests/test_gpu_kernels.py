@@ -247,6 +247,37 @@ def test_jacobi_eigh(n):
         assert np.allclose(V[b] @ np.diag(w[b]) @ V[b].T, A[b], atol=1e-13 * nrm)
 
 
+@pytest.mark.parametrize("n,batch", [(20, 300), (21, 2), (55, 3), (56, 3), (57, 260), (65, 40), (128, 2), (129, 2),
+                                     (141, 1), (159, 2), (160, 1)])
+def test_jacobi_edges(n, batch):
+    """Where the Jacobi solver changes form: two waves or all, the square or the
+    triangle of the matrix, odd orders (a dummy player), one or two waves of
+    rotations, and from one to many workgroups sharing the vectors' rows (few
+    matrices; more than the chip has CUs)."""
+    torch = need_gpu()
+    from paper_1911_12954_amd import trg_eigh
+    announce("jacobi edges", n, batch)
+    A = np.stack([gram_like(n, n, 70 + i) if i % 2 else random_symmetric(n, 80 + i) for i in range(min(batch, 4))])
+    A = A[np.arange(batch) % A.shape[0]]
+    dA = torch.from_numpy(A).cuda()
+    dw = torch.empty((batch, n), dtype=torch.float64, device="cuda")
+    dV = torch.empty((batch, n, n), dtype=torch.float64, device="cuda")
+    ds = torch.empty(batch, dtype=torch.int32, device="cuda")
+    trg_eigh(dA.data_ptr(), dw.data_ptr(), dV.data_ptr(), ds.data_ptr(), n, batch,
+             torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    w, V = dw.cpu().numpy(), dV.cpu().numpy()
+    assert int(ds.min()) >= 0
+    for b in range(batch):
+        if b >= 4:   # equal matrices of a batch give equal bits
+            assert np.array_equal(w[b], w[b % 4]) and np.array_equal(V[b], V[b % 4])
+            continue
+        nrm = np.linalg.norm(A[b])
+        assert np.max(np.abs(w[b] - np.linalg.eigvalsh(A[b])[::-1])) < 1e-13 * nrm
+        assert np.allclose(V[b].T @ V[b], np.eye(n), atol=1e-13)
+        assert np.allclose(V[b] @ np.diag(w[b]) @ V[b].T, A[b], atol=1e-13 * nrm)
+
+
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "bf16x3"])
 def test_gemm_empty_products(precision):
     """K = 0: C is zeroed (or left as it was when accumulating); M = 0 or
