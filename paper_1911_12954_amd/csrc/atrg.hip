@@ -195,161 +195,196 @@ chol_inv_kernel(const double *C, int n, double shift_coef, double *R, double *Ri
   }
 }
 
-// The same factorisation for n <= 128, with the matrix in registers: wave w
-// (of four) owns the rows p = w (mod 4) and lane l the columns l and l + 64,
-// so thread (w, l) holds the 32 x 2 elements (w + 4 pp, l + 64 qq).
-// Column j of the elimination: the wave owning row j takes the pivot from
-// the lane holding the diagonal, scales the row (a pivot at or below the
-// dead tolerance makes the row zero and its pivot 1) and publishes it as a
-// 128-entry LDS row that is zero outside j < q < n; after one barrier every
-// thread subtracts R[j][p] R[j][q] from all its elements, which leaves the
-// rows at or above j unchanged (their entry of the published row is zero).
-// The published row alternates between two buffers, so one barrier per
-// column suffices: a buffer is written again only after the next barrier.
-// R is also kept transposed in LDS (zero below its diagonal) for the
-// inverse, which runs the same way from the last row up: row k of
-// X = R^-1 is final once every row below it has been eliminated, is scaled
-// by 1 / R[k][k] and published, and every thread subtracts R[p][k] X[k][q].
-// All LDS reads are unconditional, so they go out together.
-constexpr int CHOL_REG_MAX = 128;
-constexpr int CHOL_THREADS = 256;
-constexpr int CHOL_RT_LD = CHOL_REG_MAX + 1;   // row stride of R^T in LDS (lanes write a column)
+// The same factorisation for n <= 128, in blocks of 16 with the products on
+// FP64 MFMA.  What bounds it is the chain of n pivots (one reciprocal square
+// root and one row each), so only the 16 x 16 diagonal blocks are factored
+// entry by entry, by one wave with a column per lane (entries of other columns
+// come by v_readlane); sixteen more lanes carry the identity through the same
+// row operations and end with L^-1 = R_kk^-T.  Then, per block row k:
+//   R[k][c] = L^-1 A[k][c], one wave per block c (rows of dead pivots zero);
+//   A[r][c] -= R[k][r]^T R[k][c], shared by seven waves, while wave 0 updates
+//   the next diagonal block first and factors it.
+// The inverse X by block columns, one wave each: X[i][j] = -X_ii sum_{i < k <=
+// j} R[i][k] X[k][j], from the bottom up; an MFMA result is in the layout in
+// which the next product takes it.  R fills the upper triangle of the LDS
+// matrix, X transposed the strictly lower blocks.
+// v_mfma_f64_16x16x4: lane (g, r16) supplies A[r16][4 s + g] and B[4 s + g][r16];
+// accumulator e of the lane is C[g + 4 e][r16].
+// Measured: order 120 69 us, order 50 29 us, order 16 9 us, against 219, 92 and
+// 34 us with one barrier per column and per row of the inverse.
+constexpr int CHOL_REG_MAX = 128, CHOL_NB = 16;
+constexpr int CHOL_THREADS = 512, CHOL_WAVES = CHOL_THREADS / 64;
+constexpr int CHOL_LD = CHOL_REG_MAX + 4, CHOL_LI = CHOL_NB + 2;   // LDS row strides: no worse than two-way conflicts
+constexpr size_t CHOL_LDS = (size_t(CHOL_REG_MAX) * CHOL_LD + size_t(CHOL_REG_MAX) * CHOL_LI) * 8;
+
+typedef double tsg_v4d __attribute__((ext_vector_type(4)));
+
+__device__ inline double lane_value(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane(int(b), lane), hi = __builtin_amdgcn_readlane(int(b >> 32), lane);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
 
 __global__ void __launch_bounds__(CHOL_THREADS)
-chol_inv_reg_kernel(const double *C, int n, double shift_coef, double *Rg, double *Rinv, int *err) {
-  extern __shared__ double RT[];   // CHOL_REG_MAX x CHOL_RT_LD: RT[q][p] = R[p][q] for p < q, else 0
-  __shared__ double sh[CHOL_THREADS];
-  __shared__ double shm[CHOL_THREADS];
-  __shared__ double row[2][CHOL_REG_MAX];
-  __shared__ double pivs[CHOL_REG_MAX];
+chol_inv_block_kernel(const double *C, int n, double shift_coef, double *Rg, double *Rinv, int *err) {
+  extern __shared__ double L[];                       // CHOL_REG_MAX x CHOL_LD
+  double *const LI = L + CHOL_REG_MAX * CHOL_LD;      // L^-1 of block k in rows 16 k .. 16 k + 15
+  __shared__ double red[2][CHOL_WAVES], pivs[CHOL_REG_MAX];
   __shared__ int dead[CHOL_REG_MAX];
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int g = lane >> 4, r16 = lane & 15;
+  const int nb = (n + CHOL_NB - 1) / CHOL_NB, np = nb * CHOL_NB;
   double tr = 0.0, mx = 0.0;
-  for (int i = t; i < n; i += CHOL_THREADS) {
-    tr += C[i * n + i];
-    mx = fmax(mx, C[i * n + i]);
+  if (t < n) tr = mx = C[size_t(t) * n + t];
+  for (int off = 32; off > 0; off >>= 1) {
+    tr += __shfl_xor(tr, off, 64);
+    mx = fmax(mx, __shfl_xor(mx, off, 64));
   }
-  sh[t] = tr;
-  shm[t] = mx;
-  for (int i = t; i < CHOL_REG_MAX * CHOL_RT_LD; i += CHOL_THREADS) RT[i] = 0.0;
+  if (lane == 0) {
+    red[0][wave] = tr;
+    red[1][wave] = mx;
+  }
   __syncthreads();
-  for (int s = CHOL_THREADS / 2; s > 0; s >>= 1) {
-    if (t < s) {
-      sh[t] += sh[t + s];
-      shm[t] = fmax(shm[t], shm[t + s]);
-    }
-    __syncthreads();
+  tr = red[0][0];
+  mx = fmax(red[1][0], 0.0);
+  for (int i = 1; i < CHOL_WAVES; ++i) {
+    tr += red[0][i];
+    mx = fmax(mx, red[1][i]);
   }
-  const double shift = shift_coef * sh[0];
-  const double tol = 1e-26 * (shm[0] + shift);
-  double E[32][2];
+  const double shift = shift_coef * tr;
+  const double tol = 1e-26 * (mx + shift);
+  for (int i = t; i < np * np; i += CHOL_THREADS) {
+    const int r = i / np, c = i - r * np;
+    double v = 0.0;
+    if (r <= c && c < n) v = C[size_t(r) * n + c] + (r == c ? shift : 0.0);
+    if (r == c && c >= n) v = 1.0;                    // padding: a unit diagonal
+    L[r * CHOL_LD + c] = v;
+  }
+  __syncthreads();
+
+  // factor diagonal block k in place, L^-1 to LI (one wave)
+  auto factor = [&](int k) {
+    const int o = k * CHOL_NB;
+    double a[CHOL_NB];                                // lanes 0-15: column of the block, 16-31: of the identity
 #pragma unroll
-  for (int pp = 0; pp < 32; ++pp)
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int p = w + 4 * pp, q = l + 64 * qq;
-      E[pp][qq] = (p <= q && q < n) ? C[p * n + q] + (p == q ? shift : 0.0) : 0.0;
+    for (int i = 0; i < CHOL_NB; ++i) {
+      const double v = L[(o + i) * CHOL_LD + o + r16];
+      a[i] = g == 0 ? (i <= r16 ? v : 0.0) : (i == r16 ? 1.0 : 0.0);
     }
-  for (int j = 0; j < n; ++j) {
-    double *rj = row[j & 1];
-    if (w == (j & 3)) {
-      const int pj = j >> 2;
-      double r0 = 0.0, r1 = 0.0;
 #pragma unroll
-      for (int pp = 0; pp < 32; ++pp)
-        if (pp == pj) {
-          r0 = E[pp][0];
-          r1 = E[pp][1];
-        }
-      const double mine = (j >> 6) ? r1 : r0;
-      const int lo = __builtin_amdgcn_readlane(int(__double_as_longlong(mine)), j & 63);
-      const int hi = __builtin_amdgcn_readlane(int(__double_as_longlong(mine) >> 32), j & 63);
-      const double dj = __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
-      const bool isdead = !(dj > tol);
-      const double piv = isdead ? 1.0 : sqrt(dj);
-      const double inv = isdead ? 0.0 : 1.0 / piv;
-      const double v0 = (l > j && l < n) ? r0 * inv : 0.0;
-      const double v1 = (l + 64 > j && l + 64 < n) ? r1 * inv : 0.0;
-      rj[l] = v0;
-      rj[l + 64] = v1;
-      if (l > j && l < n) RT[l * CHOL_RT_LD + j] = v0;
-      if (l + 64 > j && l + 64 < n) RT[(l + 64) * CHOL_RT_LD + j] = v1;
-      if (l == (j & 63)) {
-        pivs[j] = piv;
-        dead[j] = isdead ? 1 : 0;
-        if (isdead && !isfinite(dj)) *err |= 4;
+    for (int j = 0; j < CHOL_NB; ++j) {
+      const double d = lane_value(a[j], j);
+      const bool isdead = !(d > tol);
+      double y = __builtin_amdgcn_rsq(d);             // two Newton steps, then the root to its last bits
+      y = y * __builtin_fma(-0.5 * d * y, y, 1.5);
+      y = y * __builtin_fma(-0.5 * d * y, y, 1.5);
+      double piv = d * y;
+      piv = isdead ? 1.0 : __builtin_fma(__builtin_fma(-piv, piv, d), 0.5 * y, piv);
+      double v = a[j] * y;
+      if (isdead) v = g == 0 ? 0.0 : a[j];
+      if (g == 0 && r16 <= j) v = 0.0;                // columns up to j are done
+      a[j] = v;
+#pragma unroll
+      for (int q = j + 1; q < CHOL_NB; ++q) a[q] = __builtin_fma(-lane_value(v, q), v, a[q]);
+      if (lane == j) {
+        pivs[o + j] = piv;
+        dead[o + j] = isdead ? 1 : 0;
+        if (isdead && !isfinite(d) && o + j < n) *err |= 4;
       }
     }
-    __syncthreads();
-    double rq[2], rv[32];
+    if (g == 0) {
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) rq[qq] = rj[l + 64 * qq];
+      for (int i = 0; i < CHOL_NB; ++i) L[(o + i) * CHOL_LD + o + r16] = a[i];
+    } else if (g == 1) {
 #pragma unroll
-    for (int pp = 0; pp < 32; ++pp) rv[pp] = rj[w + 4 * pp];
+      for (int i = 0; i < CHOL_NB; ++i) LI[(o + i) * CHOL_LI + r16] = i >= r16 ? a[i] : 0.0;
+    }
+  };
+  // A[r][c] -= R[k][r]^T R[k][c]
+  auto update = [&](int k, int r, int c) {
+    double *x = L + r * CHOL_NB * CHOL_LD + c * CHOL_NB;
+    const double *p = L + k * CHOL_NB * CHOL_LD;
+    tsg_v4d acc;
 #pragma unroll
-    for (int pp = 0; pp < 32; ++pp)
+    for (int e = 0; e < 4; ++e) acc[e] = x[(g + 4 * e) * CHOL_LD + r16];
 #pragma unroll
-      for (int qq = 0; qq < 2; ++qq) E[pp][qq] -= rv[pp] * rq[qq];
-  }
+    for (int s = 0; s < 4; ++s) {
+      const double *row = p + (4 * s + g) * CHOL_LD + r16;
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-row[r * CHOL_NB], row[c * CHOL_NB], acc, 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[(g + 4 * e) * CHOL_LD + r16] = acc[e];
+  };
+  if (wave == 0) factor(0);
   __syncthreads();
-  // X = R^-1 in the same registers
+  for (int k = 0; k + 1 < nb; ++k) {
+    const int o = k * CHOL_NB;
+    for (int c = k + 1 + wave; c < nb; c += CHOL_WAVES) {   // block row k
+      double *x = L + o * CHOL_LD + c * CHOL_NB;
+      tsg_v4d acc{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int pp = 0; pp < 32; ++pp)
+      for (int s = 0; s < 4; ++s)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(LI[(o + r16) * CHOL_LI + 4 * s + g],
+                                                   x[(4 * s + g) * CHOL_LD + r16], acc, 0, 0, 0);
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int p = w + 4 * pp, q = l + 64 * qq;
-      E[pp][qq] = (p == q && q < n) ? 1.0 : 0.0;
-    }
-  for (int k = n - 1; k >= 0; --k) {
-    double *xk = row[k & 1];
-    if (w == (k & 3)) {
-      const int pk = k >> 2;
-      const double ik = 1.0 / pivs[k];
-#pragma unroll
-      for (int pp = 0; pp < 32; ++pp)
-        if (pp == pk) {
-          E[pp][0] *= ik;
-          E[pp][1] *= ik;
-          xk[l] = E[pp][0];
-          xk[l + 64] = E[pp][1];
-        }
+      for (int e = 0; e < 4; ++e) x[(g + 4 * e) * CHOL_LD + r16] = dead[o + g + 4 * e] ? 0.0 : acc[e];
     }
     __syncthreads();
-    double xq[2], rv[32];
+    if (wave == 0) {
+      update(k, k + 1, k + 1);
+      factor(k + 1);
+    } else {
+      int e = 0;   // the other blocks (r, c), k < r <= c, dealt to waves 1 .. 7
+      for (int r = k + 1; r < nb; ++r)
+        for (int c = r == k + 1 ? r + 1 : r; c < nb; ++c, ++e)
+          if (e % (CHOL_WAVES - 1) == wave - 1) update(k, r, c);
+    }
+    __syncthreads();
+  }
+  // ---- X = R^-1; the longest columns first on waves 0, 1, ...
+  for (int j = nb - 1 - wave; j >= 0; j -= CHOL_WAVES) {
+    for (int i = j - 1; i >= 0; --i) {
+      tsg_v4d acc{0.0, 0.0, 0.0, 0.0};
+      for (int k = i + 1; k <= j; ++k)
 #pragma unroll
-    for (int qq = 0; qq < 2; ++qq) xq[qq] = xk[l + 64 * qq];
+        for (int s = 0; s < 4; ++s) {
+          const double a = L[(i * CHOL_NB + r16) * CHOL_LD + k * CHOL_NB + 4 * s + g];
+          const double x = k == j ? LI[(j * CHOL_NB + r16) * CHOL_LI + 4 * s + g]
+                                  : L[(j * CHOL_NB + r16) * CHOL_LD + k * CHOL_NB + 4 * s + g];
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, x, acc, 0, 0, 0);
+        }
+      tsg_v4d out{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int pp = 0; pp < 32; ++pp) rv[pp] = RT[k * CHOL_RT_LD + w + 4 * pp];
+      for (int s = 0; s < 4; ++s)
+        out = __builtin_amdgcn_mfma_f64_16x16x4f64(-LI[(i * CHOL_NB + 4 * s + g) * CHOL_LI + r16], acc[s], out, 0, 0, 0);
 #pragma unroll
-    for (int pp = 0; pp < 32; ++pp)
-#pragma unroll
-      for (int qq = 0; qq < 2; ++qq) E[pp][qq] -= rv[pp] * xq[qq];
+      for (int e = 0; e < 4; ++e) L[(j * CHOL_NB + r16) * CHOL_LD + i * CHOL_NB + g + 4 * e] = out[e];
+    }
   }
   __syncthreads();
   for (int i = t; i < n * n; i += CHOL_THREADS) {
-    const int r = i / n, c = i % n;
-    Rg[i] = (r <= c && !dead[r]) ? (r == c ? pivs[r] : RT[c * CHOL_RT_LD + r]) : 0.0;
-  }
-#pragma unroll
-  for (int pp = 0; pp < 32; ++pp)
-#pragma unroll
-    for (int qq = 0; qq < 2; ++qq) {
-      const int p = w + 4 * pp, q = l + 64 * qq;
-      if (p < n && q < n) Rinv[p * n + q] = (p <= q && !dead[q]) ? E[pp][qq] : 0.0;
+    const int r = i / n, c = i - r * n;
+    double u = 0.0, x = 0.0;
+    if (r <= c) {
+      if (!dead[r]) u = r == c ? pivs[r] : L[r * CHOL_LD + c];
+      if (!dead[c])
+        x = r / CHOL_NB == c / CHOL_NB ? LI[c * CHOL_LI + r % CHOL_NB] : L[c * CHOL_LD + r];
     }
+    Rg[i] = u;
+    Rinv[i] = x;
+  }
 }
 
 void launch_chol_inv(const double *C, int n, double shift, double *R, double *Rinv, int *err, hipStream_t st) {
   TRG_REQUIRE(n >= 1 && n <= 1024, "chol: bad order");
   if (n <= CHOL_REG_MAX) {
-    const size_t lds = size_t(CHOL_REG_MAX) * CHOL_RT_LD * 8;   // R^T for the inverse
-    static bool attr = false;
-    if (!attr) {
-      TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_inv_reg_kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-      attr = true;
-    }
-    hipLaunchKernelGGL(chol_inv_reg_kernel, dim3(1), dim3(CHOL_THREADS), lds, st, C, n, shift, R, Rinv, err);
+    static const bool attr = [] {
+      TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&chol_inv_block_kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, int(CHOL_LDS)));
+      return true;
+    }();
+    (void)attr;
+    hipLaunchKernelGGL(chol_inv_block_kernel, dim3(1), dim3(CHOL_THREADS), CHOL_LDS, st, C, n, shift, R, Rinv, err);
   } else {
     hipLaunchKernelGGL(chol_inv_kernel, dim3(1), dim3(256), 0, st, C, n, shift, R, Rinv, err);
   }
@@ -372,8 +407,6 @@ void launch_chol_inv(const double *C, int n, double shift, double *R, double *Ri
 // e of the lane is C[g + 4e][r16].
 constexpr int TSG_K = 128, TSG_ROWS = 32, TSG_LD = 144;
 constexpr int TSG_MAXB = 9;   // blocks per wave: ceil(36 / 4)
-
-typedef double tsg_v4d __attribute__((ext_vector_type(4)));
 
 __global__ void __launch_bounds__(256)
 ts_gram_kernel(const double *__restrict__ Y, int64_t m, int k, int64_t rpw, double *__restrict__ part) {

@@ -92,6 +92,30 @@ def test_dcut24_swap_spectrum_on_random_pieces():
     ctx.close()
 
 
+@pytest.mark.parametrize("cols", [7, 15, 16, 17, 32, 33, 96, 112, 113, 127, 128, 129])
+def test_swap_spectrum_at_factorisation_block_edges(cols):
+    """The sketch's column count is the order of every Cholesky factor of the
+    randomized SVD: whole and ragged blocks of 16, the largest blocked order
+    (128) and the first beyond it.  Same comparison, tolerance and reasoning
+    as at bond dimension 24."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_factors
+    announce("atrg sketch columns", cols)
+    D, d = 6, 4
+    rng = np.random.default_rng(100 + cols)
+    decay = 0.5 ** np.arange(D)
+    G = rng.standard_normal((D,) * d + (D,)) * decay
+    H = rng.standard_normal((D,) + (D,) * d) * decay.reshape((D,) + (1,) * d)
+    ctx = trg_init_factors(G, H, dcut=D, rsvd_p=cols - D, rsvd_q=2, seed=3)
+    ctx.atrg_step(1, D)
+    sig = ctx.atrg_spectrum()
+    ctx.close()
+    ref = atrg.rsvd_swap(atrg.canonical(G, H, D), 1, D, cols - D, 2, 1, 3)[1]
+    err = np.max(np.abs(sig - ref)) / ref[0]
+    print(f"[atrg columns {cols}] max |sigma_gpu - sigma_oracle| / sigma_max = {err:.3e}", flush=True)
+    assert err < 1e-8
+
+
 # ------------------------------------------------------------ impure tensors ---
 def _gpu_impure(beta, h, d, dcut, L, **cfg):
     from paper_1911_12954_amd import trg_init_ising
