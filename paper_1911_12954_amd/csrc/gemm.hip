@@ -131,22 +131,47 @@ __device__ inline int pipe_swz(int row) {
 // tile from LDS right before its MFMAs with one wave per SIMD (FP64) or two in
 // step (FP32).  Of the FP32 gain, 129 -> 138 comes from adding a finished
 // group to the FP64 sums block by block between the next tile's first MFMAs.
-template <int PREC, int BM, int BN, int WM, int WN, int MINW, bool ACCUM>
+//
+// RIGHT selects the right operand: RowsRight is the K-contiguous Bt above;
+// ColsRight (FP64 only) reads B as it lies in memory with its columns
+// contiguous, element (k, n) at (k / k1) sk2 + (k % k1) sk1 + (n / n1) sn2 + n % n1,
+// so that a tensor whose summed leg is an outer one needs no transposed copy.
+// A K tile of it is 16 rows of BN columns; its LDS rows are BN + 4 doubles, so
+// the two rows of a half wave's 8-byte reads fall on different banks.  Rows
+// past K repeat the last one (A is zero there), columns past N the last one
+// (not stored); C is M x N, unpadded.
+// Measured: 13824 x 2880 x 576 in 128 x 128 tiles 62 TFLOP/s, 576 x 2880 x
+// 13824 in six K ranges of 64 x 128 tiles 61, as fast as from packed
+// operands (63 and 61), whose copies took half as long again.
+struct RowsRight {
+  static constexpr bool cols = false, pairs = false;
+};
+template <bool PAIRS>   // columns 2 i and 2 i + 1 adjacent and 16-byte aligned
+struct ColsRight {
+  static constexpr bool cols = true, pairs = PAIRS;
+  uint32_t M, N, K, k1, n1;
+  uint64_t sk1, sk2, sn2;
+};
+
+template <int PREC, int BM, int BN, int WM, int WN, int MINW, bool ACCUM, class RIGHT = RowsRight>
 __global__ void __launch_bounds__(64 * WM * WN, MINW)
 gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename Prec<PREC>::in_t *__restrict__ Bt,
                  typename Prec<PREC>::out_t *__restrict__ C, uint32_t tiles_m, uint32_t tiles_n, uint32_t ktiles,
                  uint64_t lda, uint64_t ldb, uint64_t ldc, uint64_t c_split_stride, uint64_t batch_a,
-                 uint64_t batch_b, uint64_t batch_c) {
+                 uint64_t batch_b, uint64_t batch_c, RIGHT rt) {
   using P = Prec<PREC>;
   using acc_t = typename P::acc_t;
   using frag_t = typename P::frag_t;
+  constexpr bool COLS = RIGHT::cols;
+  static_assert(!COLS || PREC == 0, "column-contiguous right operands are FP64");
   constexpr int NT = 64 * WM * WN;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr int FM = TM / 16, FN = TN / 16;
   constexpr int RB = 128, CPR = 8, BK = RB / P::elem;
   constexpr int LA = BM * CPR / NT, LB = BN * CPR / NT;
   static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/threads mismatch");
-  constexpr int STAGE = (BM + BN) * RB;
+  constexpr int LDN = (BN + 4) * 8;   // bytes of an LDS row of a column-contiguous tile
+  constexpr int STAGE = BM * RB + (COLS ? BK * LDN : BN * RB);
   constexpr bool F64SUM = PREC == 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -166,13 +191,61 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
   const unsigned char *gB = reinterpret_cast<const unsigned char *>(Bt + (n0 + row0) * ldb + koff) + col0 * 16;
   const uint64_t stepA = uint64_t(NT / CPR) * lda * P::elem, stepB = uint64_t(NT / CPR) * ldb * P::elem;
 
+  // column-contiguous right operand: this thread's pair of columns and its
+  // LB rows of a K tile, as (k / k1, k % k1), which advance by 16 a tile
+  constexpr int CPT = COLS ? BN / 2 : 1, RSTEP = COLS ? NT / CPT : 1;
+  uint32_t ktn = ktiles, kq[COLS ? LB : 1], kr[COLS ? LB : 1];
+  uint32_t kleft = 0, kq16 = 0, kr16 = 0, brow = 0, bcol = 0;
+  const double *bc0 = nullptr, *bc1 = nullptr;
+  uint64_t klast = 0;
+  if constexpr (COLS) {
+    const uint32_t k0 = uint32_t(koff), total = (rt.K + BK - 1) / BK - blockIdx.y * ktiles;
+    ktn = ktiles < total ? ktiles : total;
+    brow = uint32_t(tid) / CPT;
+    if constexpr (CPT == 64) brow = __builtin_amdgcn_readfirstlane(brow);
+    bcol = uint32_t(tid) % CPT * 2;
+    // a whole pair stays inside: N is even where pairs are loaded
+    const uint32_t c0 = uint32_t(n0) + bcol < rt.N ? uint32_t(n0) + bcol : rt.N - (RIGHT::pairs ? 2 : 1);
+    const uint32_t c1 = c0 + 1 < rt.N ? c0 + 1 : rt.N - 1;
+    bc0 = Bt + (c0 / rt.n1) * rt.sn2 + c0 % rt.n1;
+    bc1 = Bt + (c1 / rt.n1) * rt.sn2 + c1 % rt.n1;
+    kq16 = BK / rt.k1;
+    kr16 = BK % rt.k1;
+    kleft = rt.K - k0;   // rows of this workgroup's first tile and after
+    klast = uint64_t((rt.K - 1) / rt.k1) * rt.sk2 + uint64_t((rt.K - 1) % rt.k1) * rt.sk1;
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const uint32_t k = k0 + brow + i * RSTEP;
+      kq[i] = k / rt.k1;
+      kr[i] = k % rt.k1;
+    }
+  }
   u32x4 ra[LA], rb[LB];
   auto gload = [&](uint32_t kt) {
     const uint64_t kb = uint64_t(kt) * RB;
 #pragma unroll
     for (int i = 0; i < LA; ++i) ra[i] = *reinterpret_cast<const u32x4 *>(gA + i * stepA + kb);
+    if constexpr (COLS) {
 #pragma unroll
-    for (int i = 0; i < LB; ++i) rb[i] = *reinterpret_cast<const u32x4 *>(gB + i * stepB + kb);
+      for (int i = 0; i < LB; ++i) {
+        uint64_t off = kq[i] * rt.sk2 + kr[i] * rt.sk1;
+        off = kt * BK + brow + i * RSTEP < kleft ? off : klast;
+        if constexpr (RIGHT::pairs) {
+          rb[i] = *reinterpret_cast<const u32x4 *>(bc0 + off);
+        } else {
+          rb[i] = __builtin_bit_cast(u32x4, frag_t{bc0[off], bc1[off]});
+        }
+        kq[i] += kq16;
+        kr[i] += kr16;
+        if (kr[i] >= rt.k1) {
+          kr[i] -= rt.k1;
+          ++kq[i];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < LB; ++i) rb[i] = *reinterpret_cast<const u32x4 *>(gB + i * stepB + kb);
+    }
   };
   // rows of one thread differ by NT / 8, a multiple of 16: one swizzle for all
   static_assert((NT / CPR) % 16 == 0, "swizzle period");
@@ -180,22 +253,37 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
   auto sstore = [&](int stage) {
 #pragma unroll
     for (int i = 0; i < LA; ++i) *reinterpret_cast<u32x4 *>(sbase + stage * STAGE + i * (NT / CPR) * RB) = ra[i];
+    if constexpr (COLS) {
 #pragma unroll
-    for (int i = 0; i < LB; ++i)
-      *reinterpret_cast<u32x4 *>(sbase + stage * STAGE + BM * RB + i * (NT / CPR) * RB) = rb[i];
+      for (int i = 0; i < LB; ++i)
+        *reinterpret_cast<u32x4 *>(smem + stage * STAGE + BM * RB + (brow + i * RSTEP) * LDN + bcol * 8) = rb[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < LB; ++i)
+        *reinterpret_cast<u32x4 *>(sbase + stage * STAGE + BM * RB + i * (NT / CPR) * RB) = rb[i];
+    }
   };
   // half f of a lane's K share of a row: chunk 2 g + f
   const int swz = pipe_swz(r16);
   const int fro[2] = {((2 * g) ^ swz) << 4, ((2 * g + 1) ^ swz) << 4};
-  const int abase = (wm * TM + r16) * RB, bbase = BM * RB + (wn * TN + r16) * RB;
+  const int abase = (wm * TM + r16) * RB;
+  const int bbase = BM * RB + (COLS ? 4 * g * LDN + (wn * TN + r16) * 8 : (wn * TN + r16) * RB);
   frag_t fa[2][FM], fb[2][FN];
   auto fload = [&](int stage, auto half) {
     constexpr int f = decltype(half)::value;
     const unsigned char *s = smem + stage * STAGE + fro[f];
 #pragma unroll
     for (int i = 0; i < FM; ++i) fa[f][i] = *reinterpret_cast<const frag_t *>(s + abase + i * 16 * RB);
+    if constexpr (COLS) {   // rows 4 g + 2 f and 4 g + 2 f + 1 of the tile
+      const unsigned char *sb = smem + stage * STAGE + bbase + 2 * f * LDN;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) fb[f][j] = *reinterpret_cast<const frag_t *>(s + bbase + j * 16 * RB);
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) fb[f][j][s2] = *reinterpret_cast<const double *>(sb + s2 * LDN + j * 16 * 8);
+    } else {
+#pragma unroll
+      for (int j = 0; j < FN; ++j) fb[f][j] = *reinterpret_cast<const frag_t *>(s + bbase + j * 16 * RB);
+    }
   };
   acc_t acc[FM][FN];
   v4d acc64[F64SUM ? FM : 1][F64SUM ? FN : 1];
@@ -260,7 +348,7 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
 
   gload(0);
   sstore(0);
-  if (ktiles > 1) gload(1);
+  if (ktn > 1) gload(1);
   barrier();
   fload(0, I0);
   // one K tile: `store`: tile kt + 1 (in registers) goes to the other stage, `load`: tile kt + 2 is fetched
@@ -306,8 +394,8 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc64[i][j][e] += double(acc[i][j][e]);
   } else {
-    while (kt + 2 < ktiles) body(kt++, NO, YES, YES);
-    if (kt + 1 < ktiles) body(kt++, NO, YES, NO);
+    while (kt + 2 < ktn) body(kt++, NO, YES, YES);
+    if (kt + 1 < ktn) body(kt++, NO, YES, NO);
     body(kt, NO, NO, NO);
   }
 #pragma unroll
@@ -318,6 +406,9 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
       for (int e = 0; e < 4; ++e) {
         // row of accumulator e: 4 g + e for the FP32 instruction, g + 4 e for the FP64 one
         const int row = PREC == 0 ? g + 4 * e : 4 * g + e;
+        if constexpr (COLS) {
+          if (m0 + wm * TM + i * 16 + row >= rt.M || n0 + wn * TN + j * 16 + r16 >= rt.N) continue;
+        }
         auto *dst = C + (m0 + wm * TM + i * 16 + row) * ldc + n0 + wn * TN + j * 16 + r16;
         if constexpr (F64SUM)
           *dst = ACCUM ? float(double(*dst) + acc64[i][j][e]) : float(acc64[i][j][e]);
@@ -573,10 +664,27 @@ void launch_pipe(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N,
   auto *c = static_cast<out_t *>(C);
   if (accum)
     hipLaunchKernelGGL((gemm_pipe_kernel<PREC, BM, BN, WM, WN, MINW, true>), grid, block, lds, st, a, b, c, tm, tn, kt,
-                       lda, ldb, ldc, c_split_stride, batch_a, batch_b, batch_c);
+                       lda, ldb, ldc, c_split_stride, batch_a, batch_b, batch_c, RowsRight{});
   else
     hipLaunchKernelGGL((gemm_pipe_kernel<PREC, BM, BN, WM, WN, MINW, false>), grid, block, lds, st, a, b, c, tm, tn,
-                       kt, lda, ldb, ldc, c_split_stride, batch_a, batch_b, batch_c);
+                       kt, lda, ldb, ldc, c_split_stride, batch_a, batch_b, batch_c, RowsRight{});
+  TRG_HIP_CHECK(hipGetLastError());
+}
+
+template <int BM, int BN, int MINW, bool PAIRS>
+void launch_cols(const double *A, const double *B, double *C, uint64_t lda, uint32_t splits, uint32_t kt,
+                 const ColsRight<PAIRS> &rt, hipStream_t st) {
+  constexpr size_t lds = 2 * (size_t(BM) * 128 + 16 * size_t(BN + 4) * 8);
+  auto *kernel = &gemm_pipe_kernel<0, BM, BN, 2, 2, MINW, false, ColsRight<PAIRS>>;
+  static const bool attr = [kernel] {
+    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+    return true;
+  }();
+  (void)attr;
+  const uint32_t tm = (rt.M + BM - 1) / BM, tn = (rt.N + BN - 1) / BN;
+  hipLaunchKernelGGL(kernel, dim3(tm * tn, splits), dim3(256), lds, st, A, B, C, tm, tn, kt, lda, uint64_t(0),
+                     uint64_t(rt.N), uint64_t(rt.M) * rt.N, uint64_t(0), uint64_t(0), uint64_t(0), rt);
   TRG_HIP_CHECK(hipGetLastError());
 }
 
@@ -859,6 +967,76 @@ void gemm_nt_splitk_f64(const double *A, const double *Bt, double *Cpart, uint64
   TRG_REQUIRE(K == uint64_t(splits) * kper, "splitk: K != splits * kper");
   if (check_gemm<0>(64, 64, 16, Cpart, M, N, K, lda, ldb, N, false, st, splits, 1, 0, 0, 0))
     gemm_f64(A, Bt, Cpart, M, N, K, lda, ldb, N, false, st, splits, M * N, 1, 0, 0, 0, false);
+}
+
+// Tile and number of K ranges of a product with a column-contiguous right
+// operand, by the time of its rounds on 256 CUs (tile area times the length of
+// a range over the rate of the tile, as for the other FP64 products) and, with
+// several ranges, the traffic of the partial sums (4 TB/s) and their launch.
+ColsPlan gemm_cols_plan(uint64_t M, uint64_t N, uint64_t K) {
+  struct Tile {
+    uint64_t bm, bn;
+    double rate;
+  };
+  constexpr Tile tiles[3] = {{128, 128, RATE_128}, {64, 128, RATE_64_128}, {64, 64, RATE_64}};
+  const uint64_t kt = (K + 15) / 16;
+  ColsPlan best{};
+  double tbest = 1e300;
+  for (int i = 0; i < 3; ++i) {
+    const Tile &t = tiles[i];
+    const uint64_t n = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    for (uint64_t want = 1; want <= 32 && want <= kt; ++want) {
+      const uint64_t per = (kt + want - 1) / want, splits = (kt + per - 1) / per;
+      double time = std::ceil(double(n) * double(splits) / 256.0) * double(t.bm * t.bn * 2 * 16) * double(per) * 256.0 /
+                    (t.rate * 1e12);
+      if (splits > 1) time += 5e-6 + double(splits + 1) * double(M) * double(N) * 8.0 / 4e12;
+      if (time < tbest) {
+        tbest = time;
+        best = ColsPlan{i, uint32_t(splits), uint32_t(per)};
+      }
+    }
+  }
+  return best;
+}
+
+// C[m][n] = sum_k A[m][k] B(k, n): A K-contiguous with pitch lda, its rows
+// zero-padded to a multiple of 128 and its columns to one of 16; B as described
+// at ColsRight; C (M x N, unpadded) or, with several K ranges, `part` receives
+// one M x N slab per range, summed into C in order.
+void gemm_cols_f64(const ColsPlan &plan, const double *A, uint64_t lda, const double *B, const ColsShape &s, double *C,
+                   double *part, hipStream_t st) {
+  constexpr uint64_t lim = uint64_t(1) << 31;
+  TRG_REQUIRE(s.M >= 1 && s.N >= 1 && s.K >= 1 && s.M < lim && s.N < lim && s.K < lim && s.k1 >= 1 && s.n1 >= 1 &&
+                  s.k1 <= s.K && s.n1 <= s.N,
+              "gemm_cols: bad shape");
+  TRG_REQUIRE(lda % 2 == 0 && lda >= (s.K + 15) / 16 * 16 && reinterpret_cast<uintptr_t>(A) % 16 == 0,
+              "gemm_cols: bad left operand");
+  TRG_REQUIRE(plan.splits >= 1 && uint64_t(plan.splits - 1) * plan.ktiles < (s.K + 15) / 16 &&
+                  uint64_t(plan.splits) * plan.ktiles >= (s.K + 15) / 16 && (plan.splits == 1 || part),
+              "gemm_cols: bad plan");
+  TRG_REQUIRE(((s.M + 63) / 64) * ((s.N + 63) / 64) < lim, "gemm_cols: too many tiles");
+  const bool pairs = s.N % 2 == 0 && s.n1 % 2 == 0 && s.sk1 % 2 == 0 && s.sk2 % 2 == 0 && s.sn2 % 2 == 0 &&
+                     reinterpret_cast<uintptr_t>(B) % 16 == 0;
+  double *out = plan.splits > 1 ? part : C;
+  auto launch = [&](auto rt) {
+    constexpr bool P = decltype(rt)::pairs;
+    rt.M = uint32_t(s.M);
+    rt.N = uint32_t(s.N);
+    rt.K = uint32_t(s.K);
+    rt.k1 = uint32_t(s.k1);
+    rt.n1 = uint32_t(s.n1);
+    rt.sk1 = s.sk1;
+    rt.sk2 = s.sk2;
+    rt.sn2 = s.sn2;
+    if (plan.tile == 0) launch_cols<128, 128, 2, P>(A, B, out, lda, plan.splits, plan.ktiles, rt, st);
+    else if (plan.tile == 1) launch_cols<64, 128, 3, P>(A, B, out, lda, plan.splits, plan.ktiles, rt, st);
+    else launch_cols<64, 64, 4, P>(A, B, out, lda, plan.splits, plan.ktiles, rt, st);
+  };
+  if (pairs) launch(ColsRight<true>{});
+  else launch(ColsRight<false>{});
+  if (plan.splits > 1)
+    reduce_splits(part, int(plan.splits), int64_t(s.M), int64_t(s.N), int64_t(s.N), int64_t(s.M * s.N), C, int64_t(s.N),
+                  st);
 }
 
 }  // namespace trg

@@ -30,6 +30,18 @@ bool gemm_f64_ksplit(uint64_t M, uint64_t N, uint64_t K);
 void gemm_nt_splitk_f64(const double *A, const double *Bt, double *Cpart, uint64_t M, uint64_t N,
                         uint64_t K, uint64_t lda, uint64_t ldb, uint32_t splits, uint64_t kper,
                         hipStream_t st);
+// FP64 product whose right operand is a tensor read in place, its columns
+// contiguous: C[m][n] = sum_k A[m][k] B[(k / k1) sk2 + (k % k1) sk1 + (n / n1) sn2 + n % n1]
+struct ColsShape {
+  uint64_t M, N, K, k1, sk1, sk2, n1, sn2;
+};
+struct ColsPlan {   // tile, K ranges (each writes an M x N slab if several) and their length in 16s
+  int tile;
+  uint32_t splits, ktiles;
+};
+ColsPlan gemm_cols_plan(uint64_t M, uint64_t N, uint64_t K);
+void gemm_cols_f64(const ColsPlan &plan, const double *A, uint64_t lda, const double *B, const ColsShape &s, double *C,
+                   double *part, hipStream_t st);
 
 // Contexts one batched launch serves (pointer tables are passed by value)
 constexpr int TRG_MAXB = 64;

@@ -116,6 +116,30 @@ def test_swap_spectrum_at_factorisation_block_edges(cols):
     assert err < 1e-8
 
 
+@pytest.mark.parametrize("D,d,mu,cols", [(2, 4, 0, 5), (2, 2, 1, 4), (3, 4, 3, 9), (5, 4, 2, 20), (5, 3, 0, 25),
+                                         (9, 3, 2, 33), (17, 2, 0, 34), (8, 4, 1, 66), (10, 4, 3, 50)])
+def test_swap_spectrum_over_product_shapes(D, d, mu, cols):
+    """The products of the power iteration read their tensors in place: summed
+    legs shorter than a K tile and wrapping inside one, odd and even column
+    counts, partial tiles in both directions, one and several K ranges.
+    Tolerance as at bond dimension 24."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_factors
+    announce("atrg products", D, d, mu, cols)
+    rng = np.random.default_rng(1000 * D + cols)
+    decay = 0.5 ** np.arange(D)
+    G = rng.standard_normal((D,) * d + (D,)) * decay
+    H = rng.standard_normal((D,) + (D,) * d) * decay.reshape((D,) + (1,) * d)
+    ctx = trg_init_factors(G, H, dcut=D, rsvd_p=cols - D, rsvd_q=2, seed=7)
+    ctx.atrg_step(mu, D)
+    sig = ctx.atrg_spectrum()
+    ctx.close()
+    ref = atrg.rsvd_swap(atrg.canonical(G, H, D), mu, D, cols - D, 2, 1, 7)[1]
+    err = np.max(np.abs(sig - ref)) / ref[0]
+    print(f"[atrg products {D} {d} {mu} {cols}] max |sigma_gpu - sigma_oracle| / sigma_max = {err:.3e}", flush=True)
+    assert err < 1e-8
+
+
 # ------------------------------------------------------------ impure tensors ---
 def _gpu_impure(beta, h, d, dcut, L, **cfg):
     from paper_1911_12954_amd import trg_init_ising
