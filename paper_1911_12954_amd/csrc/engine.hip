@@ -111,13 +111,15 @@ std::vector<int64_t> canon_strides(const int *dims, int d) {
 }
 
 // ---------------------------------------------------------------- Grams ---
-// Environment of one site keeping legs l1 (rows major) and l2: X[(l1,l2)][rest]
-// then X X^T by split-K MFMA.  Result R x R (R = dim(l1) dim(l2)) in out.
-void environment(trg_ctx &c, const double *T, int l1, int l2, double *out, const std::string &tag) {
+// Environments of one site keeping legs l1 (rows major) and l2: X[(l1,l2)][rest],
+// then X X^T, for leg pairs whose R = dim(l1) dim(l2) agree; results R x R, one
+// after the other in out.  Columns are split over workgroups (about 1024 tiles
+// of 64 x 64), so a slab's sum does not depend on how many environments one
+// launch takes.
+void environments(trg_ctx &c, const double *T, const std::vector<std::pair<int, int>> &legs, double *out) {
   const int d = c.d;
   auto st_ = canon_strides(c.dims, d);
-  const int64_t n1 = c.dims[l1 / 2], n2 = c.dims[l2 / 2];
-  const int64_t R = n1 * n2, C = c.total() / R;
+  const int64_t R = int64_t(c.dims[legs[0].first / 2]) * c.dims[legs[0].second / 2], C = c.total() / R;
   const int64_t Rp = int64_t(round_up(R, 64));
   const int64_t tiles = (Rp / 64) * (Rp / 64);
   int64_t splits = (1024 + tiles - 1) / tiles;
@@ -126,22 +128,52 @@ void environment(trg_ctx &c, const double *T, int l1, int l2, double *out, const
   if (splits < 1) splits = 1;
   const int64_t kper = int64_t(round_up((C + splits - 1) / splits, 16));
   const int64_t Cp = kper * splits;
-  double *X = c.wsp<double>("gram_X" + tag, size_t(Rp) * Cp * 8);
-  double *part = c.wsp<double>("gram_part" + tag, size_t(splits) * Rp * Rp * 8);
-  // X rows (l1, l2), columns: the other legs in canonical order
-  View inv;
-  for (int l = 0; l < 2 * d; ++l) inv.push_back(Leg{"l" + std::to_string(l), c.dims[l / 2], st_[l]});
-  std::vector<std::pair<std::string, int64_t>> cols;
-  for (int l = 0; l < 2 * d; ++l)
-    if (l != l1 && l != l2) cols.push_back({"l" + std::to_string(l), c.dims[l / 2]});
-  View outv = contiguous(cols);
-  outv.insert(outv.begin(), Leg{"l" + std::to_string(l2), n2, Cp});
-  outv.insert(outv.begin(), Leg{"l" + std::to_string(l1), n1, n2 * Cp});
-  apply_map(T, IN_F64, inv, nullptr, {}, {}, X, OUT_F64, 0, outv, c.st);
-  zero_pad(X, R, Rp, C, Cp, 8, 1, 0, c.st);
-  gemm_nt_splitk_f64(X, X, part, uint64_t(Rp), uint64_t(Rp), uint64_t(Cp), uint64_t(Cp), uint64_t(Cp),
-                     uint32_t(splits), uint64_t(kper), c.st);
-  reduce_splits(part, int(splits), R, R, Rp, Rp * Rp, out, R, c.st);
+  if (R <= ENV_MAXR && C < (int64_t(1) << 31)) {
+    // As many environments in a launch as take no more scratch than one
+    // environment's padded copy and padded slabs (4D Dcut 4: all 12, 6: 5, 8: 5).
+    int64_t most = Rp * (kper + Rp) / (R * R);
+    most = std::max<int64_t>(1, std::min<int64_t>(most, ENV_MAXE));
+    double *part = c.wsp<double>("gram_part", size_t(std::min<int64_t>(most, int64_t(legs.size()))) * splits * R * R * 8);
+    for (size_t l = 0; l < legs.size(); l += size_t(most)) {
+      const int n = int(std::min<size_t>(size_t(most), legs.size() - l));
+      EnvGrams p{};
+      for (int e = 0; e < n; ++e) {
+        const auto [l1, l2] = legs[l + size_t(e)];
+        EnvGram &v = p.env[e];
+        v.s1 = st_[l1];
+        v.s2 = st_[l2];
+        v.n2 = c.dims[l2 / 2];
+        for (int x = 0; x < 2 * d; ++x)
+          if (x != l1 && x != l2) {
+            v.div[v.nc] = make_fastdiv(uint32_t(c.dims[x / 2]));
+            v.sc[v.nc++] = st_[x];
+          }
+      }
+      env_grams(T, p, n, int(R), C, kper, int(splits), part, c.st);
+      reduce_splits(part, int(splits), R, R, R, R * R, out + int64_t(l) * R * R, R, c.st, n, splits * R * R, R * R);
+    }
+    return;
+  }
+  double *X = c.wsp<double>("gram_X", size_t(Rp) * Cp * 8);
+  double *part = c.wsp<double>("gram_part", size_t(splits) * Rp * Rp * 8);
+  for (size_t l = 0; l < legs.size(); ++l) {
+    const auto [l1, l2] = legs[l];
+    const int64_t n1 = c.dims[l1 / 2], n2 = c.dims[l2 / 2];
+    // X rows (l1, l2), columns: the other legs in canonical order
+    View inv;
+    for (int x = 0; x < 2 * d; ++x) inv.push_back(Leg{"l" + std::to_string(x), c.dims[x / 2], st_[x]});
+    std::vector<std::pair<std::string, int64_t>> cols;
+    for (int x = 0; x < 2 * d; ++x)
+      if (x != l1 && x != l2) cols.push_back({"l" + std::to_string(x), c.dims[x / 2]});
+    View outv = contiguous(cols);
+    outv.insert(outv.begin(), Leg{"l" + std::to_string(l2), n2, Cp});
+    outv.insert(outv.begin(), Leg{"l" + std::to_string(l1), n1, n2 * Cp});
+    apply_map(T, IN_F64, inv, nullptr, {}, {}, X, OUT_F64, 0, outv, c.st);
+    zero_pad(X, R, Rp, C, Cp, 8, 1, 0, c.st);
+    gemm_nt_splitk_f64(X, X, part, uint64_t(Rp), uint64_t(Rp), uint64_t(Cp), uint64_t(Cp), uint64_t(Cp),
+                       uint32_t(splits), uint64_t(kper), c.st);
+    reduce_splits(part, int(splits), R, R, Rp, Rp * Rp, out + int64_t(l) * R * R, R, c.st);
+  }
 }
 
 // ------------------------------------------------------------ operands ---
@@ -423,22 +455,25 @@ void isometries_batch(std::vector<trg_ctx *> &cs, std::vector<StepPrep> &ps, int
   const size_t slot_n = size_t(nmax);   // = every n_a when same_n
   auto gbase = [&](int a) { return size_t(a) * per_ax * slot_n * slot_n; };
   auto wbase = [&](int a) { return size_t(a) * per_ax * slot_n; };
-  for (int a = 0; a < nax; ++a) {
-    const int ax = others[a];
-    const int dn = c0.dims[ax];
-    const int n = dn * dn;
-    const size_t ms = size_t(n) * n;   // matrix stride inside the slot
-    const int dmu = c0.dims[mu];
+  // the environments of axes of one order together, else axis by axis
+  const int naxg = same_n ? nax : 1;
+  const int dmu = c0.dims[mu];
+  for (int a = 0; a < nax; a += naxg) {
+    const int dn = c0.dims[others[a]];
     const int64_t R = int64_t(dmu) * dn;
+    const size_t ms = size_t(dn) * dn * dn * dn;   // matrix stride inside the slot
+    std::vector<std::pair<int, int>> legs;
+    for (int x = a; x < a + naxg; ++x)
+      for (int side = 0; side < 2; ++side) {
+        legs.push_back({2 * mu + 1, 2 * others[x] + side});
+        legs.push_back({2 * mu, 2 * others[x] + side});
+      }
     for (int i = 0; i < nc; ++i) {
       trg_ctx &c = *cs[i];
-      double *PQ = c.wsp<double>("gram_PQ", size_t(2) * R * R * 8);
-      const double *T = static_cast<const double *>(c.T.ptr);
-      for (int side = 0; side < 2; ++side) {
-        environment(c, T, 2 * mu + 1, 2 * ax + side, PQ, "");
-        environment(c, T, 2 * mu, 2 * ax + side, PQ + R * R, "");
-        gram_combine(PQ, PQ + R * R, dmu, dn, G + gbase(a) + (size_t(i) * 2 + side) * ms, c.st);
-      }
+      double *PQ = c.wsp<double>("gram_PQ", legs.size() * R * R * 8);
+      environments(c, static_cast<const double *>(c.T.ptr), legs, PQ);
+      gram_combine(PQ, PQ + R * R, dmu, dn, G + gbase(a) + size_t(i) * 2 * ms, c.st, 2 * naxg,
+                   int64_t(per_ax) * ms);
     }
   }
   // every eigenvalue, and the eigenvectors of the kept columns plus a

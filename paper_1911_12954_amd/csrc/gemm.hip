@@ -43,7 +43,6 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int NUM_XCD = 8;
 // FP32 join: K tiles (32 floats each) summed by the MFMA in FP32 before the
 // partial sum is added to the FP64 accumulator
 constexpr uint32_t F32_FLUSH = 4;

@@ -5,6 +5,8 @@
 
 namespace trg {
 
+constexpr int NUM_XCD = 8;   // workgroups go to the XCDs (one L2 each) in turn
+
 // ------------------------------------------------------------------ GEMM ---
 struct GemmTile {
   int m, n, k;
@@ -80,12 +82,31 @@ void fill_zero(void *buf, size_t bytes, hipStream_t st);
 
 // sum of split-K partials: out[r*ldo + c] = sum_s part[s][r*ldp + c]
 void reduce_splits(const double *part, int splits, int64_t rows, int64_t cols, int64_t ldp,
-                   int64_t split_stride, double *out, int64_t ldo, hipStream_t st);
+                   int64_t split_stride, double *out, int64_t ldo, hipStream_t st, int nb = 1,
+                   int64_t part_batch = 0, int64_t out_batch = 0);
+
+// Environment Grams of leg pairs of one tensor: rows (l1, l2) with strides s1,
+// s2 and n2 values of l2; nc column legs, outermost first.  Environment e's
+// slab of columns [s kper, (s + 1) kper) is part + (e splits + s) R^2.
+constexpr int ENV_MAXE = 12, ENV_MAXC = 6, ENV_MAXR = 128;
+struct EnvGram {
+  int64_t s1, s2, sc[ENV_MAXC];
+  FastDiv div[ENV_MAXC];
+  int32_t n2, nc;
+};
+struct EnvGrams {
+  EnvGram env[ENV_MAXE];
+};
+void env_grams(const double *T, const EnvGrams &p, int nenv, int R, int64_t C, int64_t kper, int splits, double *part,
+               hipStream_t st);
 
 // Gram of the two-site tensor from the one-site environments P and Q
 // (both (dmu*dn) x (dmu*dn), row index (i, a)): G[(a,b),(a',b')] =
 // sum_{i,i'} P[(i,a),(i',a')] Q[(i,b),(i',b')]
-void gram_combine(const double *P, const double *Q, int dmu, int dn, double *G, hipStream_t st);
+// npairs > 1: pair y (P, Q behind each other, 2 (dmu dn)^2 apart) is side y % 2
+// of axis y / 2, whose two Grams start axis_stride apart from the next axis's
+void gram_combine(const double *P, const double *Q, int dmu, int dn, double *G, hipStream_t st, int npairs = 1,
+                  int64_t axis_stride = 0);
 
 // Frobenius norm of n doubles: partials then one block; writes
 // scal[0] = c, scal[1] = 1/c, scal[2] = ln c, acc[0] += weight * ln c; sets

@@ -4,6 +4,7 @@
 // tensors.
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -207,9 +208,12 @@ __device__ inline double sum_splits(const double *p, int k0, int splits, int64_t
 }
 
 __global__ void reduce_splits_kernel(const double *part, int splits, int64_t rows, int64_t cols,
-                                     int64_t ldp, int64_t sstride, double *out, int64_t ldo) {
+                                     int64_t ldp, int64_t sstride, double *out, int64_t ldo, int64_t pbatch,
+                                     int64_t obatch) {
   const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= rows * cols) return;
+  part += int64_t(blockIdx.y) * pbatch;
+  out += int64_t(blockIdx.y) * obatch;
   const int64_t r = i / cols, c = i % cols;
   out[r * ldo + c] = sum_splits<1>(part + r * ldp + c, 0, splits, sstride);
 }
@@ -223,7 +227,9 @@ constexpr int RS_OUT = 32, RS_GROUPS = 8;
 
 __global__ void __launch_bounds__(RS_OUT * RS_GROUPS)
 reduce_splits_grouped_kernel(const double *part, int splits, int64_t rows, int64_t cols, int64_t ldp,
-                             int64_t sstride, double *out, int64_t ldo) {
+                             int64_t sstride, double *out, int64_t ldo, int64_t pbatch, int64_t obatch) {
+  part += int64_t(blockIdx.y) * pbatch;
+  out += int64_t(blockIdx.y) * obatch;
   __shared__ double sh[RS_GROUPS][RS_OUT];
   const int o = threadIdx.x % RS_OUT, g = threadIdx.x / RS_OUT;
   const int64_t i = int64_t(blockIdx.x) * RS_OUT + o;
@@ -241,8 +247,143 @@ reduce_splits_grouped_kernel(const double *part, int splits, int64_t rows, int64
   }
 }
 
-__global__ void gram_combine_kernel(const double *P, const double *Q, int dmu, int dn, double *G) {
-  // G[(a,b),(a2,b2)] = sum_{i,i2} P[(i,a),(i2,a2)] Q[(i,b),(i2,b2)]
+// Environment Grams X X^T of up to EG_MAXE leg pairs of one tensor, read in
+// place: X has rows (l1, l2) (R <= 128 of them) and the other legs in canonical
+// order as columns, element T[row offset + column offset].  Workgroup (s, e)
+// sums the columns [s kper, (s + 1) kper) of environment e into its own R x R
+// slab.  Columns come in chunks of 32, gathered along the rows where the last
+// row leg is contiguous and along the columns otherwise, into LDS rows of one
+// column each (16 nb + 4 doubles: the two columns of a half wave's reads fall
+// on different banks); the next chunk is fetched while the MFMAs of the current
+// one run.  Only the blocks of 16 x 16 on and above the diagonal are computed,
+// dealt to the four waves.  MFMA t of a group of 16 columns takes column 4 g + t
+// from lane group g: the sum over the columns of a slab in the order of the
+// padded K-contiguous product, to the last bit.
+// Latency and launches bound it, so there is no packed copy, no padding and one
+// launch for several environments, and the block count is a template parameter
+// (one kernel for all had 207 registers, two waves per SIMD: 94 us where 56 now).
+// Measured, with the sum of the slabs, against packing, padding, the 64 x 64
+// split-K product and its sum environment by environment: 12 of 16 x 4096
+// (4D Dcut 4) 12 against 175 us, four of 36 x 46656 (Dcut 6) 67 against 205,
+// four of 64 x 262144 (Dcut 8) 0.28 against 2.7 ms.
+constexpr int EG_KC = 32;
+
+template <int NB>   // ceil(R / 16)
+__global__ void __launch_bounds__(256)
+env_gram_kernel(const double *__restrict__ T, EnvGrams p, int R, int64_t C, int64_t kper, double *__restrict__ part) {
+  constexpr int MAXB = (NB * (NB + 1) / 2 + 3) / 4, PER = 2 * NB;   // blocks of a wave, loads of a thread and chunk
+  typedef double v4d __attribute__((ext_vector_type(4)));
+  extern __shared__ double X[];   // [2][EG_KC][ld]
+  __shared__ int64_t roff[ENV_MAXR], coff[2][EG_KC];
+  const EnvGram &e = p.env[blockIdx.y];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int g = lane >> 4, r16 = lane & 15;
+  constexpr int ld = 16 * NB + 4;
+  // neighbouring column ranges on one XCD (bijective): their runs share cache lines
+  const uint32_t xcd = blockIdx.x % NUM_XCD, per = gridDim.x / NUM_XCD, rem = gridDim.x % NUM_XCD;
+  const int64_t split = xcd * per + (xcd < rem ? xcd : rem) + blockIdx.x / NUM_XCD;
+  const int64_t k0 = split * kper;
+  const int64_t k1 = k0 + kper < C ? k0 + kper : C;
+  const int nch = k1 > k0 ? int((k1 - k0 + EG_KC - 1) / EG_KC) : 0;
+  if (t < 16 * NB) {
+    const int r = t < R ? t : R - 1;
+    roff[t] = (r / e.n2) * e.s1 + (r % e.n2) * e.s2;
+  }
+  auto columns = [&](int ch) {   // offsets of the columns of a chunk (the last column again past the end)
+    if (t >= EG_KC) return;
+    const int64_t k = k0 + int64_t(ch) * EG_KC + t;
+    uint32_t q = uint32_t(k < k1 ? k : k1 - 1);
+    int64_t o = 0;
+#pragma unroll
+    for (int j = ENV_MAXC - 1; j >= 0; --j)
+      if (j < e.nc) {
+        const uint32_t qd = fast_div(q, e.div[j]);
+        o += int64_t(q - qd * e.div[j].d) * e.sc[j];
+        q = qd;
+      }
+    coff[ch & 1][t] = o;
+  };
+  if (nch > 0) columns(0);
+  __syncthreads();
+  const bool along = e.s2 == 1;   // lanes along the rows
+  double pre[PER];
+  auto where = [&](int u, int &r, int &k) {
+    const int idx = t + 256 * u;
+    r = along ? (idx & 15) + 16 * (idx >> 9) : idx >> 5;
+    k = along ? (idx >> 4) & 31 : idx & 31;
+  };
+  auto gload = [&](int ch) {
+    const int64_t left = k1 - k0 - int64_t(ch) * EG_KC;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      int r, k;
+      where(u, r, k);
+      const double x = T[roff[r] + coff[ch & 1][k]];
+      pre[u] = r < R && k < left ? x : 0.0;
+    }
+  };
+  auto sstore = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      int r, k;
+      where(u, r, k);
+      X[(buf * EG_KC + k) * ld + r] = pre[u];
+    }
+  };
+  int bi[MAXB], bj[MAXB], nmine = 0;
+#pragma unroll
+  for (int q = 0; q < MAXB; ++q) bi[q] = bj[q] = 0;
+  for (int i = 0, b = 0; i < NB; ++i)
+    for (int j = i; j < NB; ++j, ++b)
+      if ((b & 3) == wave && nmine < MAXB) {
+        bi[nmine] = i;
+        bj[nmine] = j;
+        ++nmine;
+      }
+  v4d acc[MAXB];
+#pragma unroll
+  for (int q = 0; q < MAXB; ++q) acc[q] = v4d{0.0, 0.0, 0.0, 0.0};
+  if (nch > 0) {
+    gload(0);
+    sstore(0);
+    if (nch > 1) columns(1);
+  }
+  __syncthreads();
+  for (int ch = 0; ch < nch; ++ch) {
+    if (ch + 1 < nch) gload(ch + 1);
+#pragma unroll
+    for (int s = 0; s < EG_KC / 4; ++s) {
+      const double *col = X + ((ch & 1) * EG_KC + 16 * (s >> 2) + 4 * g + (s & 3)) * ld + r16;
+#pragma unroll
+      for (int q = 0; q < MAXB; ++q)
+        if (q < nmine) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(col[16 * bi[q]], col[16 * bj[q]], acc[q], 0, 0, 0);
+    }
+    // both buffers' last readers passed the barrier that ended the chunk before
+    if (ch + 1 < nch) sstore((ch + 1) & 1);
+    if (ch + 2 < nch) columns(ch + 2);
+    __syncthreads();
+  }
+  double *out = part + (int64_t(blockIdx.y) * gridDim.x + split) * R * R;
+#pragma unroll
+  for (int q = 0; q < MAXB; ++q)
+    if (q < nmine)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = 16 * bi[q] + g + 4 * i, col = 16 * bj[q] + r16;
+        if (row < R && col < R) {
+          out[row * R + col] = acc[q][i];
+          out[col * R + row] = acc[q][i];
+        }
+      }
+}
+
+__global__ void gram_combine_kernel(const double *P, const double *Q, int dmu, int dn, double *G, int64_t axis_stride) {
+  // G[(a,b),(a2,b2)] = sum_{i,i2} P[(i,a),(i2,a2)] Q[(i,b),(i2,b2)]; grid.y =
+  // 2 axis + side: pairs P, Q one after the other, G's sides together
+  const int64_t pq = int64_t(blockIdx.y) * 2 * dmu * dn * dmu * dn;
+  P += pq;
+  Q += pq;
+  G += int64_t(blockIdx.y >> 1) * axis_stride + int64_t(blockIdx.y & 1) * dn * dn * dn * dn;
   const int n = dn * dn;
   const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (t >= int64_t(n) * n) return;
@@ -519,21 +660,62 @@ void fill_zero(void *buf, size_t bytes, hipStream_t st) {
 }
 
 void reduce_splits(const double *part, int splits, int64_t rows, int64_t cols, int64_t ldp,
-                   int64_t split_stride, double *out, int64_t ldo, hipStream_t st) {
+                   int64_t split_stride, double *out, int64_t ldo, hipStream_t st, int nb, int64_t part_batch,
+                   int64_t out_batch) {
   const int64_t n = rows * cols;
   if (splits >= 2 * RS_GROUPS && n < int64_t(256) * 1024) {
-    hipLaunchKernelGGL(reduce_splits_grouped_kernel, dim3(uint32_t((n + RS_OUT - 1) / RS_OUT)),
-                       dim3(RS_OUT * RS_GROUPS), 0, st, part, splits, rows, cols, ldp, split_stride, out, ldo);
+    hipLaunchKernelGGL(reduce_splits_grouped_kernel, dim3(uint32_t((n + RS_OUT - 1) / RS_OUT), nb),
+                       dim3(RS_OUT * RS_GROUPS), 0, st, part, splits, rows, cols, ldp, split_stride, out, ldo,
+                       part_batch, out_batch);
   } else {
-    hipLaunchKernelGGL(reduce_splits_kernel, dim3(uint32_t((n + 255) / 256)), dim3(256), 0, st, part, splits,
-                       rows, cols, ldp, split_stride, out, ldo);
+    hipLaunchKernelGGL(reduce_splits_kernel, dim3(uint32_t((n + 255) / 256), nb), dim3(256), 0, st, part, splits,
+                       rows, cols, ldp, split_stride, out, ldo, part_batch, out_batch);
   }
   TRG_HIP_CHECK(hipGetLastError());
 }
 
-void gram_combine(const double *P, const double *Q, int dmu, int dn, double *G, hipStream_t st) {
+void env_grams(const double *T, const EnvGrams &p, int nenv, int R, int64_t C, int64_t kper, int splits, double *part,
+               hipStream_t st) {
+  TRG_REQUIRE(nenv >= 1 && nenv <= ENV_MAXE && R >= 1 && R <= ENV_MAXR && C >= 1 && C < (int64_t(1) << 31) &&
+                  kper >= 1 && splits >= 1 && kper * splits >= C,
+              "env_grams: bad shape");
+  for (int e = 0; e < nenv; ++e) {
+    const EnvGram &v = p.env[e];
+    int64_t cols = 1;
+    TRG_REQUIRE(v.nc >= 0 && v.nc <= ENV_MAXC && v.n2 >= 1 && R % v.n2 == 0, "env_grams: bad legs");
+    for (int j = 0; j < v.nc; ++j) cols *= v.div[j].d;
+    TRG_REQUIRE(cols == C, "env_grams: columns do not match");
+  }
+  auto launch = [&](auto blocks) {
+    constexpr int NB = decltype(blocks)::value;
+    constexpr int lds = 2 * EG_KC * (16 * NB + 4) * 8;
+    static const bool attr = [] {   // dynamic LDS above 64 KB must be allowed per kernel
+      TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&env_gram_kernel<NB>),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      return true;
+    }();
+    (void)attr;
+    hipLaunchKernelGGL((env_gram_kernel<NB>), dim3(uint32_t(splits), uint32_t(nenv)), dim3(256), lds, st, T, p, R, C,
+                       kper, part);
+    TRG_HIP_CHECK(hipGetLastError());
+  };
+  switch ((R + 15) / 16) {
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 5: launch(std::integral_constant<int, 5>{}); break;
+    case 6: launch(std::integral_constant<int, 6>{}); break;
+    case 7: launch(std::integral_constant<int, 7>{}); break;
+    default: launch(std::integral_constant<int, 8>{}); break;
+  }
+}
+
+void gram_combine(const double *P, const double *Q, int dmu, int dn, double *G, hipStream_t st, int npairs,
+                  int64_t axis_stride) {
   const int64_t n2 = int64_t(dn) * dn * dn * dn;
-  hipLaunchKernelGGL(gram_combine_kernel, dim3(uint32_t((n2 + 255) / 256)), dim3(256), 0, st, P, Q, dmu, dn, G);
+  hipLaunchKernelGGL(gram_combine_kernel, dim3(uint32_t((n2 + 255) / 256), uint32_t(npairs)), dim3(256), 0, st, P, Q, dmu,
+                     dn, G, axis_stride);
   TRG_HIP_CHECK(hipGetLastError());
 }
 

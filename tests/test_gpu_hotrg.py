@@ -55,6 +55,32 @@ def test_single_step_matches_oracle(d, dims, mu, dcut, seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("d,dims,mu,dcut,seed", [
+    (2, (1, 5), 0, 5, 21),      # a leg of size one
+    (2, (17, 1), 0, 1, 22),     # 17 rows: one past a block of 16
+    (2, (11, 11), 1, 11, 23),   # 121 rows, ragged last block
+    (2, (8, 16), 0, 16, 24),    # 128 rows, the most one workgroup sums
+    (2, (43, 3), 0, 3, 25),     # 129 rows: the packed product
+    (3, (8, 7, 6), 1, 6, 26),   # axes of different order, 56 and 42 rows
+    (3, (4, 12, 12), 0, 12, 27),   # 48 rows, more columns than one chunk in a range
+    (4, (6, 6, 6, 6), 2, 3, 28),   # 36 rows, several environments in a launch but not all
+])
+def test_environment_grams_at_block_edges(d, dims, mu, dcut, seed):
+    """The two-site Gram spectra come straight from the environments: bounds of
+    the single-step comparison above."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_tensor
+    announce("environment grams", d, dims, mu, dcut, seed)
+    T = random_site_tensor(dims, seed, positive_bias=True)
+    _, _, choices = _oracle_step(T, mu, dcut)
+    ctx = trg_init_tensor(T, precision="fp64")
+    ctx.hotrg_step(mu, dcut)
+    for ch in choices:
+        _, spec = ctx.isometry(ch.nu)
+        assert np.max(np.abs(spec - ch.spectrum)) < 1e-13 * max(abs(ch.spectrum[0]), 1e-300)
+    ctx.close()
+
+
 @pytest.mark.parametrize("budget", [14_000_000, 30_000_000])
 def test_sliced_join_is_bitwise_equal(budget):
     """A small workspace forces the join into x0/x2 slices (14 MB: one value
