@@ -81,6 +81,33 @@ def test_environment_grams_at_block_edges(d, dims, mu, dcut, seed):
     ctx.close()
 
 
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-9), ("fp32", 1e-5), ("bf16x6", 1e-5), ("bf16x3", 1e-3)])
+@pytest.mark.parametrize("d,dims,mu,dcut,seed", [
+    (2, (3, 2), 0, 2, 31), (2, (4, 5), 0, 3, 32), (2, (5, 6), 0, 6, 33), (2, (6, 15), 0, 15, 34),
+    (2, (4, 17), 0, 17, 35), (3, (5, 3, 4), 0, 4, 36), (3, (4, 6, 2), 1, 5, 37), (4, (2, 3, 4, 2), 0, 3, 38),
+    (4, (3, 2, 4, 5), 2, 4, 39),
+])
+def test_isometry_maps_in_every_precision(d, dims, mu, dcut, seed, precision, tol):
+    """Operand and compression maps: 1 to 16 and more new indices, pairs of
+    elements and single ones, with and without an axis compressed after the
+    join.  Of the largest element: in FP64 the eigenvectors (2^-53 over the
+    smallest gap, 5e-5 of the largest eigenvalue, with a factor of 100 to spare),
+    else the rounding of the operands (2^-24 in FP32 and
+    the three-way split, 2^-16 in the two-way one), times at most 2^6 for sums
+    whose terms cancel."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_tensor
+    announce("isometry maps", d, dims, mu, dcut, seed, precision)
+    T = random_site_tensor(dims, seed, positive_bias=True)
+    ref, _, _ = _oracle_step(T, mu, dcut)
+    ctx = trg_init_tensor(T, precision=precision)
+    ctx.hotrg_step(mu, dcut)
+    got = ctx.tensor()
+    ctx.close()
+    assert got.shape == ref.shape
+    assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("budget", [14_000_000, 30_000_000])
 def test_sliced_join_is_bitwise_equal(budget):
     """A small workspace forces the join into x0/x2 slices (14 MB: one value
