@@ -478,101 +478,173 @@ ts_gram_kernel(const double *__restrict__ Y, int64_t m, int k, int64_t rpw, doub
 }
 
 // Q = Y R for a tall m x k row-major Y and an upper triangular k x k R
-// (k <= 128; the inverse Cholesky factor) on FP64 MFMA.  R is staged once
-// per workgroup in LDS (row stride 144 doubles: the four k-rows that one
-// MFMA's B fragment reads fall on the two halves of the banks); the
-// workgroup then walks row tiles of 256 rows, each of its eight waves 32
-// rows x all columns, with Y read straight from memory into the A fragments
-// (lane (g, r16) takes columns 16u + 4g .. 16u + 4g + 3 of its two rows for
-// K chunk u, the next chunk prefetched while the current one is multiplied)
-// and Q written from the accumulators.  K index 16u + 4g + e feeds MFMA e of
-// chunk u on both sides, so the order of K inside a chunk is permuted alike
-// for A and B.  Blocks of R below the diagonal are zero and skipped: chunk u
-// only meets column blocks j >= u.
-constexpr int TSM_WAVES = 8, TSM_ROWS = 32 * TSM_WAVES, TSM_LD = 144;
+// (k <= 128; the inverse Cholesky factor) on FP64 MFMA and, with GRAM, the
+// partial sums of Q^T Q for the next pass of the QR, which then reads nothing:
+// workgroup b's slab part[b] is summed over the slabs in a fixed order.
+// R is staged once per workgroup in LDS (rows of 16 NB + 4 doubles: the two
+// k-rows that half a wave reads fall on different banks).  A wave walks tiles
+// of 16 rows; lane (g, r16) holds columns 16 u + 4 g .. + 3 of row r16 for every
+// chunk u of K, four chunks ahead of their use, across tiles.
+// K index 16 u + 4 g + e feeds MFMA e of chunk u on both sides, so the order of
+// K inside a chunk is permuted alike for A and B; R is zero below the diagonal,
+// so chunk u only meets column blocks j >= u.  The result of a tile is already
+// the operand of its Gram: accumulator e of the lane is Q[g + 4 e][r16], which
+// is A[r16][g] and B[g][r16] of the product over the rows g + 4 e.
+// Bound by MFMA issue and memory together (order 120, 331776 rows: 163 us of
+// MFMA for both products, 148 us to read Y and write Q at 4.3 TB/s).
+// Measured: order 50, 10000 rows 13.8 us for both products, against 16.5 + 11.7
+// us with 256-row tiles and a Gram launch of its own; without the Gram 8.8;
+// order 120, 331776 rows 167 us without the Gram (183 with eight waves of 32 rows).
+// From order 97 on the 28 or 36 Gram blocks of a wave outgrow the 256
+// accumulation registers, and the Gram stays a launch of its own.
+constexpr int TSM_WAVES = 4, TSM_GRID = 256, TSM_GRAM_MAX = 96;
 
-__global__ void __launch_bounds__(64 * TSM_WAVES)
-ts_mul_kernel(const double *__restrict__ Y, int64_t m, int k, const double *__restrict__ R, double *__restrict__ Q) {
-  extern __shared__ double Rl[];   // TSG_K x TSM_LD
+template <int NB, bool GRAM, bool PAIRS>   // NB = ceil(k / 16); PAIRS: k even, 16-byte loads
+__global__ void __launch_bounds__(64 * TSM_WAVES, NB <= 4 ? 2 : 1)
+ts_mul_kernel(const double *__restrict__ Y, int64_t m, int k, const double *__restrict__ R, double *__restrict__ Q,
+              double *__restrict__ part) {
+  constexpr int K = 16 * NB, LD = K + 4, BLOCKS = NB * (NB + 1) / 2;
+  extern __shared__ __attribute__((aligned(16))) double Rl[];   // K x LD, then the waves' Gram sums
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int g = lane >> 4, r16 = lane & 15;
-  for (int idx = t; idx < TSG_K * TSG_K; idx += 64 * TSM_WAVES) {
-    const int r = idx / TSG_K, c = idx % TSG_K;
-    Rl[r * TSM_LD + c] = (r < k && c < k) ? R[r * k + c] : 0.0;
+  for (int idx = t; idx < K * K; idx += 64 * TSM_WAVES) {
+    const int r = idx / K, c = idx % K;
+    Rl[r * LD + c] = (r < k && c < k) ? R[r * k + c] : 0.0;
   }
   __syncthreads();
-  const int nu = (k + 15) / 16;   // K chunks = column blocks
-  const int64_t ntiles = (m + TSM_ROWS - 1) / TSM_ROWS;
-  for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const int64_t rbase = tile * TSM_ROWS + 32 * wave;
-    int64_t rows[2];
-    bool rok[2];
+  const int64_t ntiles = (m + 15) / 16, step = int64_t(gridDim.x) * TSM_WAVES;
+  constexpr int AHEAD = NB < 4 ? NB : 4;   // chunks in registers: chunk u in slot u % AHEAD
+  double a[AHEAD][4];
+  auto load = [&](int64_t tile, auto chunk) {
+    constexpr int u = decltype(chunk)::value, s = u % AHEAD;
+    const int64_t row = tile * 16 + r16;
+    const int col = 16 * u + 4 * g;
+    const double *p = Y + row * k + col;
+    if constexpr (PAIRS) {
+      const double2 z = make_double2(0.0, 0.0);
+      const double2 x = row < m && col < k ? *reinterpret_cast<const double2 *>(p) : z;
+      const double2 y = row < m && col + 2 < k ? *reinterpret_cast<const double2 *>(p + 2) : z;
+      a[s][0] = x.x;
+      a[s][1] = x.y;
+      a[s][2] = y.x;
+      a[s][3] = y.y;
+    } else {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      rows[h] = rbase + 16 * h + r16;
-      rok[h] = rows[h] < m;
+      for (int e = 0; e < 4; ++e) a[s][e] = row < m && col + e < k ? p[e] : 0.0;
     }
-    auto load = [&](int u, double (&a)[2][4]) {
+  };
+  auto chunks = [](auto f) {
+    [&]<int... U>(std::integer_sequence<int, U...>) { (f(std::integral_constant<int, U>{}), ...); }
+    (std::make_integer_sequence<int, NB>{});
+  };
+  tsg_v4d gram[GRAM ? BLOCKS : 1];
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+  for (int q = 0; q < (GRAM ? BLOCKS : 1); ++q) gram[q] = tsg_v4d{0.0, 0.0, 0.0, 0.0};
+  int64_t tile = int64_t(blockIdx.x) * TSM_WAVES + wave;
+  if (tile < ntiles)
+    chunks([&](auto u) {
+      if constexpr (decltype(u)::value < AHEAD) load(tile, u);
+    });
+  for (; tile < ntiles; tile += step) {
+    tsg_v4d acc[NB];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int col = 16 * u + 4 * g + e;
-          a[h][e] = (rok[h] && col < k) ? Y[rows[h] * k + col] : 0.0;
-        }
-    };
-    tsg_v4d acc[2][8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc[h][j] = tsg_v4d{0.0, 0.0, 0.0, 0.0};
-    double a[2][4], an[2][4];
-    load(0, a);
-    for (int u = 0; u < nu; ++u) {
-      if (u + 1 < nu) load(u + 1, an);
+    for (int j = 0; j < NB; ++j) acc[j] = tsg_v4d{0.0, 0.0, 0.0, 0.0};
+    chunks([&](auto chunk) {
+      constexpr int u = decltype(chunk)::value;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const double *brow = Rl + (16 * u + 4 * g + e) * TSM_LD + r16;
+        const double *brow = Rl + (16 * u + 4 * g + e) * LD + r16;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (j >= u && j < nu) {
-            const double b = brow[16 * j];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) acc[h][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[h][e], b, acc[h][j], 0, 0, 0);
-          }
+        for (int j = u; j < NB; ++j) acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u % AHEAD][e], brow[16 * j], acc[j], 0, 0, 0);
       }
+      // the freed slot's next chunk, of this tile or the next one
+      if constexpr (u + AHEAD < NB) load(tile, std::integral_constant<int, u + AHEAD>{});
+      else if (tile + step < ntiles) load(tile + step, std::integral_constant<int, u % AHEAD>{});
+      __builtin_amdgcn_sched_barrier(0);   // else the reads of R of every chunk are hoisted and spill
+    });
 #pragma unroll
-      for (int h = 0; h < 2; ++h)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) a[h][e] = an[h][e];
+      for (int e = 0; e < 4; ++e) {
+        const int64_t row = tile * 16 + g + 4 * e;
+        const int col = 16 * j + r16;
+        if (row < m && col < k) Q[row * k + col] = acc[j][e];
+      }
+    if constexpr (GRAM) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0, q = 0; i < NB; ++i)
+#pragma unroll
+          for (int j = i; j < NB; ++j, ++q)
+            gram[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(acc[i][e], acc[j][e], gram[q], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if constexpr (GRAM) {
+    // the waves' sums, added in the order 3, 2, 1, 0; LDS element (q, e, lane)
+    for (int w = TSM_WAVES - 1; w >= 0; --w) {
+      __syncthreads();   // R no longer read; the wave before is done
+      if (wave != w) continue;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+      for (int i = 0, q = 0; i < NB; ++i)
 #pragma unroll
-      for (int j = 0; j < 8; ++j)
+        for (int j = i; j < NB; ++j, ++q)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int64_t row = rbase + 16 * h + g + 4 * e;
-          const int col = 16 * j + r16;
-          if (row < m && col < k) Q[row * k + col] = acc[h][j][e];
-        }
+          for (int e = 0; e < 4; ++e) {
+            double *sum = Rl + (4 * q + e) * 64 + lane;
+            const double v = w == TSM_WAVES - 1 ? gram[q][e] : *sum + gram[q][e];
+            if (w > 0) {
+              *sum = v;
+            } else {
+              const int row = 16 * i + g + 4 * e, col = 16 * j + r16;
+              double *out = part + size_t(blockIdx.x) * K * K;
+              out[row * K + col] = v;
+              out[col * K + row] = v;
+            }
+          }
+    }
   }
 }
 
-void launch_ts_mul(const double *Y, int64_t m, int k, const double *R, double *Q, hipStream_t st) {
-  TRG_REQUIRE(k >= 1 && k <= TSG_K, "ts_mul: k out of range");
-  const size_t lds = size_t(TSG_K) * TSM_LD * 8;
-  static bool attr = false;
-  if (!attr) {
-    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&ts_mul_kernel),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-    attr = true;
+int ts_mul_slabs(int64_t m) {
+  const int64_t wg = (m + 16 * TSM_WAVES - 1) / (16 * TSM_WAVES);
+  return int(wg < TSM_GRID ? wg : TSM_GRID);
+}
+
+// part: nullptr, or ts_mul_slabs(m) slabs of (16 ceil(k / 16))^2 for Q^T Q
+void launch_ts_mul(const double *Y, int64_t m, int k, const double *R, double *Q, double *part, hipStream_t st) {
+  TRG_REQUIRE(k >= 1 && k <= TSG_K && m >= 1 && (!part || k <= TSM_GRAM_MAX), "ts_mul: k out of range");
+  auto launch = [&](auto blocks) {
+    constexpr int NB = decltype(blocks)::value;
+    constexpr int lds = 16 * NB * (16 * NB + 4) * 8;
+    static_assert(lds >= NB * (NB + 1) / 2 * 256 * 8, "the Gram sums fit where R was");
+    auto go = [&](auto kernel) {
+      TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      hipLaunchKernelGGL(kernel, dim3(uint32_t(ts_mul_slabs(m))), dim3(64 * TSM_WAVES), lds, st, Y, m, k, R, Q, part);
+      TRG_HIP_CHECK(hipGetLastError());
+    };
+    constexpr bool G = 16 * NB <= TSM_GRAM_MAX;
+    if (k % 2 == 0) {
+      if (G && part) go(&ts_mul_kernel<NB, G, true>);
+      else go(&ts_mul_kernel<NB, false, true>);
+    } else {
+      if (G && part) go(&ts_mul_kernel<NB, G, false>);
+      else go(&ts_mul_kernel<NB, false, false>);
+    }
+  };
+  switch ((k + 15) / 16) {
+    case 1: launch(std::integral_constant<int, 1>{}); break;
+    case 2: launch(std::integral_constant<int, 2>{}); break;
+    case 3: launch(std::integral_constant<int, 3>{}); break;
+    case 4: launch(std::integral_constant<int, 4>{}); break;
+    case 5: launch(std::integral_constant<int, 5>{}); break;
+    case 6: launch(std::integral_constant<int, 6>{}); break;
+    case 7: launch(std::integral_constant<int, 7>{}); break;
+    default: launch(std::integral_constant<int, 8>{}); break;
   }
-  // one workgroup per CU (the LDS copy of R), each walking its row tiles
-  const int64_t ntiles = (m + TSM_ROWS - 1) / TSM_ROWS;
-  const uint32_t grid = uint32_t(ntiles < 256 ? ntiles : 256);
-  hipLaunchKernelGGL(ts_mul_kernel, dim3(grid), dim3(64 * TSM_WAVES), lds, st, Y, m, k, R, Q);
-  TRG_HIP_CHECK(hipGetLastError());
 }
 
 // One isometry applied to a leg pair on FP64 MFMA:
@@ -936,9 +1008,15 @@ void cholqr3(trg_ctx &c, const double *Y, int64_t m, int k, double *Q, double *R
   // about 512 workgroups (two per CU), each a whole number of 32-row chunks
   const int64_t tsg_rows = std::max<int64_t>(TSG_ROWS, ((m + 511) / 512 + TSG_ROWS - 1) / TSG_ROWS * TSG_ROWS);
   const int64_t tsg_wg = (m + tsg_rows - 1) / tsg_rows;
-  double *part = tsg ? c.wsp<double>("qrP" + tag, size_t(tsg_wg) * TSG_K * TSG_K * 8) : nullptr;
+  const int slabs = ts_mul_slabs(m);
+  const int64_t K16 = int64_t(round_up(k, 16));
+  double *part = tsg ? c.wsp<double>("qrP" + tag, size_t(std::max<int64_t>(tsg_wg * TSG_K * TSG_K, slabs * K16 * K16)) * 8)
+                     : nullptr;
   for (int pass = 0; pass < 3; ++pass) {
-    if (tsg) {
+    const bool fused = k <= TSM_GRAM_MAX;
+    if (fused && pass > 0) {   // the pass before has left the Gram of its result
+      reduce_splits(part, slabs, k, k, K16, K16 * K16, Cg, k, c.st);
+    } else if (tsg) {
       hipLaunchKernelGGL(ts_gram_kernel, dim3(uint32_t(tsg_wg)), dim3(256), 0, c.st, src, m, k, tsg_rows, part);
       TRG_HIP_CHECK(hipGetLastError());
       reduce_splits(part, int(tsg_wg), k, k, TSG_K, int64_t(TSG_K) * TSG_K, Cg, k, c.st);
@@ -949,7 +1027,7 @@ void cholqr3(trg_ctx &c, const double *Y, int64_t m, int k, double *Q, double *R
     launch_chol_inv(Cg, k, shift, R, Ri, c.errp(), c.st);
     double *dst = pass == 2 ? Q : (pass == 0 ? bufA : bufB);
     if (tsg) {
-      launch_ts_mul(src, m, k, Ri, dst, c.st);
+      launch_ts_mul(src, m, k, Ri, dst, fused && pass < 2 ? part : nullptr, c.st);
     } else {
       einsum2(c, src, vk, Ri, contiguous({{"k", k}, {"c", k}}), dst, {"i", "c"}, TRG_FP64, "qm" + tag);
     }
