@@ -1378,7 +1378,7 @@ void atrg_indicator_traces(trg_ctx &c, int axis, double *M, double *out) {
   lg.push_back({"l", c.r});
   einsum2(c, static_cast<const double *>(c.G.ptr), contiguous(lg), static_cast<const double *>(c.H.ptr),
           contiguous(lh), M, {"x", "xp"}, TRG_FP64, "ind");
-  indicator_reduce(M, c.dims[axis], out, c.st);
+  indicator_reduce(M, c.dims[axis], out, c.st, c.host_result, c.errp());
 }
 
 void atrg_step_impl(trg_ctx &c, int mu, int dcut) {

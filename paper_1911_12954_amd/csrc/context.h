@@ -110,6 +110,7 @@ struct trg_ctx {
   Buffer T, Tn, S[2], Sn[2];
   Buffer dev_scalars;  // doubles: [0] c [1] 1/c [2] ln c [3] acc [4..6] traces [7] c0
   Buffer dev_err;      // int
+  trg::HostResult *host_result = nullptr;   // a slot of the pinned pool, or none
   Buffer dev_rec;      // per-step device records
   int rec_cap = 0;
   std::vector<trg_step_rec> host_rec;  // host-known parts
@@ -205,7 +206,7 @@ double atrg_trace(trg_ctx &c);
 double atrg_impurity_trace(trg_ctx &c, int j);
 // {Tr M, Tr(M M)} into out for M[x][x'] = sum_{l, other legs traced} G[.., x, .., l] H[l, .., x', ..]
 void atrg_indicator_traces(trg_ctx &c, int axis, double *M, double *out);
-void sync_check(trg_ctx &c);
+void sync_check(trg_ctx &c, const HostResult *host = nullptr);
 double *rec_d(trg_ctx &c, int n);
 int *rec_i(trg_ctx &c, int n);
 void ensure_records(trg_ctx &c, int need);

@@ -753,11 +753,50 @@ int guarded(trg_ctx *c, F &&f) {
   }
 }
 
-// wait for the stream and check the device error flag
-void sync_check(trg_ctx &c) {
+// Pinned result slots of the contexts: 64 in one allocation, given back with the
+// context; a context beyond them has none and copies its results instead.
+namespace {
+constexpr int HOST_SLOTS = 64;
+constexpr size_t HOST_SLOT_BYTES = 64;
+static_assert(sizeof(HostResult) <= HOST_SLOT_BYTES, "a slot holds one result");
+std::mutex g_slots_mu;
+char *g_slots = nullptr;
+bool g_slots_tried = false;
+uint64_t g_slots_used = 0;
+
+HostResult *take_host_slot() {
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  if (!g_slots_tried) {
+    g_slots_tried = true;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+      g_slots = static_cast<char *>(p);
+    else
+      (void)hipGetLastError();
+  }
+  if (!g_slots) return nullptr;
+  for (int i = 0; i < HOST_SLOTS; ++i)
+    if (!(g_slots_used >> i & 1)) {
+      g_slots_used |= uint64_t(1) << i;
+      return reinterpret_cast<HostResult *>(g_slots + i * HOST_SLOT_BYTES);
+    }
+  return nullptr;
+}
+
+void give_host_slot(HostResult *r) {
+  if (!r) return;
+  std::lock_guard<std::mutex> lock(g_slots_mu);
+  g_slots_used &= ~(uint64_t(1) << ((reinterpret_cast<char *>(r) - g_slots) / HOST_SLOT_BYTES));
+}
+}  // namespace
+
+// wait for the stream and check the device error flag (host: where the last
+// kernel has left it)
+void sync_check(trg_ctx &c, const HostResult *host) {
   TRG_HIP_CHECK(hipStreamSynchronize(c.st));
   int e = 0;
-  TRG_HIP_CHECK(hipMemcpy(&e, c.errp(), sizeof(int), hipMemcpyDeviceToHost));
+  if (host) e = *const_cast<const volatile int *>(&host->err);
+  else TRG_HIP_CHECK(hipMemcpy(&e, c.errp(), sizeof(int), hipMemcpyDeviceToHost));
   if (e) {
     c.poisoned = true;
     throw Error(TRG_ENUMERIC, (e & 1) ? "normalisation produced a zero or non-finite norm"
@@ -793,6 +832,7 @@ void init_common(trg_ctx &c) {
   fill_zero(c.dev_scalars.ptr, 16 * 8, c.st);
   fill_zero(c.dev_err.ptr, 64, c.st);
   ensure_records(c, 64);
+  c.host_result = take_host_slot();
 }
 
 void validate_cfg(const trg_config *cfg, int d) {
@@ -1100,10 +1140,16 @@ static int traces(trg_ctx *ctx, double out[4]) {
   // out[0] = acc, out[1] = Tr T, out[2] = Tr S_E, out[3] = Tr S_M
   const double *X[3] = {static_cast<const double *>(ctx->T.ptr), nullptr, nullptr};
   for (int j = 0; j < ctx->nimp; ++j) X[1 + j] = static_cast<const double *>(ctx->S[j].ptr);
-  periodic_traces(X, 1 + ctx->nimp, ctx->dims, ctx->d, ctx->scal() + 4, ctx->st);
-  sync_check(*ctx);
+  HostResult *r = ctx->host_result;
+  periodic_traces(X, 1 + ctx->nimp, ctx->dims, ctx->d, ctx->scal() + 4, ctx->st, r, ctx->scal() + 3, ctx->errp());
+  sync_check(*ctx, r);
   double h[4] = {0, 0, 0, 0};
-  TRG_HIP_CHECK(hipMemcpy(h, ctx->scal() + 3, 4 * 8, hipMemcpyDeviceToHost));
+  if (r) {
+    h[0] = r->acc;
+    for (int j = 0; j <= ctx->nimp; ++j) h[1 + j] = r->trace[j];
+  } else {
+    TRG_HIP_CHECK(hipMemcpy(h, ctx->scal() + 3, 4 * 8, hipMemcpyDeviceToHost));
+  }
   out[0] = h[0];
   out[1] = h[1];
   out[2] = out[3] = NAN;
@@ -1127,6 +1173,17 @@ int trg_free_energy(trg_ctx *ctx, double *lnz) {
   });
 }
 
+// wait for the two traces of the indicator
+static void read_indicator(trg_ctx &c, const double *out, double t[2]) {
+  sync_check(c, c.host_result);
+  if (c.host_result) {
+    t[0] = c.host_result->indicator[0];
+    t[1] = c.host_result->indicator[1];
+  } else {
+    TRG_HIP_CHECK(hipMemcpy(t, out, 2 * 8, hipMemcpyDeviceToHost));
+  }
+}
+
 int trg_indicator_x(trg_ctx *ctx, int axis, double *X) {
   if (!ctx || !X) return fail(ctx, TRG_EINVAL, "NULL argument");
   return guarded(ctx, [&]() -> int {
@@ -1137,10 +1194,10 @@ int trg_indicator_x(trg_ctx *ctx, int axis, double *X) {
     if (ctx->cfg.method == TRG_ATRG)
       atrg_indicator_traces(*ctx, axis, M, out);
     else
-      indicator_traces(static_cast<const double *>(ctx->T.ptr), ctx->dims, ctx->d, axis, M, out, ctx->st);
-    sync_check(*ctx);
+      indicator_traces(static_cast<const double *>(ctx->T.ptr), ctx->dims, ctx->d, axis, M, out, ctx->st,
+                       ctx->host_result, ctx->errp());
     double t[2];
-    TRG_HIP_CHECK(hipMemcpy(t, out, 2 * 8, hipMemcpyDeviceToHost));
+    read_indicator(*ctx, out, t);
     if (!(t[1] > 0.0) || !std::isfinite(t[0])) throw Error(TRG_ENUMERIC, "indicator: vanishing two-site trace");
     *X = t[0] * t[0] / t[1];
     return TRG_OK;
@@ -1158,10 +1215,10 @@ int trg_indicator_x_noalloc(trg_ctx *ctx, int axis, double *X) {
     double *M = reinterpret_cast<double *>(base);
     double *out = reinterpret_cast<double *>(base + NOALLOC_M_BYTES);
     // both kernels overwrite every scratch entry they later read
-    indicator_traces(static_cast<const double *>(ctx->T.ptr), ctx->dims, ctx->d, axis, M, out, ctx->st);
-    sync_check(*ctx);
+    indicator_traces(static_cast<const double *>(ctx->T.ptr), ctx->dims, ctx->d, axis, M, out, ctx->st,
+                     ctx->host_result, ctx->errp());
     double t[2];
-    TRG_HIP_CHECK(hipMemcpy(t, out, 2 * 8, hipMemcpyDeviceToHost));
+    read_indicator(*ctx, out, t);
     if (!(t[1] > 0.0) || !std::isfinite(t[0])) throw Error(TRG_ENUMERIC, "indicator: vanishing two-site trace");
     *X = t[0] * t[0] / t[1];
     return TRG_OK;
@@ -1613,6 +1670,7 @@ void trg_free(trg_ctx *ctx) {
     rel(ctx->spec[a]);
   }
   ctx->pool.reset();
+  give_host_slot(ctx->host_result);
   delete ctx;
 }
 

@@ -132,14 +132,23 @@ void norm_and_accumulate_batch(const NormBatch &b, int nb, int64_t n, double *pa
 void scale_by_inverse_batch(double *const *xs, const double *const *scals, int nb, int64_t n, double factor,
                             hipStream_t st);
 
+// What a call that returns a few numbers reads back, in pinned host memory: its
+// last kernel writes here too (nullptr: only to the device)
+struct HostResult {
+  double acc, trace[3], indicator[2];
+  int err;
+};
+
 // traces: out[j] = sum_{x_nu} X_j[x, x, y, y, ...] for up to 3 tensors
 // {Tr M, Tr(M M)} into out[0..1] for M[a][a'] = T with the legs of `axis`
 // open and every other axis' leg pair traced (M: dims[axis]^2 workspace)
-void indicator_traces(const double *T, const int *dims, int d, int axis, double *M, double *out, hipStream_t st);
+void indicator_traces(const double *T, const int *dims, int d, int axis, double *M, double *out, hipStream_t st,
+                      HostResult *host = nullptr, const int *err = nullptr);
 // {Tr M, Tr(M M)} of an n x n matrix already formed
-void indicator_reduce(const double *M, int n, double *out, hipStream_t st);
-void periodic_traces(const double *const *X, int count, const int *dims, int d, double *out,
-                     hipStream_t st);
+void indicator_reduce(const double *M, int n, double *out, hipStream_t st, HostResult *host = nullptr,
+                      const int *err = nullptr);
+void periodic_traces(const double *const *X, int count, const int *dims, int d, double *out, hipStream_t st,
+                     HostResult *host = nullptr, const double *acc = nullptr, const int *err = nullptr);
 
 // initial Ising tensors (closed form) into T, SE, SM (each may be null)
 void ising_init(double *T, double *SE, double *SM, int d, double beta, double h, hipStream_t st);

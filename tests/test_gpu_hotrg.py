@@ -108,6 +108,33 @@ def test_isometry_maps_in_every_precision(d, dims, mu, dcut, seed, precision, to
     assert np.max(np.abs(got - ref)) < tol * np.max(np.abs(ref))
 
 
+def test_observables_beyond_the_pinned_result_slots():
+    """More contexts than there are pinned result slots (64): those beyond copy
+    their results from the device, to the same bits, and a slot that was given
+    back serves the next context."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_ising
+    announce("result slots")
+
+    def observables(c):
+        return (c.free_energy(), c.impure_energy(), c.impure_magnetization(),
+                [c.indicator_x(a) for a in range(2)], c.indicator_x_noalloc(1))
+
+    ctxs = [trg_init_ising(0.42, 0.01, 2, dcut=6, impure=("E", "M")) for _ in range(67)]
+    for c in ctxs:
+        for n in range(3):
+            c.hotrg_step(n % 2, 6)
+    ref = observables(ctxs[0])
+    assert all(observables(c) == ref for c in ctxs)
+    for c in ctxs:
+        c.close()
+    again = trg_init_ising(0.42, 0.01, 2, dcut=6, impure=("E", "M"))
+    for n in range(3):
+        again.hotrg_step(n % 2, 6)
+    assert observables(again) == ref
+    again.close()
+
+
 @pytest.mark.parametrize("budget", [14_000_000, 30_000_000])
 def test_sliced_join_is_bitwise_equal(budget):
     """A small workspace forces the join into x0/x2 slices (14 MB: one value
