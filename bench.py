@@ -715,7 +715,7 @@ def main():
             "dtype": prec, "data": "synthetic (closed-form 4D Ising tensor, beta=%.4f, h=0)" % a.beta,
             "config": {"workload": "4D Ising ATRG, Dcut=%d, p=4Dcut, q=2Dcut, contraction %s" % (D, prec),
                        "lnZ_per_site_after_run": lnz},
-            "roofline": {"bound": "mfma", "kernel": "gemm_nt_kernel (ATRG contraction, M=D^4 K=D^2 N=D^3)",
+            "roofline": {"bound": "mfma", "kernel": "gemm_pipe_kernel (ATRG contraction, M=D^4 K=D^2 N=D^3)",
                          "achieved": ach, "peak": PEAK_TFLOPS[prec], "unit": "TFLOP/s",
                          "frac": (ach / PEAK_TFLOPS[prec]) if ach else None, "traffic": None,
                          "launches": nl, "gemm_ms_per_step": ms / a.steps,
@@ -759,7 +759,8 @@ def main():
                    "steps_in_run": head["steps_total"]},
         "roofline": {
             "bound": "mfma",
-            "kernel": "gemm_nt_kernel (join, D^15 block-spin contraction)",
+            "kernel": "%s (join, D^15 block-spin contraction)" % (
+                "gemm_split_kernel" if a.precision in SPLIT_PRODUCTS else "gemm_pipe_kernel"),
             "achieved": achieved,
             "peak": peak,
             "unit": "TFLOP/s",

@@ -656,6 +656,8 @@ void launch_ts_mul(const double *Y, int64_t m, int k, const double *R, double *Q
 // (g, r16) loads rows 16 h + r16 (consecutive source addresses when the
 // innermost kept leg has source stride 1) at K index 4 s + g, and the P
 // fragment comes through the cache (P is small).
+// Bound by memory (24^7 source elements at Dcut 24), with four k-steps of loads
+// in flight per wave: 8.7 ms for 36.7 GB (4.2 TB/s), 11.5 with none ahead.
 struct PairSpec {
   int nk;
   int64_t size[7], sstr[7], ostr[7];
@@ -663,8 +665,9 @@ struct PairSpec {
   int dn, nd;
   int64_t sa, sb, ostrB;
 };
-constexpr int PC_WAVES = 4;
+constexpr int PC_WAVES = 4, PC_AHEAD = 4;
 
+template <int NJ>   // ceil(nd / 16)
 __global__ void __launch_bounds__(64 * PC_WAVES)
 pair_contract_kernel(const double *__restrict__ src, const double *__restrict__ P, double *__restrict__ out,
                      PairSpec ps) {
@@ -673,7 +676,6 @@ pair_contract_kernel(const double *__restrict__ src, const double *__restrict__ 
   const int64_t m0 = (int64_t(blockIdx.x) * PC_WAVES + wave) * 32;
   if (m0 >= ps.M) return;
   const int K = ps.dn * ps.dn;
-  const int nj = (ps.nd + 15) / 16;
   // source offsets of this lane's two A rows
   int64_t soff[2];
   bool rok[2];
@@ -689,31 +691,53 @@ pair_contract_kernel(const double *__restrict__ src, const double *__restrict__ 
     }
     soff[h] = rok[h] ? off : 0;
   }
-  tsg_v4d acc[2][4];
+  tsg_v4d acc[2][NJ];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[h][j] = tsg_v4d{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < NJ; ++j) acc[h][j] = tsg_v4d{0.0, 0.0, 0.0, 0.0};
   int a = g / ps.dn, b = g - (g / ps.dn) * ps.dn;   // (a, b) of K index k = 4 s + g
-  for (int k = g; k - g < K; k += 4) {
-    const bool kok = k < K;
-    const int64_t koff = int64_t(a) * ps.sa + int64_t(b) * ps.sb;
-    double av[2];
+  // PC_AHEAD k-steps are in flight while as many are multiplied
+  double av[2][PC_AHEAD][2], bv[2][PC_AHEAD][NJ];
+  auto fetch = [&](int k0, auto buf) {
+    constexpr int q = decltype(buf)::value;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) av[h] = (rok[h] && kok) ? src[soff[h] + koff] : 0.0;
+    for (int u = 0; u < PC_AHEAD; ++u) {
+      const int k = k0 + 4 * u + g;
+      const bool kok = k < K;
+      const int64_t koff = int64_t(a) * ps.sa + int64_t(b) * ps.sb;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (j < nj) {
+      for (int h = 0; h < 2; ++h) av[q][u][h] = (rok[h] && kok) ? src[soff[h] + koff] : 0.0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
         const int n = 16 * j + r16;
-        const double bv = (kok && n < ps.nd) ? P[int64_t(k) * ps.nd + n] : 0.0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) acc[h][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[h], bv, acc[h][j], 0, 0, 0);
+        bv[q][u][j] = (kok && n < ps.nd) ? P[int64_t(k) * ps.nd + n] : 0.0;
       }
-    b += 4;
-    while (b >= ps.dn) {
-      b -= ps.dn;
-      ++a;
+      b += 4;
+      while (b >= ps.dn) {
+        b -= ps.dn;
+        ++a;
+      }
     }
+  };
+  auto multiply = [&](auto buf) {
+    constexpr int q = decltype(buf)::value;
+#pragma unroll
+    for (int u = 0; u < PC_AHEAD; ++u)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          acc[h][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[q][u][h], bv[q][u][j], acc[h][j], 0, 0, 0);
+  };
+  constexpr auto B0 = std::integral_constant<int, 0>{};
+  constexpr auto B1 = std::integral_constant<int, 1>{};
+  fetch(0, B0);
+  for (int k = 0; k < K; k += 8 * PC_AHEAD) {
+    fetch(k + 4 * PC_AHEAD, B1);
+    multiply(B0);
+    fetch(k + 8 * PC_AHEAD, B0);
+    multiply(B1);
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -728,9 +752,9 @@ pair_contract_kernel(const double *__restrict__ src, const double *__restrict__ 
         m = q;
       }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         const int n = 16 * j + r16;
-        if (j < nj && n < ps.nd) out[off + int64_t(n) * ps.ostrB] = acc[h][j][e];
+        if (n < ps.nd) out[off + int64_t(n) * ps.ostrB] = acc[h][j][e];
       }
     }
 }
@@ -1278,7 +1302,15 @@ void pair_contract(trg_ctx &c, const double *src, const View &inv, const std::st
   TRG_REQUIRE(int64_t(ps.nk) + 2 == int64_t(inv.size()) && ps.nk >= 1, "pair_contract: stray legs");
   const int64_t blocks = (ps.M + 32 * PC_WAVES - 1) / (32 * PC_WAVES);
   TRG_REQUIRE(blocks < (int64_t(1) << 31), "pair_contract: too many rows");
-  hipLaunchKernelGGL(pair_contract_kernel, dim3(uint32_t(blocks)), dim3(64 * PC_WAVES), 0, c.st, src, P, out, ps);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(uint32_t(blocks)), dim3(64 * PC_WAVES), 0, c.st, src, P, out, ps);
+  };
+  switch ((ps.nd + 15) / 16) {
+    case 1: launch(&pair_contract_kernel<1>); break;
+    case 2: launch(&pair_contract_kernel<2>); break;
+    case 3: launch(&pair_contract_kernel<3>); break;
+    default: launch(&pair_contract_kernel<4>); break;
+  }
   TRG_HIP_CHECK(hipGetLastError());
 }
 

@@ -140,6 +140,24 @@ def test_swap_spectrum_over_product_shapes(D, d, mu, cols):
     assert err < 1e-8
 
 
+@pytest.mark.parametrize("D,dcut", [(3, 9), (4, 16), (5, 25), (6, 36), (7, 49), (8, 64)])
+def test_pair_contraction_widths(D, dcut):
+    """The isometries of a 3D step keep every pair index (9 to 64 of them, one
+    to four column blocks), so the norm of the new tensor depends on no choice
+    of basis: ln c to FP64 rounding of a few thousand-term sums."""
+    need_gpu()
+    from paper_1911_12954_amd import trg_init_factors
+    announce("atrg pair contraction", D, dcut)
+    rng = np.random.default_rng(D)
+    G, H = rng.standard_normal((D, D, D, 5)), rng.standard_normal((5, D, D, D))
+    ctx = trg_init_factors(G, H, dcut=dcut, rsvd_p=8, rsvd_q=2, seed=9)
+    ctx.atrg_step(1, dcut)
+    got = ctx.step_log()[-1].ln_c
+    ctx.close()
+    c = atrg.atrg_step(atrg.canonical(G, H, dcut), 1, dcut, 8, 2, 1, 9)[2]
+    assert abs(got - math.log(c)) < 1e-10 * max(1.0, abs(math.log(c)))
+
+
 # ------------------------------------------------------------ impure tensors ---
 def _gpu_impure(beta, h, d, dcut, L, **cfg):
     from paper_1911_12954_amd import trg_init_ising
