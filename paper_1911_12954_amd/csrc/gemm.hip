@@ -103,6 +103,38 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
   tn = in_group / gm;
 }
 
+// Tiles of the split-BF16 kernels: one workgroup per CU, so 256 in a round, laid
+// out as 16 x 16 tiles of which each XCD takes 8 x 4.  Its L2 serves the 12
+// panels of those as before, and the 8 XCDs together stream 32 panels instead
+// of 96, so that most of what one XCD misses another has just brought into the
+// memory-side cache.  Bijective for any grid: blocks of 256 workgroups are
+// consecutive in the raster (the last, smaller one cut evenly among the XCDs),
+// which walks row groups of 16 in strips of 4 columns, each strip's upper 8
+// rows first.
+// These kernels run at the power limit, where traffic from memory costs clock:
+// BF16x6 30080 x 100096 x 100000 (a full slice at Dcut 10) 179.5 -> 205.6
+// TFLOP/s, 10112 x 10112 x 100000 178 -> 188; BF16x3 13312 x 13312 x 59072 469 ->
+// 490, against each XCD walking its own eighth of the tiles in groups of 4 or 8 rows.
+__device__ inline void tile_coords_shared(uint32_t wg, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
+  constexpr uint32_t ROUND = 256, GM = 16, SW = 4, HALF = 8;
+  const uint32_t total = tiles_m * tiles_n, base = wg / ROUND * ROUND;
+  const uint32_t n = total - base < ROUND ? total - base : ROUND;
+  const uint32_t xcd = wg % NUM_XCD, idx = (wg - base) / NUM_XCD;
+  const uint32_t per = n / NUM_XCD, rem = n % NUM_XCD;
+  const uint32_t w = base + xcd * per + (xcd < rem ? xcd : rem) + idx;
+  const uint32_t first_m = w / (GM * tiles_n) * GM;
+  const uint32_t gm = tiles_m - first_m < GM ? tiles_m - first_m : GM;
+  const uint32_t in_group = w - first_m * tiles_n;
+  const uint32_t strip = in_group / (gm * SW), i = in_group % (gm * SW);
+  const uint32_t sw = tiles_n - strip * SW < SW ? tiles_n - strip * SW : SW;
+  const bool split = gm == GM;
+  const uint32_t rows = split ? HALF : gm;
+  const uint32_t half = split ? i / (HALF * sw) : 0;
+  const uint32_t j = i - half * HALF * sw;
+  tm = first_m + half * HALF + j % rows;
+  tn = strip * SW + j / rows;
+}
+
 // ------------------------------------------------ pipelined FP64 / FP32 join ---
 // LDS layout of the pipelined kernel: rows of 128 bytes (8 chunks of 16),
 // two rows per 256-byte line; chunk c of row r sits at chunk c ^ pipe_swz(r).
@@ -480,7 +512,7 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   const int wm = wave / WN, wn = wave % WN, g = lane >> 4, r16 = lane & 15;
   uint32_t tm, tn;
   // PL 3: groups of four tile rows (178 TFLOP/s against 173 with eight)
-  tile_coords<PL == 3 ? 4 : GROUP_M>(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  tile_coords_shared(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
   A += uint64_t(blockIdx.z) * batch_a;
   Bt += uint64_t(blockIdx.z) * batch_b;
