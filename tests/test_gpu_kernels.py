@@ -220,6 +220,15 @@ def test_gemm_split_tile_variants(precision, M, N, K, accumulate):
     assert float(((C.double() - ref).abs() / scale).max()) < bound
 
 
+@pytest.mark.parametrize("precision,M,N", [("bf16x6", 2176, 2688), ("bf16x6", 4224, 1152), ("bf16x6", 384, 33024),
+                                           ("bf16x3", 4352, 4352), ("bf16x3", 768, 1280)])
+def test_gemm_split_tile_order_ragged(precision, M, N):
+    """Tile counts that are no multiple of the 16 rows, 4 columns and 256 tiles
+    of the shared order: every tile is written once.  Bounds as above."""
+    test_gemm_split_tile_variants(precision, M, N, 64, False)
+
+
+
 @pytest.mark.parametrize("n", [1, 2, 4, 7, 16, 33, 100, 144, 161, 200, 333, 576])
 def test_jacobi_eigh(n):
     """Orders up to 160 use cyclic Jacobi, larger ones Householder
