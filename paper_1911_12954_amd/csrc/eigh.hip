@@ -1072,14 +1072,18 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
   for (int i = t; i < n; i += TD_FIN) {
     dd[i] = T.dd[i];
     ee[i] = T.ee[i];
-    lam[i] = T.lam[i];
+    const double v = T.lam[i];
+    lam[i] = v == v ? v : INFINITY;
   }
   __syncthreads();
-  // ---- sort descending (ties by slot)
+  // ---- sort descending (ties by slot).  NaN, the spectrum of a matrix that is
+  // not finite, sorts as infinity: the ranks are a permutation of the slots
+  // whatever the matrix holds, so every slot_of that is read has been written
+  // and every block bound taken from it lies inside the matrix.
   for (int slot = t; slot < n; slot += TD_FIN) {
-    const double v = lam[slot];
+    const double key = lam[slot], v = T.lam[slot];
     int rk = 0;
-    for (int u = 0; u < n; ++u) rk += (lam[u] > v) || (lam[u] == v && u < slot);
+    for (int u = 0; u < n; ++u) rk += (lam[u] > key) || (lam[u] == key && u < slot);
     w[rk] = v;
     slot_of[rk] = slot;
     wall[size_t(b) * n + rk] = v;

@@ -492,3 +492,33 @@ def test_eigh_top_parity_blocks_stay_exact():
     q = int(kk[1])
     in_b = np.abs(V[1][n0:, :q]).sum(0) > 0
     assert 0 < int(in_b.sum()) < q
+
+
+@pytest.mark.parametrize("n", [161, 300])
+@pytest.mark.parametrize("bad", ["all nan", "all inf", "one nan"])
+def test_eigh_top_matrix_that_is_not_finite(n, bad):
+    """A matrix of NaN or infinite entries between two finite ones of a batch
+    (a run that has overflowed steps on until its error flag is read): the
+    number of vectors stays within the order, they are not finite either, so
+    that the next norm shows it, and the finite matrices are solved to the
+    bounds above.  The ranks of NaN eigenvalues must not coincide, or the
+    solver would take block bounds from memory that nobody wrote."""
+    announce("eigh_top not finite", n, bad)
+    k = 20
+    A = np.stack([gram_like(n, 40, 50), gram_like(n, 40, 51), gram_like(n, 40, 52)])
+    if bad == "one nan":
+        A[1, n // 2, n // 2 + 1] = A[1, n // 2 + 1, n // 2] = np.nan
+    else:
+        A[1] = np.nan if bad == "all nan" else np.inf
+    w, V, kk = _eigh_top(A, k, 1e-10)
+    assert k <= int(kk[1]) <= n
+    assert not np.any(np.isfinite(V[1][:, : int(kk[1])]).all(0))
+    if bad != "one nan":
+        assert np.all(np.isnan(w[1]))
+    for b in (0, 2):
+        nrm = np.linalg.norm(A[b])
+        q = int(kk[b])
+        assert np.max(np.abs(w[b] - np.linalg.eigvalsh(A[b])[::-1])) < 1e-13 * nrm
+        Vk = V[b][:, :q]
+        assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
+        assert np.max(np.abs(A[b] @ Vk - Vk * w[b][:q])) < 1e-12 * nrm
