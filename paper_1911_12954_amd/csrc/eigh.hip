@@ -1369,7 +1369,9 @@ select_kernel(const double *w2, const double *V2, const int *sweeps2, int n, int
       int first = n;
       for (int i = t; i < n; i += SEL_THREADS)
         if (diag[i] >= (1.0 - SIGN_REL) * mx && i < first) first = i;
-      const int r = sel_min_index(first, shi);
+      // no coordinate qualifies when the vectors are NaN: the last one then, whose
+      // entries are as good as any, for n is past the end of V, U and col
+      const int found = sel_min_index(first, shi), r = found < n ? found : n - 1;
       // column of the remaining projector at coordinate r
       for (int i = t; i < n; i += SEL_THREADS) {
         double v = 0.0;

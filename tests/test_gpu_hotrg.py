@@ -339,3 +339,24 @@ def test_fp64_path_matches_stored_oracle_values(name):
     assert abs(E - float(c["energy"])) <= 1e-10 * abs(float(c["energy"]))
     m_ref = float(c["magnetization"])
     assert abs(M - m_ref) <= 1e-10 * abs(m_ref) + 1e-12
+
+
+@pytest.mark.parametrize("d,dcut,L", [(2, 4, 16), (2, 14, 64), (3, 4, 4)])
+def test_run_that_overflows_ends_in_a_numeric_error(d, dcut, L):
+    """cosh(800) overflows, so every tensor of the run is NaN: each step's
+    eigensolvers (Jacobi, and tridiagonal for the Gram matrices of order 196)
+    and selections still address only their own memory, the wait after the
+    last step reports the error, and a run beside it is not disturbed."""
+    need_gpu()
+    from paper_1911_12954_amd import TrgError, trg_init_ising
+    announce("overflowing run", d, dcut, L)
+    good = trg_init_ising(0.2, 0.0, d, dcut=4)
+    bad = trg_init_ising(800.0, 0.0, d, dcut=dcut)
+    with pytest.raises(TrgError) as e:
+        bad.run(L)
+    assert e.value.code == -5
+    bad.close()
+    good.run(4)
+    ref = hotrg.run(0.2, 0.0, d, 4, 4)
+    assert abs(good.free_energy() - ref.ln_z_per_site) <= 1e-10 * abs(ref.ln_z_per_site)
+    good.close()
