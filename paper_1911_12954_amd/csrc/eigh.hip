@@ -737,7 +737,8 @@ __device__ inline double top_start(int r, int i) {
 // scratch of one matrix (offsets in units of n doubles from its end of work)
 struct TdScratch {
   double *dd, *ee, *lam, *p[2], *v[2], *tau;   // diagonal, subdiagonal, eigenvalues by slot, A v and v of a column
-  int *slot_of, *s0, *e0, *kk;                 // slot of each rank, block of each slot, vectors needed
+  double *eb;                                  // subdiagonal with zeros between the blocks
+  int *s0, *e0, *kk;                           // block of each slot, vectors needed
   unsigned long long *piv;                     // row swaps of the LU, one bit per lane
   double *X;                                   // iterates of a chunk, [entry][lane]
 };
@@ -751,7 +752,7 @@ __device__ inline TdScratch td_scratch(double *scr, int n) {
   t.v[0] = scr + 5 * n;
   t.v[1] = scr + 6 * n;
   t.tau = scr + 7 * n;
-  t.slot_of = reinterpret_cast<int *>(scr + 8 * n);
+  t.eb = scr + 8 * n;
   t.s0 = reinterpret_cast<int *>(scr + 9 * n);
   t.e0 = reinterpret_cast<int *>(scr + 10 * n);
   t.kk = reinterpret_cast<int *>(scr + 11 * n);
@@ -993,7 +994,7 @@ td_values_kernel(double *workall, int n) {
   for (int i = t; i < n; i += TD_THREADS) {
     const double e = ee2[i];
     if (blockIdx.x == 0) {
-      T.ee[i] = e;                         // cleaned; read by td_vectors_kernel
+      T.eb[i] = e;   // not over T.ee, which other workgroups may still be reading
       T.s0[i] = s0s[i];
       T.e0[i] = e0s[i];
     }
@@ -1071,7 +1072,7 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
   const double eps = 2.220446049250313e-16;
   for (int i = t; i < n; i += TD_FIN) {
     dd[i] = T.dd[i];
-    ee[i] = T.ee[i];
+    ee[i] = T.eb[i];
     const double v = T.lam[i];
     lam[i] = v == v ? v : INFINITY;
   }
