@@ -1403,10 +1403,27 @@ select_kernel(const double *w2, const double *V2, const int *sweeps2, int n, int
 // Jacobi up to order JACOBI_MAX_N (accurate, and cheap while the matrix is
 // small), tridiagonalisation + QL above.
 
+namespace {
+// The solvers' matrices are grid.y (a workgroup index of a matrix is grid.x),
+// which ends at 65535: larger batches go in pieces, f(first matrix, count).
+constexpr int MAX_GRID_Y = 65535;
+template <class F>
+void each_piece(int batch, F &&f) {
+  for (int b0 = 0; b0 < batch;) {
+    const int nb = std::min(batch - b0, MAX_GRID_Y);
+    f(size_t(b0), nb);
+    b0 += nb;
+  }
+}
+}  // namespace
+
 void eigh_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, hipStream_t st) {
   TRG_REQUIRE(n >= 1 && n <= MAX_N && batch >= 1, "eigh: order must be in [1, 1024]");
+  const size_t n2 = size_t(n) * n;
   if (n <= JACOBI_MAX_N)
-    launch_jacobi(A, w, V, sweeps, n, batch, false, st);
+    each_piece(batch, [&](size_t b, int nb) {
+      launch_jacobi(A + b * n2, w + b * n, V + b * n2, sweeps + b, n, nb, false, st);
+    });
   else
     hipLaunchKernelGGL(tridiag_ql_kernel, dim3(batch), dim3(TQ_THREADS), 0, st, A, w, V, sweeps, n);
   TRG_HIP_CHECK(hipGetLastError());
@@ -1419,12 +1436,15 @@ size_t eigh_top_work_doubles(int n, int batch) {
 void eigh_top_batched(double *A, double *w, double *V, int *sweeps, int n, int batch, int k, double cluster_rel,
                       double *work, hipStream_t st, bool square) {
   TRG_REQUIRE(n >= 1 && n <= MAX_N && batch >= 1 && k >= 1, "eigh_top: bad sizes");
-  if (n <= JACOBI_MAX_N) {
-    launch_jacobi(A, w, V, sweeps, n, batch, square, st);
-  } else {
-    TRG_REQUIRE(work != nullptr, "eigh_top: workspace missing");
-    launch_tridiag_top(A, w, V, sweeps, n, batch, k, cluster_rel, work, st);
-  }
+  TRG_REQUIRE(work != nullptr || n <= JACOBI_MAX_N, "eigh_top: workspace missing");
+  const size_t n2 = size_t(n) * n;
+  each_piece(batch, [&](size_t b, int nb) {
+    if (n <= JACOBI_MAX_N)
+      launch_jacobi(A + b * n2, w + b * n, V + b * n2, sweeps + b, n, nb, square, st);
+    else
+      launch_tridiag_top(A + b * n2, w + b * n, V + b * n2, sweeps + b, n, nb, k, cluster_rel,
+                         work + eigh_top_work_doubles(n, 1) * b, st);
+  });
   TRG_HIP_CHECK(hipGetLastError());
 }
 

@@ -522,3 +522,30 @@ def test_eigh_top_matrix_that_is_not_finite(n, bad):
         Vk = V[b][:, :q]
         assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
         assert np.max(np.abs(A[b] @ Vk - Vk * w[b][:q])) < 1e-12 * nrm
+
+
+@pytest.mark.parametrize("top", [False, True])
+@pytest.mark.parametrize("n,batch", [(2, 65535), (2, 65537), (3, 131071)])
+def test_eigh_more_matrices_than_one_launch_takes(n, batch, top):
+    """Batches at and beyond the largest second grid dimension (65535): every
+    matrix, the first and last of each piece among them, against LAPACK."""
+    torch = need_gpu()
+    from paper_1911_12954_amd import trg_eigh
+    announce("eigh batch", n, batch, top)
+    X = np.random.default_rng(n).standard_normal((batch, n, n))
+    A = X + X.transpose(0, 2, 1)
+    if top:
+        w, V, sweeps = _eigh_top(A, n, 1e-10)
+    else:
+        dA = torch.from_numpy(A.copy()).cuda()
+        dw = torch.full((batch, n), np.nan, dtype=torch.float64, device="cuda")
+        dV = torch.full((batch, n, n), np.nan, dtype=torch.float64, device="cuda")
+        ds = torch.full((batch,), -7, dtype=torch.int32, device="cuda")
+        trg_eigh(dA.data_ptr(), dw.data_ptr(), dV.data_ptr(), ds.data_ptr(), n, batch,
+                 torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        w, V, sweeps = dw.cpu().numpy(), dV.cpu().numpy(), ds.cpu().numpy()
+    assert np.all(sweeps >= 0)
+    nrm = np.linalg.norm(A, axis=(1, 2))
+    assert np.max(np.abs(w - np.linalg.eigvalsh(A)[:, ::-1]) / nrm[:, None]) < 1e-13
+    assert np.max(np.abs(A @ V - V * w[:, None, :]) / nrm[:, None, None]) < 1e-12
