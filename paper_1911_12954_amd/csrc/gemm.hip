@@ -43,6 +43,7 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));   // at any bf16 element
 
 // FP32 join: K tiles (32 floats each) summed by the MFMA in FP32 before the
 // partial sum is added to the FP64 accumulator
@@ -487,12 +488,17 @@ __device__ inline int split_swz(int row) { return int((0x1320u >> (4 * ((row >> 
 // PL 3: the MFMAs sum FLUSH tiles in FP32; a finished group is added to FP64
 // sums between the first MFMAs of the next one.
 //
+// DMA false serves operands that do not start on 16 bytes, which loads straight
+// to LDS are not known to take: a tile travels through registers, loaded after
+// the barrier of the tile two before it and stored to LDS (two stages) right
+// before the barrier that publishes it.  Same products in the same order.
+//
 // Measured against the kernel before (loads through registers, all fragments
 // of a tile read right before its MFMAs), TFLOP/s of the product:
 //   PL 3  10112^2 x 25056: 154 -> 178 (1.07 PFLOP/s of MFMA, pipes busy 46 ->
 //         57 %); 3200^2 x 3136: 158 -> 192
 //   PL 2  10240^2 x 25056: 346 -> 407 (1.22 PFLOP/s); 2048^2 x 8192: 125 -> 338
-template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH, bool ACCUM>
+template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH, bool DMA, bool ACCUM>
 __global__ void __launch_bounds__(64 * WM * WN)
 gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bt, float *__restrict__ C,
                   uint32_t tiles_m, uint32_t tiles_n, uint32_t ktiles, uint64_t lda, uint64_t ldb, uint64_t ldc,
@@ -502,6 +508,7 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   constexpr int LA = BM / 16 / NW, LB = BN / 16 / NW;   // 1 KB blocks (16 rows) per wave and plane
   static_assert(LA >= 1 && LB >= 1, "every wave loads whole blocks");
   static_assert(FLUSH == 0 || FLUSH == 4, "the loop below folds every fourth tile");
+  static_assert(DMA || NST == 2, "through registers only with two stages");
   constexpr int PLANE = (BM + BN) * RB, STAGE = PLANE * PL;
   constexpr int PERT = PL * (LA + LB);                  // loads of a wave per tile
   constexpr int NTERM = PL == 3 ? 6 : 3;
@@ -542,6 +549,20 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   auto dma = [&](uint32_t kt, uint32_t stage) {
 #pragma unroll
     for (int q = 0; q < PERT; ++q) dma1(uint64_t(kt) * RB, lds0 + stage * STAGE, q);
+  };
+  // the same block into a register, and the tile in registers into a stage
+  u32x4 rg[DMA ? 1 : PERT];
+  auto fetch1 = [&](uint64_t kb, int q) {
+    const int p = q / (LA + LB), u = q % (LA + LB);
+    rg[q] = *reinterpret_cast<const u32x4_any *>((u < LA ? pa[p][u] : pb[p][u - LA]) + kb);
+  };
+  auto put = [&](uint32_t stage) {
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) {
+      const int p = q / (LA + LB), u = q % (LA + LB);
+      const int at = p * PLANE + (u < LA ? (wave * LA + u) * 1024 : BM * RB + (wave * LB + u - LA) * 1024);
+      *reinterpret_cast<u32x4 *>(smem + stage * STAGE + at + lane * 16) = rg[q];
+    }
   };
   const int fro = (g ^ split_swz(r16)) << 4;
   const int aoff = (wm * TM + r16) * RB + fro, boff = BM * RB + (wn * TN + r16) * RB + fro;
@@ -610,10 +631,11 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
     phase();
     // this wave's part of tile kt + 1 has landed; past the barrier all of it
     // has, and no wave reads the stage of tile kt any more
-    wait_vm<(NST - 2) * PERT>();
+    const uint32_t nxt = cur + 1 == NST ? 0 : cur + 1;
+    if constexpr (DMA) wait_vm<(NST - 2) * PERT>();
+    else put(nxt);
     barrier();
     phase();
-    const uint32_t nxt = cur + 1 == NST ? 0 : cur + 1;
     const uint32_t kn = kt + NST < last ? kt + NST : last;   // past the end: the last tile again, never read
     const uint64_t kb = uint64_t(kn) * RB;
     const uint32_t base = lds0 + cur * STAGE;
@@ -629,7 +651,8 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
         any = true;
       }
       if (n % DS == DS / 2 && n / DS < PERT) {
-        dma1(kb, base, n / DS);
+        if constexpr (DMA) dma1(kb, base, n / DS);
+        else fetch1(kb, n / DS);
         any = true;
       }
       if (any) phase();
@@ -637,9 +660,17 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
     phase();
     cur = nxt;
   };
+  if constexpr (DMA) {
 #pragma unroll
-  for (int s = 0; s < NST; ++s) dma(uint32_t(s) < last ? s : last, s);
-  wait_vm<(NST - 1) * PERT>();
+    for (int s = 0; s < NST; ++s) dma(uint32_t(s) < last ? s : last, s);
+    wait_vm<(NST - 1) * PERT>();
+  } else {
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) fetch1(0, q);
+    put(0);
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) fetch1(last > 0 ? RB : 0, q);
+  }
   barrier();
 #pragma unroll
   for (int q = 0; q < PL * HM; ++q) aload1(0, 0, q);
@@ -852,7 +883,7 @@ bool check_gemm(uint64_t BM, uint64_t BN, uint64_t BK, void *C, uint64_t M, uint
   return true;
 }
 
-template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH>
+template <int PL, int BM, int BN, int WM, int WN, int NST, int FLUSH, bool DMA = true>
 void launch_split(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, uint64_t K, uint64_t lda,
                   uint64_t ldb, uint64_t ldc, bool accum, hipStream_t st, uint32_t nb, uint64_t batch_a,
                   uint64_t batch_b, uint64_t batch_c) {
@@ -860,10 +891,10 @@ void launch_split(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N
   static_assert(lds <= 160 * 1024, "LDS tile exceeds 160 KB");
   static const bool attr = [] {   // dynamic LDS above 64 KB must be allowed per kernel
     TRG_HIP_CHECK(hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, true>),
+        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, DMA, true>),
         hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
     TRG_HIP_CHECK(hipFuncSetAttribute(
-        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, false>),
+        reinterpret_cast<const void *>(&gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, DMA, false>),
         hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
     return true;
   }();
@@ -875,10 +906,10 @@ void launch_split(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N
   auto *c = static_cast<float *>(C);
   const uint64_t plA = M * lda, plB = N * ldb;
   if (accum)
-    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, true>), grid, block, lds, st, a, b, c, tm, tn,
+    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, DMA, true>), grid, block, lds, st, a, b, c, tm, tn,
                        kt, lda, ldb, ldc, plA, plB, batch_a, batch_b, batch_c);
   else
-    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, false>), grid, block, lds, st, a, b, c, tm,
+    hipLaunchKernelGGL((gemm_split_kernel<PL, BM, BN, WM, WN, NST, FLUSH, DMA, false>), grid, block, lds, st, a, b, c, tm,
                        tn, kt, lda, ldb, ldc, plA, plB, batch_a, batch_b, batch_c);
   TRG_HIP_CHECK(hipGetLastError());
 }
@@ -941,6 +972,15 @@ bool split_small(uint64_t M, uint64_t N, uint32_t nb, uint64_t big, uint64_t sma
   return cost(small) < rate * cost(big);
 }
 
+// Whether every row of both split-BF16 operands starts on 16 bytes (the rows
+// of a plane and the planes are multiples of that apart: check_gemm).  Others
+// go through registers, at 60 % of the rate: BF16x6 10112^2 x 25056 115 against
+// 188 TFLOP/s, BF16x3 10240^2 x 25056 267 against 431.
+bool split_direct(const void *A, const void *Bt, uint32_t nb, uint64_t batch_a, uint64_t batch_b) {
+  const bool bases = (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Bt)) % 16 == 0;
+  return bases && (nb == 1 || (batch_a * 2 % 16 == 0 && batch_b * 2 % 16 == 0));
+}
+
 }  // namespace
 
 bool gemm_f64_ksplit(uint64_t M, uint64_t N, uint64_t K) {
@@ -972,14 +1012,20 @@ void gemm_nt(int prec, const void *A, const void *Bt, void *C, uint64_t M, uint6
       if (!check_gemm<2>(256, 256, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
       // four waves of 64 x 64, two workgroups per CU, while the 256 x 256 tiles leave CUs idle in
       // their last round: 2048^2 x 8192 338 against 186 TFLOP/s, 10240^2 x 25056 290 against 407
-      if (split_small(M, N, nb, 256, 128, 290.0 / 407.0))
+      if (!split_direct(A, Bt, nb, batch_a, batch_b))
+        launch_split<2, 128, 128, 2, 2, 2, 0, false>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
+                                                     batch_c);
+      else if (split_small(M, N, nb, 256, 128, 290.0 / 407.0))
         launch_split<2, 128, 128, 2, 2, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
       else
         launch_split<2, 256, 256, 2, 4, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
       return;
     case 3:
       if (!check_gemm<3>(128, 128, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
-      if (split_small(M, N, nb, 128, 64, 0.6))
+      if (!split_direct(A, Bt, nb, batch_a, batch_b))
+        launch_split<3, 128, 128, 2, 4, 2, BF6_FLUSH, false>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a,
+                                                           batch_b, batch_c);
+      else if (split_small(M, N, nb, 128, 64, 0.6))
         launch_split<3, 64, 64, 2, 2, 3, BF6_FLUSH>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
                                                     batch_c);
       else

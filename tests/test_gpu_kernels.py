@@ -549,3 +549,38 @@ def test_eigh_more_matrices_than_one_launch_takes(n, batch, top):
     nrm = np.linalg.norm(A, axis=(1, 2))
     assert np.max(np.abs(w - np.linalg.eigvalsh(A)[:, ::-1]) / nrm[:, None]) < 1e-13
     assert np.max(np.abs(A @ V - V * w[:, None, :]) / nrm[:, None, None]) < 1e-12
+
+
+@pytest.mark.parametrize("precision,M,N", [("bf16x3", 256, 512), ("bf16x6", 128, 256), ("bf16x6", 1280, 1152)])
+@pytest.mark.parametrize("K", [32, 64, 96, 160, 288])
+@pytest.mark.parametrize("off_a,off_b", [(1, 0), (0, 4), (2, 6)])
+def test_gemm_split_operands_off_16_bytes(precision, M, N, K, off_a, off_b):
+    """Operands that start 2, 4, 8 or 12 bytes past a 16-byte boundary, which a
+    16-byte load straight to LDS is not known to take: the bits of the same
+    product from aligned operands, from one K tile to past two FP32 groups."""
+    torch = need_gpu()
+    from paper_1911_12954_amd import trg_gemm
+    announce("gemm split off 16 bytes", precision, M, N, K, off_a, off_b)
+    planes = 2 if precision == "bf16x3" else 3
+    g = torch.Generator(device="cuda").manual_seed(K)
+
+    def operand(rows, off):
+        x = torch.randn((rows, K), generator=g, device="cuda")
+        out = torch.empty((planes, rows, K), dtype=torch.bfloat16, device="cuda")
+        for p in range(planes):
+            out[p] = x.to(torch.bfloat16)
+            x = x - out[p].float()
+        moved = torch.empty(out.numel() + off, dtype=torch.bfloat16, device="cuda")
+        moved[off:] = out.flatten()
+        assert out.data_ptr() % 16 == 0 and moved.data_ptr() % 16 == 0
+        return out, moved[off:]
+
+    A, A2 = operand(M, off_a)
+    B, B2 = operand(N, off_b)
+    for accumulate in (False, True):
+        C = [torch.ones((M, N), dtype=torch.float32, device="cuda") for _ in range(2)]
+        for a, b, c in ((A, B, C[0]), (A2, B2, C[1])):
+            trg_gemm(precision, a.data_ptr(), b.data_ptr(), c.data_ptr(), M, N, K, K, K, N, accumulate,
+                     torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert torch.equal(C[0], C[1])
