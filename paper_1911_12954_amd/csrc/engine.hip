@@ -755,6 +755,9 @@ int guarded(trg_ctx *c, F &&f) {
 
 // Pinned result slots of the contexts: 64 in one allocation, given back with the
 // context; a context beyond them has none and copies its results instead.
+// The allocation comes with the first context, which may be created while a
+// stream is being captured, on this thread or another: outside the relaxed
+// mode it would invalidate that capture, of which it is no part.
 namespace {
 constexpr int HOST_SLOTS = 64;
 constexpr size_t HOST_SLOT_BYTES = 64;
@@ -769,7 +772,11 @@ HostResult *take_host_slot() {
   if (!g_slots_tried) {
     g_slots_tried = true;
     void *p = nullptr;
-    if (hipHostMalloc(&p, HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    TRG_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
+    const hipError_t e = hipHostMalloc(&p, HOST_SLOTS * HOST_SLOT_BYTES, hipHostMallocPortable | hipHostMallocMapped);
+    TRG_HIP_CHECK(hipThreadExchangeStreamCaptureMode(&mode));
+    if (e == hipSuccess)
       g_slots = static_cast<char *>(p);
     else
       (void)hipGetLastError();
