@@ -613,26 +613,33 @@ int ts_mul_slabs(int64_t m) {
   return int(wg < TSM_GRID ? wg : TSM_GRID);
 }
 
+template <int NB, bool GRAM, bool PAIRS>
+void launch_ts_mul_as(const double *Y, int64_t m, int k, const double *R, double *Q, double *part, hipStream_t st) {
+  constexpr int lds = 16 * NB * (16 * NB + 4) * 8;
+  static_assert(lds >= NB * (NB + 1) / 2 * 256 * 8, "the Gram sums fit where R was");
+  static const bool attr = [] {   // dynamic LDS above 64 KB must be allowed per kernel
+    TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(&ts_mul_kernel<NB, GRAM, PAIRS>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+    return true;
+  }();
+  (void)attr;
+  hipLaunchKernelGGL((ts_mul_kernel<NB, GRAM, PAIRS>), dim3(uint32_t(ts_mul_slabs(m))), dim3(64 * TSM_WAVES), lds, st, Y,
+                     m, k, R, Q, part);
+  TRG_HIP_CHECK(hipGetLastError());
+}
+
 // part: nullptr, or ts_mul_slabs(m) slabs of (16 ceil(k / 16))^2 for Q^T Q
 void launch_ts_mul(const double *Y, int64_t m, int k, const double *R, double *Q, double *part, hipStream_t st) {
   TRG_REQUIRE(k >= 1 && k <= TSG_K && m >= 1 && (!part || k <= TSM_GRAM_MAX), "ts_mul: k out of range");
   auto launch = [&](auto blocks) {
     constexpr int NB = decltype(blocks)::value;
-    constexpr int lds = 16 * NB * (16 * NB + 4) * 8;
-    static_assert(lds >= NB * (NB + 1) / 2 * 256 * 8, "the Gram sums fit where R was");
-    auto go = [&](auto kernel) {
-      TRG_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-      hipLaunchKernelGGL(kernel, dim3(uint32_t(ts_mul_slabs(m))), dim3(64 * TSM_WAVES), lds, st, Y, m, k, R, Q, part);
-      TRG_HIP_CHECK(hipGetLastError());
-    };
     constexpr bool G = 16 * NB <= TSM_GRAM_MAX;
     if (k % 2 == 0) {
-      if (G && part) go(&ts_mul_kernel<NB, G, true>);
-      else go(&ts_mul_kernel<NB, false, true>);
+      if (G && part) launch_ts_mul_as<NB, G, true>(Y, m, k, R, Q, part, st);
+      else launch_ts_mul_as<NB, false, true>(Y, m, k, R, Q, part, st);
     } else {
-      if (G && part) go(&ts_mul_kernel<NB, G, false>);
-      else go(&ts_mul_kernel<NB, false, false>);
+      if (G && part) launch_ts_mul_as<NB, G, false>(Y, m, k, R, Q, part, st);
+      else launch_ts_mul_as<NB, false, false>(Y, m, k, R, Q, part, st);
     }
   };
   switch ((k + 15) / 16) {
