@@ -332,6 +332,7 @@ chol_inv_block_kernel(const double *C, int n, double shift_coef, double *Rg, dou
     __syncthreads();
     if (wave == 0) {
       update(k, k + 1, k + 1);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // factor's lanes read what other lanes stored
       factor(k + 1);
     } else {
       int e = 0;   // the other blocks (r, c), k < r <= c, dealt to waves 1 .. 7
