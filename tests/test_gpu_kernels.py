@@ -584,3 +584,23 @@ def test_gemm_split_operands_off_16_bytes(precision, M, N, K, off_a, off_b):
                      torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert torch.equal(C[0], C[1])
+
+
+@pytest.mark.parametrize("n,k,rank", [(640, 130, 640), (600, 20, 8), (1024, 70, 1024)])
+def test_eigh_top_several_chunks_at_large_orders(n, k, rank):
+    """Above order 576 (the widest back-transformation) with more than one
+    chunk of 64 vectors, so that every solve factors its chunk anew: by the
+    number of vectors asked for, and by a rank below it, whose zero cluster
+    the cut splits so that every vector is computed.  Bounds as above."""
+    announce("eigh_top chunks", n, k, rank)
+    X = np.random.default_rng(n + k).standard_normal((n, rank)) * 0.95 ** np.arange(rank)
+    A = X @ X.T
+    w, V, kk = _eigh_top(A[None], k, 1e-10)
+    nrm = np.linalg.norm(A)
+    q = int(kk[0])
+    assert 64 < q <= n and (q == n if rank < k else q >= k)
+    assert np.max(np.abs(w[0] - np.linalg.eigvalsh(A)[::-1])) < 1e-13 * nrm
+    Vk = V[0][:, :q]
+    assert np.all(V[0][:, q:] == 0.0)
+    assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
+    assert np.max(np.abs(A @ Vk - Vk * w[0][:q])) < 1e-12 * nrm
