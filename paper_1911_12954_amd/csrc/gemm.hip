@@ -87,7 +87,6 @@ template <> struct Prec<3> {  // BF16 x6
   static constexpr int elem = 2;
 };
 
-template <int GM>
 __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm,
                                    uint32_t &tn) {
   const uint32_t total = tiles_m * tiles_n;
@@ -95,11 +94,11 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
   const uint32_t xcd = wg % NUM_XCD, idx = wg / NUM_XCD;
   const uint32_t per = total / NUM_XCD, rem = total % NUM_XCD;
   const uint32_t w = xcd * per + (xcd < rem ? xcd : rem) + idx;
-  // grouped raster: GM tile-rows walked column by column
-  const uint32_t group_size = GM * tiles_n;
+  // grouped raster: GROUP_M tile-rows walked column by column
+  const uint32_t group_size = GROUP_M * tiles_n;
   const uint32_t group = w / group_size;
-  const uint32_t first_m = group * GM;
-  const uint32_t gm = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
+  const uint32_t first_m = group * GROUP_M;
+  const uint32_t gm = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
   const uint32_t in_group = w % group_size;
   tm = first_m + in_group % gm;
   tn = in_group / gm;
@@ -213,7 +212,7 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
   const int wm = wave / WN, wn = wave % WN;
   const int g = lane >> 4, r16 = lane & 15;
   uint32_t tm, tn;
-  tile_coords<GROUP_M>(blockIdx.x, tiles_m, tiles_n, tm, tn);
+  tile_coords(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
   A += uint64_t(blockIdx.z) * batch_a;
   Bt += uint64_t(blockIdx.z) * batch_b;
