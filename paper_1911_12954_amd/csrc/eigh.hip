@@ -2,10 +2,12 @@
 // the paper: the isometries are the leading eigenvectors of the two-site
 // environment) and the selection of the truncated isometry.
 //
-// Eigensolver: cyclic two-sided Jacobi in parallel (round-robin) order, one
-// workgroup per matrix.  Each round rotates n/2 disjoint index pairs (A <- J^T
-// A J, V <- V J).  A sweep is n-1 rounds; sweeps repeat until the off-diagonal
-// Frobenius norm falls below 1e-14 of the matrix norm, plus one final sweep.
+// Eigensolver up to order 160: cyclic two-sided Jacobi in parallel (round-robin)
+// order.  Each round rotates n/2 disjoint index pairs (A <- J^T A J, V <- V J); the
+// workgroups of a matrix all rotate A and share the rows of V.  A sweep is n-1
+// rounds; sweeps repeat until the off-diagonal Frobenius norm falls below
+// 1e-14 of the matrix norm, plus one final sweep.  Above order 160:
+// Householder reduction, with QL or with multisection and inverse iteration.
 // Everything is deterministic: fixed pairing order, fixed reduction trees.
 #include <algorithm>
 #include <cmath>
@@ -97,11 +99,14 @@ __device__ inline int jac_tri(int x, int y) {   // x >= y
 // as before), 5e-15 (triangle).
 //
 // TRI false keeps all of A and, operation for operation, the rotations of that
-// slower form (hypot, two square roots, three divisions), so that its
-// eigensystems come out bit for bit: in a mixed-precision HOTRG run the sign
-// and the pick among near-degenerate vectors hang on the last bits of the
-// Grams' eigensystems, and a run repeated, resumed or batched with another
-// form of the solver would part from its earlier tensors after a few steps.
+// slower form (hypot, two square roots, three divisions).  In a mixed-precision
+// HOTRG run the sign and the pick among near-degenerate vectors hang on the
+// last bits of the Grams' eigensystems, so a run that is continued from a state
+// written by a library with the slower form would part from it after a few
+// steps if the bits differed.  They agree as long as both forms stop at the
+// same sweep: the norm that decides it is summed in another order, so one
+// that falls within a rounding of the threshold may not.  HOTRG asks for this
+// form up to order JACOBI_SQUARE_N; the matrices above it fit LDS as triangles only.
 template <int NT, bool TRI>
 __global__ void __launch_bounds__(NT)
 jacobi_kernel(const double *Aall, double *wall, double *Vall, int *sweeps_out, int n, int rl, FastDiv by_n,
@@ -712,14 +717,16 @@ tridiag_ql_kernel(double *Aall, double *wall, double *Vall, int *status, int n) 
 // 0.6 ms in LDS, values 1.1, vectors 1.6) and 2.0 ms for two of order 196 (68
 // columns of 7 us, 0.6 in LDS, 0.4, 0.4), against 81 and 11.2 ms with one
 // workgroup per matrix for all of it (140 us a column at order 576: 2.6 MB
-// through one CU and 33 barriers).
+// through one CU and 33 barriers).  The column and finish kernels hold the
+// pointers of TdScratch in private memory (120 bytes per lane), because p and v
+// are indexed by the parity of the column.
 constexpr int TD_THREADS = 256, TD_WAVES = TD_THREADS / 64;
 constexpr int TD_LDS = 128;          // order from which the trailing matrix lives in LDS
 constexpr int TD_FIN = 1024;         // threads of td_finish_kernel and td_vectors_kernel
 constexpr int TOP_ITERS = 3;
 constexpr int TD_CHUNK = 64;         // vectors solved together: lanes of a wave
 constexpr int TD_MS = 16;            // multisection points per eigenvalue
-// doubles of scratch per n beside two n x n matrices; td_scratch uses 78 of them
+// doubles of scratch per n beside two n x n matrices; td_scratch uses 77 of them
 constexpr int TOP_SCRATCH = 96;
 
 // fixed start vector of inverse iteration: entries in [-1, 1) from a hash of

@@ -428,10 +428,10 @@ StepPrep prepare_step(trg_ctx &c, int mu, int dcut) {
   p.ri = rec_i(c, p.n_step);
   return p;
 }
-// Gram matrices of every context into one buffer, one batched Jacobi launch
-// for all of them, then each context's isometry selection.  Every matrix is
-// processed by its own workgroup, so a batch gives the same bits as single
-// contexts.
+// Gram matrices of every context into one buffer, one batched eigensolver run
+// for all of them, then each context's isometry selection.  Every matrix has
+// workgroups of its own, which do the same operations however many matrices
+// there are, so a batch gives the same bits as single contexts.
 void isometries_batch(std::vector<trg_ctx *> &cs, std::vector<StepPrep> &ps, int mu) {
   trg_ctx &c0 = *cs[0];
   const int nc = int(cs.size());

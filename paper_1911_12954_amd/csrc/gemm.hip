@@ -25,8 +25,9 @@
 // Workgroup ids are remapped (ids are dealt round-robin to the 8 XCDs).  FP64
 // and FP32: each XCD works on one contiguous range of tiles, walked in groups of
 // GROUP_M tile-rows, so that neighbouring tiles on one XCD share A and Bt rows
-// in that XCD's L2.  Split BF16: the XCDs also share blocks (tile_coords_shared,
-// which made the FP64 kernel 0.3 % slower).
+// in that XCD's L2.  Split BF16: the XCDs also share blocks (tile_coords_shared).
+// In FP64 that order is 0.3 % slower; in FP32 it gives 7808^2 x 7776 132.9 against
+// 130.5 TFLOP/s and 8192^2 x 8192 137.8 against 138.4.
 #include <algorithm>
 #include <cmath>
 #include <type_traits>
@@ -104,8 +105,9 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
   tn = in_group / gm;
 }
 
-// Tiles of the split-BF16 kernels: one workgroup per CU, so 256 in a round, laid
-// out as 16 x 16 tiles of which each XCD takes 8 x 4.  Its L2 serves the 12
+// Tiles of the split-BF16 kernels.  The large ones run one workgroup per CU, so
+// 256 in a round, laid out as 16 x 16 tiles of which each XCD takes 8 x 4 (the
+// small ones, several per CU and few rounds, keep the order).  Its L2 serves the 12
 // panels of those as before, and the 8 XCDs together stream 32 panels instead
 // of 96, so that most of what one XCD misses another has just brought into the
 // memory-side cache.  Bijective for any grid: blocks of 256 workgroups are
@@ -115,7 +117,8 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
 // These kernels run at the power limit, where traffic from memory costs clock:
 // BF16x6 30080 x 100096 x 100000 (a full slice at Dcut 10) 179.5 -> 205.6
 // TFLOP/s, 10112 x 10112 x 100000 178 -> 188; BF16x3 13312 x 13312 x 59072 469 ->
-// 490, against each XCD walking its own eighth of the tiles in groups of 4 or 8 rows.
+// 490, against each XCD walking its own eighth of the tiles in groups of 4 or
+// 8 rows (after it, on another card, 185 and 478).
 __device__ inline void tile_coords_shared(uint32_t wg, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
   constexpr uint32_t ROUND = 256, GM = 16, SW = 4, HALF = 8;
   const uint32_t total = tiles_m * tiles_n, base = wg / ROUND * ROUND;
@@ -155,7 +158,9 @@ __device__ inline int pipe_swz(int row) {
 // LDS, the next tile is stored to the other LDS stage and the one after that
 // is loaded from memory; the barrier of a tile falls between two MFMA groups.
 // MINW waves per SIMD come from different workgroups, so one workgroup's
-// barrier is covered by another's MFMAs.
+// barrier is covered by another's MFMAs.  The FP32 64 x 128 tile, with FP64
+// sums beside its accumulators, does not fit the 256 registers that two waves
+// per SIMD leave: 76 spill (172 bytes of scratch per lane).
 //
 // Measured (M = N = 10112, K = 25008 / 25056): FP64 58.3 -> 72.3 TFLOP/s (92 %
 // of 78.6; MFMA pipes busy 77 -> 96 % at 8192^2), FP32 96 -> 138 TFLOP/s
@@ -454,6 +459,8 @@ gemm_pipe_kernel(const typename Prec<PREC>::in_t *__restrict__ A, const typename
 // (lds: wave-uniform byte offset).  No register receives the data; the
 // compiler does not count the load, so wait_vm must cover it before a barrier
 // publishes it.  Writing M0 needs one wait state before the load reads it.
+// M0 is reserved: the compiler takes no clobber of it and writes it itself
+// right before each instruction that reads it, of which these kernels have none.
 __device__ inline void dma16(const void *p, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(p), "s"(lds) : "memory");
 }
@@ -518,7 +525,6 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WN, wn = wave % WN, g = lane >> 4, r16 = lane & 15;
   uint32_t tm, tn;
-  // PL 3: groups of four tile rows (178 TFLOP/s against 173 with eight)
   tile_coords_shared(blockIdx.x, tiles_m, tiles_n, tm, tn);
   const uint64_t m0 = uint64_t(tm) * BM, n0 = uint64_t(tn) * BN;
   A += uint64_t(blockIdx.z) * batch_a;
@@ -966,6 +972,9 @@ void gemm_f64(const void *A, const void *Bt, void *C, uint64_t M, uint64_t N, ui
 // Split-BF16 products: whether tiles of `small` squared finish before tiles of
 // `big` squared, whose last round may leave most of the 256 CUs idle; `rate`
 // is the speed of the small-tile kernel over the big-tile one on full rounds.
+// BF16x6, 64 x 64 against 128 x 128 tiles, TFLOP/s: 512^2 x 1024 44 and 18,
+// 1024^2 x 1024 115 and 67, 1280^2 x 1024 115 and 104, 1664^2 x 1664 132 and 170,
+// 2176^2 x 2048 130 and 146, 7808^2 x 7776 116 and 192, 10112^2 x 25056 110 and 188.
 bool split_small(uint64_t M, uint64_t N, uint32_t nb, uint64_t big, uint64_t small, double rate) {
   auto cost = [&](uint64_t b) { return std::ceil(double(M / b) * double(N / b) * nb / 256.0) * double(b * b); };
   return cost(small) < rate * cost(big);

@@ -382,7 +382,7 @@ reduce_splits_grouped_kernel(const double *part, int splits, int64_t rows, int64
   }
 }
 
-// Environment Grams X X^T of up to EG_MAXE leg pairs of one tensor, read in
+// Environment Grams X X^T of up to ENV_MAXE leg pairs of one tensor, read in
 // place: X has rows (l1, l2) (R <= 128 of them) and the other legs in canonical
 // order as columns, element T[row offset + column offset].  Workgroup (s, e)
 // sums the columns [s kper, (s + 1) kper) of environment e into its own R x R
