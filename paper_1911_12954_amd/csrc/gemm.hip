@@ -114,11 +114,12 @@ __device__ inline void tile_coords(uint32_t wg, uint32_t tiles_m, uint32_t tiles
 // consecutive in the raster (the last, smaller one cut evenly among the XCDs),
 // which walks row groups of 16 in strips of 4 columns, each strip's upper 8
 // rows first.
-// These kernels run at the power limit, where traffic from memory costs clock:
-// BF16x6 30080 x 100096 x 100000 (a full slice at Dcut 10) 179.5 -> 205.6
-// TFLOP/s, 10112 x 10112 x 100000 178 -> 188; BF16x3 13312 x 13312 x 59072 469 ->
-// 490, against each XCD walking its own eighth of the tiles in groups of 4 or
-// 8 rows (after it, on another card, 185 and 478).
+// Measured against each XCD walking its own eighth of the tiles in groups of 4
+// (BF16x6) or 8 rows (BF16x3), TFLOP/s: a full slice of the Dcut 10 step, 30080 x
+// 100096 x 100000, 179.5 -> 205.6 (6.6 -> 5.5 TB read from beyond the L2s, MFMA
+// pipes 47 -> 52 % busy at 2.26 and 2.27 GHz); 10112 x 10112 x 100000 random
+// operands 178 -> 188 (pipes 56 % busy at 1.79 -> 1.88 GHz, where the power limit
+// sets the clock); BF16x3 13312 x 13312 x 59072 469 -> 490 (1.60 -> 1.66 GHz).
 __device__ inline void tile_coords_shared(uint32_t wg, uint32_t tiles_m, uint32_t tiles_n, uint32_t &tm, uint32_t &tn) {
   constexpr uint32_t ROUND = 256, GM = 16, SW = 4, HALF = 8;
   const uint32_t total = tiles_m * tiles_n, base = wg / ROUND * ROUND;
@@ -482,8 +483,9 @@ __device__ inline int split_swz(int row) { return int((0x1320u >> (4 * ((row >> 
 //
 // What bounds it: an MFMA takes 16 cycles, so a K tile is over in 1536 (PL 3,
 // 128 x 128) to 3072 cycles (PL 2, 256 x 256) and neither LDS reads nor the
-// 1-2 us of a load from beyond L2 may stand between two tiles; under a long
-// launch the clock then falls to 1.8-1.9 GHz (of 2.4).  Hence:
+// 1-2 us of a load from beyond L2 may stand between two tiles.  On dense
+// operands the power limit holds the clock at 1.7-1.9 GHz (of 2.4), with the
+// pipes 56 to 80 % busy.  Hence:
 // - tiles go from memory straight to LDS (no staging registers, no LDS
 //   stores), issued NST tiles ahead into a ring of NST stages;
 // - every LDS read is issued half a tile ahead of the MFMAs that use it, A in
