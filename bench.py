@@ -37,22 +37,17 @@ PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16x3": 2500.0, "bf16x6": 2500.0}
 # BF16 MFMA products per multiply-add of the split joins
 SPLIT_PRODUCTS = {"bf16x3": 3.0, "bf16x6": 6.0}
 HBM_PEAK_GBS = 8000.0
-# HBM bytes per join launch of the steady Dcut 10 step (three full x0
+# Bytes beyond the L2s per join launch of the steady Dcut 10 step (three full x0
 # slices and one of a single x0 value per step, averaged), from rocprofv3
 # FETCH_SIZE and WRITE_SIZE of the join kernel, each scaled by what the
 # counter reads for a device-to-device copy of 4 GiB (FETCH x 2.0, WRITE x
 # 1.0).  Each entry names the SHA-256 of the kernel source it was taken on;
 # the figure is reported only while csrc/gemm.hip still has that hash.
 JOIN_TRAFFIC = {
-    ("bf16x6", 10): {"bytes_per_launch": 4.912e12, "algorithmic_bytes_per_launch": 8.51e10,
-                     "gemm_sha16": "372fd768a9adad15",
-                     "source": "profiles/join_gemm_hotrg_dcut10_bf16x6.md (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0)"},
-    ("fp64", 10): {"bytes_per_launch": 1.510e13, "algorithmic_bytes_per_launch": 1.202e11,
-                   "gemm_sha16": "372fd768a9adad15",
-                   "source": "profiles/join_gemm_hotrg_dcut10_fp64.md (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0)"},
-    ("fp32", 10): {"bytes_per_launch": 3.121e12, "algorithmic_bytes_per_launch": 6.01e10,
-                   "gemm_sha16": "372fd768a9adad15",
-                   "source": "profiles/join_gemm_hotrg_dcut10_fp32.md (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0)"},
+    (prec, 10): {"bytes_per_launch": moved, "algorithmic_bytes_per_launch": needed, "gemm_sha16": "59ede67c164f9a72",
+                 "source": "profiles/join_gemm_hotrg_dcut10_%s.md (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0)" % prec}
+    for prec, moved, needed in (("bf16x6", 4.601e12, 8.51e10), ("bf16x3", 2.037e12, 6.02e10),
+                                ("fp32", 1.538e13, 6.01e10), ("fp64", 6.966e12, 1.202e11))
 }
 GEMM_SRC = os.path.join(ROOT, "paper_1911_12954_amd", "csrc", "gemm.hip")
 

@@ -352,8 +352,9 @@ const char *trg_last_error(const trg_ctx *ctx);
  * double out), FP32 (float in, float out), BF16X3 (A = A_hi, A + M*lda
  * elements = A_lo, likewise for Bt; bf16 in, float out), BF16X6 (three
  * planes M*lda elements apart: A_hi, A_mid, A_lo; likewise for Bt; bf16 in,
- * float out).  accumulate != 0 adds to C.  Returns TRG_EINVAL on shape
- * violations. */
+ * float out).  accumulate != 0 adds to C.  A and Bt may start at any element;
+ * the BF16 precisions are faster when both start on 16 bytes.  Returns
+ * TRG_EINVAL on shape violations. */
 int trg_gemm(int precision, const void *A, const void *Bt, void *C, long long M, long long N,
              long long K, long long lda, long long ldb, long long ldc, int accumulate,
              void *stream);
