@@ -717,7 +717,11 @@ tridiag_ql_kernel(double *Aall, double *wall, double *Vall, int *status, int n) 
 // 0.6 ms in LDS, values 1.1, vectors 1.6) and 2.0 ms for two of order 196 (68
 // columns of 7 us, 0.6 in LDS, 0.4, 0.4), against 81 and 11.2 ms with one
 // workgroup per matrix for all of it (140 us a column at order 576: 2.6 MB
-// through one CU and 33 barriers).  The column and finish kernels hold the
+// through one CU and 33 barriers).  Columns that are zero already (diagonal and
+// block-diagonal matrices) change nothing and are passed over; what they leave
+// is their launch (order 576, two matrices: diagonal 2.4 ms, blocks of 8 5.2, zero
+// with all 576 vectors 6.0; 5.5, 5.7 and 71 with every column worked through and
+// every pair of vectors orthogonalised).  The column and finish kernels hold the
 // pointers of TdScratch in private memory (120 bytes per lane), because p and v
 // are indexed by the parity of the column.
 constexpr int TD_THREADS = 256, TD_WAVES = TD_THREADS / 64;
@@ -728,6 +732,8 @@ constexpr int TD_CHUNK = 64;         // vectors solved together: lanes of a wave
 constexpr int TD_MS = 16;            // multisection points per eigenvalue
 // doubles of scratch per n beside two n x n matrices; td_scratch uses 77 of them
 constexpr int TOP_SCRATCH = 96;
+
+constexpr double TD_ZERO = -1.0;     // tau of a column with nothing below the diagonal
 
 // fixed start vector of inverse iteration: entries in [-1, 1) from a hash of
 // the vector's rank and the entry's index
@@ -743,7 +749,8 @@ __device__ inline double top_start(int r, int i) {
 
 // scratch of one matrix (offsets in units of n doubles from its end of work)
 struct TdScratch {
-  double *dd, *ee, *lam, *p[2], *v[2], *tau;   // diagonal, subdiagonal, eigenvalues by slot, A v and v of a column
+  double *dd, *ee, *lam, *p[2], *v[2];         // diagonal, subdiagonal, eigenvalues by slot, A v and v of a column
+  double *tau;                                 // of each reflector, or TD_ZERO
   double *eb;                                  // subdiagonal with zeros between the blocks
   int *s0, *e0, *kk;                           // block of each slot, vectors needed
   unsigned long long *piv;                     // row swaps of the LU, one bit per lane
@@ -777,9 +784,11 @@ __device__ inline double *td_work(double *work, int n, int b) {
 // the matrix's scale (a parity block of a Gram whose weights are 1e-150 of
 // the other block's) neither underflow nor make tau overflow.  vv becomes v
 // (zero and tau = 0 for a column that is reduced already); returns the new
-// subdiagonal entry.  Every thread calls it; vv is complete after it.
+// subdiagonal entry.  zero: every entry is exactly 0 (a NaN among them is not),
+// so that nothing of the trailing matrix changes.  Every thread calls it; vv is
+// complete after it.
 template <int NT>
-__device__ inline double td_reflector(double *vv, int m, double &tau, double *sh0, double *sh1) {
+__device__ inline double td_reflector(double *vv, int m, double &tau, bool &zero, double *sh0, double *sh1) {
   const int t = threadIdx.x;
   double amax = 0.0;
   for (int i = t; i < m; i += NT) amax = fmax(amax, fabs(vv[i]));
@@ -793,6 +802,7 @@ __device__ inline double td_reflector(double *vv, int m, double &tau, double *sh
   }
   const double raw0 = vv[0];
   const double nrm2 = wg_reduce<NT / 64, false>(s2, sh1);   // its barrier: raw0 is read everywhere
+  zero = nrm2 == 0.0;
   const double x0 = ldexp(raw0, -ex);
   const double alpha = x0 >= 0.0 ? -sqrt(nrm2) : sqrt(nrm2);
   const double vtv = nrm2 - 2.0 * alpha * x0 + alpha * alpha;  // |x - alpha e1|^2
@@ -807,7 +817,7 @@ __device__ inline double td_reflector(double *vv, int m, double &tau, double *sh
 // product p = A v, brings row k up to date and forms the reflector of column
 // k; then each wave updates its rows of the trailing matrix with column k - 1
 // and multiplies them by the new v in the same pass, so the matrix is read and
-// written once per column.
+// written once per column, and not at all when both columns are zero.
 __global__ void __launch_bounds__(TD_THREADS)
 td_column_kernel(double *Aall, double *workall, int n, int k) {
   __shared__ double vo[MAX_N], wo[MAX_N], vn[MAX_N];
@@ -818,10 +828,10 @@ td_column_kernel(double *Aall, double *workall, int n, int k) {
   TdScratch T = td_scratch(work + size_t(2) * n * n, n);
   const int m = n - k - 1;                 // trailing order; entry i of vn is row k + 1 + i
   const double *p = T.p[(k + 1) & 1], *vp = T.v[(k + 1) & 1];
-  double tau_o = 0.0;
-  if (k > 0) {
+  const double tau_o = k > 0 ? T.tau[k - 1] : TD_ZERO;
+  const bool still = tau_o < 0.0;          // column k - 1 leaves the matrix as it is
+  if (!still) {
     // vo, wo: entries of rows k .. n - 1
-    tau_o = T.tau[k - 1];
     double pv = 0.0;
     for (int i = t; i <= m; i += TD_THREADS) {
       vo[i] = vp[i];
@@ -839,7 +849,8 @@ td_column_kernel(double *Aall, double *workall, int n, int k) {
   for (int i = t; i < m; i += TD_THREADS) vn[i] = row[1 + i] - (v0 * wo[1 + i] + w0 * vo[1 + i]);
   __syncthreads();
   double tau;
-  const double sub = td_reflector<TD_THREADS>(vn, m, tau, sh[1], sh[2]);
+  bool zero;
+  const double sub = td_reflector<TD_THREADS>(vn, m, tau, zero, sh[1], sh[2]);
   if (blockIdx.x == 0) {
     double *u = work + size_t(k) * n;      // reflector k, scaled: H = I - u u^T
     const double st = sqrt(tau);
@@ -849,9 +860,10 @@ td_column_kernel(double *Aall, double *workall, int n, int k) {
     if (t == 0) {
       T.dd[k] = row[0] - 2.0 * v0 * w0;
       T.ee[k] = sub;
-      T.tau[k] = tau;
+      T.tau[k] = zero ? TD_ZERO : tau;
     }
   }
+  if (still && zero) return;
   // rows of this wave, two at a time
   const int nw = gridDim.x * TD_WAVES;
   double *pk = T.p[k & 1];
@@ -893,22 +905,34 @@ td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
   const int q = n - k0;
   {
     const double *p = T.p[(k0 + 1) & 1], *vp = T.v[(k0 + 1) & 1];
-    const double tau = k0 > 0 ? T.tau[k0 - 1] : 0.0;
+    const double tau_o = k0 > 0 ? T.tau[k0 - 1] : TD_ZERO;
+    const bool still = tau_o < 0.0;
+    const double tau = still ? 0.0 : tau_o;
     double pv = 0.0;
     if (t < q) {
-      vo[t] = k0 > 0 ? vp[t] : 0.0;
-      wo[t] = k0 > 0 ? tau * p[t] : 0.0;
+      vo[t] = still ? 0.0 : vp[t];
+      wo[t] = still ? 0.0 : tau * p[t];
       pv = wo[t] * vo[t];
     }
     const double K = 0.5 * tau * wg_reduce<TD_FIN / 64, false>(pv, sh[0]);
     if (t < q) wo[t] -= K * vo[t];
     __syncthreads();
+    bool off = false;
     for (int idx = t; idx < q * q; idx += TD_FIN) {
       const int i = idx / q, j = idx - i * q;
-      L[i * TD_LD + j] = A[size_t(k0 + i) * n + k0 + j] - (vo[i] * wo[j] + wo[i] * vo[j]);
+      const double x = A[size_t(k0 + i) * n + k0 + j] - (vo[i] * wo[j] + wo[i] * vo[j]);
+      L[i * TD_LD + j] = x;
+      off = off || (i != j && !(x == 0.0));
+    }
+    if (!__syncthreads_or(off)) {          // diagonal: no reflector, and td_back_kernel reads none
+      if (t < q) {
+        T.dd[k0 + t] = L[t * TD_LD + t];
+        T.ee[k0 + t] = 0.0;
+        T.tau[k0 + t] = TD_ZERO;
+      }
+      return;
     }
   }
-  __syncthreads();
   // thread (g, c) of 8 x 128: column c, every eighth row
   const int c = t & (TD_LDS - 1), g = t / TD_LDS;
   for (int s = 0; s + 2 < q; ++s) {
@@ -917,25 +941,28 @@ td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
     if (t < m) vo[t] = L[s * TD_LD + s + 1 + t];
     __syncthreads();
     double tau;
-    const double off = td_reflector<TD_FIN>(vo, m, tau, sh[0], sh[1]);
-    double a = 0.0;
-    if (c < m)
-      for (int i = g; i < m; i += 8) a += sub[i * TD_LD + c] * vo[i];
-    part[g][c] = a;
-    __syncthreads();
-    double pv = 0.0;
-    if (t < m) {
-      double x = part[0][t];
-      for (int u = 1; u < 8; ++u) x += part[u][t];
-      wo[t] = tau * x;
-      pv = wo[t] * vo[t];
-    }
-    const double K = 0.5 * tau * wg_reduce<TD_FIN / 64, false>(pv, sh[2]);
-    if (t < m) wo[t] -= K * vo[t];
-    __syncthreads();
-    if (c < m) {
-      const double vc = vo[c], wc = wo[c];
-      for (int i = g; i < m; i += 8) sub[i * TD_LD + c] -= vo[i] * wc + wo[i] * vc;
+    bool zero;
+    const double off = td_reflector<TD_FIN>(vo, m, tau, zero, sh[0], sh[1]);
+    if (!zero) {
+      double a = 0.0;
+      if (c < m)
+        for (int i = g; i < m; i += 8) a += sub[i * TD_LD + c] * vo[i];
+      part[g][c] = a;
+      __syncthreads();
+      double pv = 0.0;
+      if (t < m) {
+        double x = part[0][t];
+        for (int u = 1; u < 8; ++u) x += part[u][t];
+        wo[t] = tau * x;
+        pv = wo[t] * vo[t];
+      }
+      const double K = 0.5 * tau * wg_reduce<TD_FIN / 64, false>(pv, sh[2]);
+      if (t < m) wo[t] -= K * vo[t];
+      __syncthreads();
+      if (c < m) {
+        const double vc = vo[c], wc = wo[c];
+        for (int i = g; i < m; i += 8) sub[i * TD_LD + c] -= vo[i] * wc + wo[i] * vc;
+      }
     }
     double *u = work + size_t(k) * n;
     const double st = sqrt(tau);
@@ -943,6 +970,7 @@ td_finish_kernel(const double *Aall, double *workall, int n, int k0) {
     if (t == 0) {
       T.dd[k] = L[s * TD_LD + s];
       T.ee[k] = off;
+      T.tau[k] = zero ? TD_ZERO : tau;
     }
     __syncthreads();
   }
@@ -1012,6 +1040,10 @@ td_values_kernel(double *workall, int n) {
   const int slot = (blockIdx.x * TD_THREADS + t) / TD_MS, l = t % TD_MS;
   if (slot >= n) return;   // whole groups of TD_MS lanes
   const int s0 = s0s[slot], e0 = e0s[slot];
+  if (e0 - s0 == 1 && isfinite(dd[s0])) {   // a block of one entry is its own eigenvalue
+    if (l == 0) T.lam[slot] = dd[s0];
+    return;
+  }
   const int target = e0 - slot;   // (slot - s0 + 1)-th largest = target-th smallest
   double lo = 0.0, hi = 0.0, emax2 = 0.0;
   for (int i = s0 + l; i < e0; i += TD_MS) {
@@ -1068,7 +1100,7 @@ __global__ void __launch_bounds__(TD_FIN)
 td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, int k, double cluster_rel,
                   double *workall) {
   __shared__ double dd[MAX_N], ee[MAX_N], lam[MAX_N], w[MAX_N];
-  __shared__ int slot_of[MAX_N];
+  __shared__ int slot_of[MAX_N], s0_of[MAX_N], e0_of[MAX_N];   // by rank: slot, bounds of its block
   __shared__ int kk_s;
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   double *work = td_work(workall, n, b);
@@ -1094,6 +1126,8 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
     for (int u = 0; u < n; ++u) rk += (lam[u] > key) || (lam[u] == key && u < slot);
     w[rk] = v;
     slot_of[rk] = slot;
+    s0_of[rk] = T.s0[slot];
+    e0_of[rk] = T.e0[slot];
     wall[size_t(b) * n + rk] = v;
   }
   __syncthreads();
@@ -1184,39 +1218,46 @@ td_vectors_kernel(double *Aall, double *wall, double *Vall, int *status, int n, 
       __syncthreads();
     }
     // Gram-Schmidt in descending order: vector r, normalised, is taken out of
-    // all later ones (vectors of different blocks have disjoint entries)
+    // the later ones of its block (vectors of different blocks have disjoint
+    // entries).  Lane l of a wave holds the entries l mod 64 whatever the block.
     for (int r = 0; r < kk; ++r) {
       double *z = Zv + size_t(r) * n;
+      const int s0 = s0_of[r], i0 = (s0 & ~63) + lane, i1 = e0_of[r];
       double amax = 0.0;
-      for (int i = lane; i < n; i += 64) amax = fmax(amax, fabs(z[i]));
+      for (int i = i0; i < i1; i += 64) amax = fmax(amax, fabs(z[i]));
       amax = wave_max(amax);
       int ex = 0;
       if (amax > 0.0) (void)frexp(amax, &ex);
       double nrm = 0.0;
-      for (int i = lane; i < n; i += 64) {
+      for (int i = i0; i < i1; i += 64) {
         const double x = ldexp(z[i], -ex);
         nrm += x * x;
       }
       nrm = wave_sum(nrm);
       const double inv = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
-      for (int r2 = r + 1 + wave; r2 < kk; r2 += TD_FIN / 64) {
-        double *y = Zv + size_t(r2) * n;
-        double dot = 0.0;
-        for (int i = lane; i < n; i += 64) dot += ldexp(z[i], -ex) * inv * y[i];
-        dot = wave_sum(dot);
-        if (dot != 0.0)
-          for (int i = lane; i < n; i += 64) y[i] -= dot * (ldexp(z[i], -ex) * inv);
+      // this wave's later vectors, every TD_FIN / 64-th, 64 of them looked at together
+      for (int base = r + 1 + wave; base < kk; base += TD_FIN) {
+        const int mine = base + lane * (TD_FIN / 64);
+        for (unsigned long long same = __ballot(mine < kk && s0_of[mine < kk ? mine : r] == s0); same; same &= same - 1) {
+          double *y = Zv + size_t(base + (__ffsll(same) - 1) * (TD_FIN / 64)) * n;
+          double dot = 0.0;
+          for (int i = i0; i < i1; i += 64) dot += ldexp(z[i], -ex) * inv * y[i];
+          dot = wave_sum(dot);
+          if (dot != 0.0)
+            for (int i = i0; i < i1; i += 64) y[i] -= dot * (ldexp(z[i], -ex) * inv);
+        }
       }
       __syncthreads();
       if (wave == r % (TD_FIN / 64))   // nobody reads z in this pass any more
-        for (int i = lane; i < n; i += 64) z[i] = ldexp(z[i], -ex) * inv;
+        for (int i = i0; i < i1; i += 64) z[i] = ldexp(z[i], -ex) * inv;
     }
     __syncthreads();
   }
 }
 
 // Back-transformation z <- H_0 ... H_{n-3} z, one wave per vector, z in
-// registers (entry lane + 64 u), the next reflector loaded during the sum.
+// registers (entry lane + 64 u), the next reflector loaded during the sum.  The
+// reflectors before the first and after the last that is one are left out.
 template <int R>
 __global__ void __launch_bounds__(TD_THREADS)
 td_back_kernel(double *workall, int n) {
@@ -1224,18 +1265,27 @@ td_back_kernel(double *workall, int n) {
   double *work = td_work(workall, n, blockIdx.y);
   const TdScratch T = td_scratch(work + size_t(2) * n * n, n);
   if (r >= *T.kk) return;
+  int first = n, last = -1;
+  for (int base = 0; base < n - 2; base += 64) {
+    const unsigned long long on = __ballot(base + lane < n - 2 && !(T.tau[base + lane] < 0.0));
+    if (on) {
+      if (last < 0) first = base + __ffsll(on) - 1;
+      last = base + 63 - __clzll(on);
+    }
+  }
+  if (last < 0) return;
   double *zg = work + size_t(n) * n + size_t(r) * n;
   double z[R], u[R], un[R];
 #pragma unroll
   for (int q = 0; q < R; ++q) {
     const int i = lane + 64 * q;
     z[q] = i < n ? zg[i] : 0.0;
-    un[q] = i < n ? work[size_t(n - 3) * n + i] : 0.0;
+    un[q] = i < n ? work[size_t(last) * n + i] : 0.0;
   }
-  for (int j = n - 3; j >= 0; --j) {
+  for (int j = last; j >= first; --j) {
 #pragma unroll
     for (int q = 0; q < R; ++q) u[q] = un[q];
-    const double *next = work + size_t(j > 0 ? j - 1 : 0) * n;
+    const double *next = work + size_t(j > first ? j - 1 : first) * n;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
       const int i = lane + 64 * q;

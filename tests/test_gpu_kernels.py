@@ -494,6 +494,49 @@ def test_eigh_top_parity_blocks_stay_exact():
     assert 0 < int(in_b.sum()) < q
 
 
+@pytest.mark.parametrize("n,k", [(161, 12), (300, 300), (640, 25)])
+@pytest.mark.parametrize("kind", ["zero", "diagonal", "runs of zero columns", "blocks of 8"])
+def test_eigh_top_columns_that_are_reduced_already(n, k, kind):
+    """Matrices with columns that are zero below the diagonal, which need no
+    reflector: all of them, runs of them between full blocks (the first and last
+    columns, and the ones on both sides of the order at which the trailing
+    matrix moves to LDS, n - 128), and matrices of many blocks, whose vectors
+    are orthogonalised within their blocks.  Beside a full matrix; bounds as
+    above, and every vector stays within one block."""
+    announce("eigh_top reduced columns", n, k, kind)
+    rng = np.random.default_rng(n + len(kind))
+    A = np.zeros((2, n, n))
+    block = np.arange(n)
+    if kind == "diagonal":
+        A[1] = np.diag(rng.uniform(-1.0, 1.0, n))
+    elif kind == "runs of zero columns":
+        d = rng.uniform(0.0, 1.0, n)
+        d[5:8] = 0.0
+        A[1] = np.diag(d)
+        for lo, hi in ((10, 24), (n - 131, n - 129), (n - 127, n - 60), (n - 20, n - 2)):
+            A[1, lo:hi, lo:hi] = gram_like(hi - lo, hi - lo, lo)
+            block[lo:hi] = lo
+    elif kind == "blocks of 8":
+        for lo in range(0, n, 8):
+            hi = min(lo + 8, n)
+            A[1, lo:hi, lo:hi] = random_symmetric(hi - lo, lo)
+            block[lo:hi] = lo
+    A[0] = gram_like(n, 40, 60)
+    w, V, kk = _eigh_top(A, k, 1e-10)
+    for b in range(2):
+        ref = np.linalg.eigvalsh(A[b])[::-1]
+        nrm = np.linalg.norm(A[b])
+        assert np.max(np.abs(w[b] - ref)) <= 1e-13 * nrm
+        q = int(kk[b])
+        assert k <= q <= n and (q == n if kind == "zero" and b else True)
+        Vk = V[b][:, :q]
+        assert np.all(V[b][:, q:] == 0.0)
+        assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
+        assert np.max(np.abs(A[b] @ Vk - Vk * w[b][:q])) <= 1e-12 * nrm
+    for v in V[1][:, : int(kk[1])].T:
+        assert len(set(block[v != 0.0])) == 1
+
+
 @pytest.mark.parametrize("n", [161, 300])
 @pytest.mark.parametrize("bad", ["all nan", "all inf", "one nan"])
 def test_eigh_top_matrix_that_is_not_finite(n, bad):
