@@ -497,9 +497,15 @@ __device__ inline int split_swz(int row) { return int((0x1320u >> (4 * ((row >> 
 // sums between the first MFMAs of the next one.
 //
 // DMA false serves operands that do not start on 16 bytes, which loads straight
-// to LDS are not known to take: a tile travels through registers, loaded after
-// the barrier of the tile two before it and stored to LDS (two stages) right
-// before the barrier that publishes it.  Same products in the same order.
+// to LDS are not known to take: a tile travels through registers.  In the first
+// half of a tile the next one is stored to LDS (two stages) block by block between
+// the MFMAs, each block's register right away loaded with the tile after that.
+// Same products in the same order.  Bound by the second 64 bytes that most rows
+// of a tile touch, hence tiles as large as the registers allow.  Operands 2 and 8
+// bytes off, TFLOP/s: BF16x6 10112^2 x 25056 125 and 141, BF16x3 10240^2 x 25056 246
+// and 277 (188 and 431 aligned), against 101 and 115, 212 and 267 with the stores
+// in a block before the barrier, 128 x 128 tiles and the loads of a tile moved by
+// the compiler behind the MFMAs that should cover them.
 //
 // Measured against the kernel before (loads through registers, all fragments
 // of a tile read right before its MFMAs), TFLOP/s of the product:
@@ -557,19 +563,16 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
 #pragma unroll
     for (int q = 0; q < PERT; ++q) dma1(uint64_t(kt) * RB, lds0 + stage * STAGE, q);
   };
-  // the same block into a register, and the tile in registers into a stage
+  // the same block into a register, and from there into a stage
   u32x4 rg[DMA ? 1 : PERT];
   auto fetch1 = [&](uint64_t kb, int q) {
     const int p = q / (LA + LB), u = q % (LA + LB);
     rg[q] = *reinterpret_cast<const u32x4_any *>((u < LA ? pa[p][u] : pb[p][u - LA]) + kb);
   };
-  auto put = [&](uint32_t stage) {
-#pragma unroll
-    for (int q = 0; q < PERT; ++q) {
-      const int p = q / (LA + LB), u = q % (LA + LB);
-      const int at = p * PLANE + (u < LA ? (wave * LA + u) * 1024 : BM * RB + (wave * LB + u - LA) * 1024);
-      *reinterpret_cast<u32x4 *>(smem + stage * STAGE + at + lane * 16) = rg[q];
-    }
+  auto put1 = [&](uint32_t stage, int q) {
+    const int p = q / (LA + LB), u = q % (LA + LB);
+    const int at = p * PLANE + (u < LA ? (wave * LA + u) * 1024 : BM * RB + (wave * LB + u - LA) * 1024);
+    *reinterpret_cast<u32x4 *>(smem + stage * STAGE + at + lane * 16) = rg[q];
   };
   const int fro = (g ^ split_swz(r16)) << 4;
   const int aoff = (wm * TM + r16) * RB + fro, boff = BM * RB + (wn * TN + r16) * RB + fro;
@@ -629,26 +632,34 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   auto body = [&](uint32_t kt, auto par, auto fold) {
     constexpr int P = decltype(par)::value;
     constexpr auto PN = std::integral_constant<int, P ^ 1>{};
+    constexpr int NR = PL * (HM + FN);        // LDS reads of the second phase
+    constexpr int DS = NM / PERT;             // MFMAs per load
+    static_assert(DS >= 1 && NM > 4, "phase too short");
+    auto ahead = [&] {   // bytes into a row; past the end: the last tile again, never read
+      const uint32_t kn = kt + NST < last ? kt + NST : last;
+      return uint64_t(kn) * RB;
+    };
     mfma(par, I0, IH, fold, [&](int n) {
-      if (n < PL * HM) {
-        aload1(cur, HM, n);
-        phase();
+      bool any = n < PL * HM;
+      if (n < PL * HM) aload1(cur, HM, n);
+      if constexpr (!DMA) {
+        if (n % DS == DS / 2 && n / DS < PERT) {
+          put1(cur ^ 1, n / DS);
+          fetch1(ahead(), n / DS);
+          any = true;
+        }
       }
+      if (any) phase();
     });
     phase();
     // this wave's part of tile kt + 1 has landed; past the barrier all of it
     // has, and no wave reads the stage of tile kt any more
     const uint32_t nxt = cur + 1 == NST ? 0 : cur + 1;
     if constexpr (DMA) wait_vm<(NST - 2) * PERT>();
-    else put(nxt);
     barrier();
     phase();
-    const uint32_t kn = kt + NST < last ? kt + NST : last;   // past the end: the last tile again, never read
-    const uint64_t kb = uint64_t(kn) * RB;
+    const uint64_t kb = ahead();
     const uint32_t base = lds0 + cur * STAGE;
-    constexpr int NR = PL * (HM + FN);        // LDS reads of the phase
-    constexpr int DS = NM / PERT;             // MFMAs per load
-    static_assert(DS >= 1 && NM > 4, "phase too short");
     mfma(par, IH, IF, fold, [&](int n) {
       bool any = false;
 #pragma unroll
@@ -657,10 +668,11 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
         else aload1(nxt, 0, q - PL * FN);
         any = true;
       }
-      if (n % DS == DS / 2 && n / DS < PERT) {
-        if constexpr (DMA) dma1(kb, base, n / DS);
-        else fetch1(kb, n / DS);
-        any = true;
+      if constexpr (DMA) {
+        if (n % DS == DS / 2 && n / DS < PERT) {
+          dma1(kb, base, n / DS);
+          any = true;
+        }
       }
       if (any) phase();
     });
@@ -674,7 +686,8 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
   } else {
 #pragma unroll
     for (int q = 0; q < PERT; ++q) fetch1(0, q);
-    put(0);
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) put1(0, q);
 #pragma unroll
     for (int q = 0; q < PERT; ++q) fetch1(last > 0 ? RB : 0, q);
   }
@@ -684,15 +697,28 @@ gemm_split_kernel(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B
 #pragma unroll
   for (int q = 0; q < PL * FN; ++q) bload1(0, I0, q);
   constexpr auto FD = std::integral_constant<bool, F64>{};
-  for (uint32_t kt = 0;; kt += 4) {
-    body(kt, I0, FD);
-    if (kt == last) break;
-    body(kt + 1, I1, NO);
-    if (kt + 1 == last) break;
-    body(kt + 2, I0, NO);
-    if (kt + 2 == last) break;
-    body(kt + 3, I1, NO);
-    if (kt + 3 == last) break;
+  if constexpr (DMA) {
+    for (uint32_t kt = 0;; kt += 4) {
+      body(kt, I0, FD);
+      if (kt == last) break;
+      body(kt + 1, I1, NO);
+      if (kt + 1 == last) break;
+      body(kt + 2, I0, NO);
+      if (kt + 2 == last) break;
+      body(kt + 3, I1, NO);
+      if (kt + 3 == last) break;
+    }
+  } else {   // four tiles without an exit, past which the compiler would move their loads and reads
+    uint32_t kt = 0;
+    for (; kt + 4 <= ktiles; kt += 4) {
+      body(kt, I0, FD);
+      body(kt + 1, I1, NO);
+      body(kt + 2, I0, NO);
+      body(kt + 3, I1, NO);
+    }
+    if (kt < ktiles) body(kt, I0, FD);
+    if (kt + 1 < ktiles) body(kt + 1, I1, NO);
+    if (kt + 2 < ktiles) body(kt + 2, I0, NO);
   }
   wait_vm<0>();
 #pragma unroll
@@ -984,8 +1010,7 @@ bool split_small(uint64_t M, uint64_t N, uint32_t nb, uint64_t big, uint64_t sma
 
 // Whether every row of both split-BF16 operands starts on 16 bytes (the rows
 // of a plane and the planes are multiples of that apart: check_gemm).  Others
-// go through registers, at 60 % of the rate: BF16x6 10112^2 x 25056 115 against
-// 188 TFLOP/s, BF16x3 10240^2 x 25056 267 against 431.
+// go through registers, at 60 to 75 % of the rate.
 bool split_direct(const void *A, const void *Bt, uint32_t nb, uint64_t batch_a, uint64_t batch_b) {
   const bool bases = (reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(Bt)) % 16 == 0;
   return bases && (nb == 1 || (batch_a * 2 % 16 == 0 && batch_b * 2 % 16 == 0));
@@ -1020,12 +1045,20 @@ void gemm_nt(int prec, const void *A, const void *Bt, void *C, uint64_t M, uint6
       return;
     case 2:
       if (!check_gemm<2>(256, 256, 32, C, M, N, K, lda, ldb, ldc, accum, st, 1, nb, batch_a, batch_b, batch_c)) return;
+      if (!split_direct(A, Bt, nb, batch_a, batch_b)) {
+        // 128 x 256 tiles once they fill three quarters of the CUs, against 128 x 128 ones:
+        // 2048^2 x 4096 211 and 249 TFLOP/s, 3072 x 2048 x 4096 290 and 230, 4096^2 x 6400 351 and 291
+        if ((M / 128) * (N / 256) * nb >= 192)
+          launch_split<2, 128, 256, 2, 4, 2, 0, false>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
+                                                       batch_c);
+        else
+          launch_split<2, 128, 128, 2, 2, 2, 0, false>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
+                                                       batch_c);
+        return;
+      }
       // four waves of 64 x 64, two workgroups per CU, while the 256 x 256 tiles leave CUs idle in
       // their last round: 2048^2 x 8192 338 against 186 TFLOP/s, 10240^2 x 25056 290 against 407
-      if (!split_direct(A, Bt, nb, batch_a, batch_b))
-        launch_split<2, 128, 128, 2, 2, 2, 0, false>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b,
-                                                     batch_c);
-      else if (split_small(M, N, nb, 256, 128, 290.0 / 407.0))
+      if (split_small(M, N, nb, 256, 128, 290.0 / 407.0))
         launch_split<2, 128, 128, 2, 2, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);
       else
         launch_split<2, 256, 256, 2, 4, 2, 0>(A, Bt, C, M, N, K, lda, ldb, ldc, accum, st, nb, batch_a, batch_b, batch_c);

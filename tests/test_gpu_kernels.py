@@ -647,3 +647,13 @@ def test_eigh_top_several_chunks_at_large_orders(n, k, rank):
     assert np.all(V[0][:, q:] == 0.0)
     assert np.allclose(Vk.T @ Vk, np.eye(q), atol=1e-12)
     assert np.max(np.abs(A @ Vk - Vk * w[0][:q])) < 1e-12 * nrm
+
+
+@pytest.mark.parametrize("precision,M,N", [("bf16x3", 256, 256), ("bf16x3", 3072, 2048), ("bf16x3", 2048, 3328),
+                                           ("bf16x6", 256, 128)])
+@pytest.mark.parametrize("K", [32, 64, 96, 128, 192, 224, 256, 352])
+def test_gemm_split_through_registers(precision, M, N, K):
+    """Operands off 16 bytes in both tiles of the BF16x3 kernel that takes them
+    (the larger from 192 tiles on) and that of BF16x6: every remainder of K
+    behind groups of four tiles, bit for bit as aligned operands."""
+    test_gemm_split_operands_off_16_bytes(precision, M, N, K, 1, 4)
