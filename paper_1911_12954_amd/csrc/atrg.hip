@@ -500,7 +500,7 @@ ts_gram_kernel(const double *__restrict__ Y, int64_t m, int k, int64_t rpw, doub
 // accumulation registers, and the Gram stays a launch of its own.
 constexpr int TSM_WAVES = 4, TSM_GRID = 256, TSM_GRAM_MAX = 96;
 
-template <int NB, bool GRAM, bool PAIRS>   // NB = ceil(k / 16); PAIRS: k even, 16-byte loads
+template <int NB, bool GRAM, bool PAIRS>   // NB = ceil(k / 16); PAIRS: k even, Y on 16 bytes, 16-byte loads
 __global__ void __launch_bounds__(64 * TSM_WAVES, NB <= 4 ? 2 : 1)
 ts_mul_kernel(const double *__restrict__ Y, int64_t m, int k, const double *__restrict__ R, double *__restrict__ Q,
               double *__restrict__ part) {
@@ -635,7 +635,7 @@ void launch_ts_mul(const double *Y, int64_t m, int k, const double *R, double *Q
   auto launch = [&](auto blocks) {
     constexpr int NB = decltype(blocks)::value;
     constexpr bool G = 16 * NB <= TSM_GRAM_MAX;
-    if (k % 2 == 0) {
+    if (k % 2 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
       if (G && part) launch_ts_mul_as<NB, G, true>(Y, m, k, R, Q, part, st);
       else launch_ts_mul_as<NB, false, true>(Y, m, k, R, Q, part, st);
     } else {

@@ -1130,8 +1130,7 @@ void gemm_cols_f64(const ColsPlan &plan, const double *A, uint64_t lda, const do
   TRG_REQUIRE(s.M >= 1 && s.N >= 1 && s.K >= 1 && s.M < lim && s.N < lim && s.K < lim && s.k1 >= 1 && s.n1 >= 1 &&
                   s.k1 <= s.K && s.n1 <= s.N,
               "gemm_cols: bad shape");
-  TRG_REQUIRE(lda % 2 == 0 && lda >= (s.K + 15) / 16 * 16 && reinterpret_cast<uintptr_t>(A) % 16 == 0,
-              "gemm_cols: bad left operand");
+  TRG_REQUIRE(lda % 2 == 0 && lda >= (s.K + 15) / 16 * 16, "gemm_cols: bad left operand");
   TRG_REQUIRE(plan.splits >= 1 && uint64_t(plan.splits - 1) * plan.ktiles < (s.K + 15) / 16 &&
                   uint64_t(plan.splits) * plan.ktiles >= (s.K + 15) / 16 && (plan.splits == 1 || part),
               "gemm_cols: bad plan");

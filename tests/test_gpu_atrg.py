@@ -237,3 +237,41 @@ def test_impure_fp32_contraction_error():
     err = {k: abs(a[k] - b[k]) / abs(a[k]) for k in ("f", "E", "M")}
     print(f"[atrg impure fp32] rel err {err}", flush=True)
     assert err["f"] < 1e-6 and err["E"] < 1e-4 and err["M"] < 1e-3
+
+
+@pytest.mark.parametrize("method,precision,dcut", [("atrg", "fp64", 5), ("atrg", "fp32", 4), ("hotrg", "fp64", 4),
+                                                   ("hotrg", "fp32", 3), ("hotrg", "bf16x3", 3), ("hotrg", "bf16x6", 3)])
+def test_allocator_that_hands_out_multiples_of_8_bytes(monkeypatch, method, precision, dcut):
+    """The allocator of a program may hand out memory at any multiple of 8
+    bytes: every value equals that with aligned buffers, bit for bit."""
+    need_gpu()
+    from paper_1911_12954_amd import trg
+    announce("allocator off 16 bytes", method, precision, dcut)
+    make = trg._torch_allocator
+
+    def off_by_8(stream_ptr):
+        alloc, free = make(stream_ptr)
+
+        @trg.L.ALLOC_FN
+        def alloc8(nbytes, user):
+            p = alloc(nbytes + 8, user)
+            return p + 8 if p else None
+
+        @trg.L.FREE_FN
+        def free8(ptr, user):
+            free(ptr - 8, user)
+
+        alloc8.keep, free8.keep = alloc, free
+        return alloc8, free8
+
+    def run():
+        c = trg.trg_init_ising(0.1497, 1e-3, 3, dcut=dcut, method=method, precision=precision, impure=("E",))
+        for i in range(5):
+            (c.atrg_step if method == "atrg" else c.hotrg_step)(i % 3, dcut)
+        out = [c.free_energy(), c.impure_energy(), c.indicator_x(0)] + [r.ln_c for r in c.step_log()]
+        c.close()
+        return out
+
+    aligned = run()
+    monkeypatch.setattr(trg, "_torch_allocator", off_by_8)
+    assert run() == aligned
